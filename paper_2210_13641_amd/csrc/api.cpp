@@ -447,7 +447,9 @@ int nsl_train_step(nsl_mapper* m, const nsl_field* f, float* params, float* grad
   HIP_TRY(mark(0), "profile event");
   // with the encoding kept, the encoding kernel also counts the
   // table-gradient records per bin and unit
-  const bool counted = c->keep_encoding != 0 && b.plan.bl.max_level_bins <= kEncodeLevelBins;
+  // (unless the plan takes no records)
+  const bool counted =
+      c->keep_encoding != 0 && b.plan.direct_parts == 0 && b.plan.bl.max_level_bins <= kEncodeLevelBins;
   // the mixed step prepares (FP16 table copy, gradient clearing,
   // overflow-flag reset, BF16 operands) and counts the candidates' samples in
   // one launch; profiled steps keep them apart to time the two phases
@@ -661,8 +663,9 @@ int nsl_field_bwd(const nsl_field* f, const float* params, const float* xn, cons
   FieldArgs fa{params, w.wprep, f->lv};
   HIP_TRY(field_backward(f->shape, fa, src, kBwdBlocks, dsigma, drgb, w.rec, w.partial, f->wo, grads, st),
           "field backward");
-  HIP_TRY(field_dw_reduce(f->shape, w.partial, kBwdBlocks, f->wo, grads, nullptr, nullptr, st), "weight gradient");
-  HIP_TRY(bin_scatter(w.plan, w.rec, src, f->lv, false, false, grads, nullptr, st), "table gradient");
+  const WeightSum wsum{f->shape, w.partial, kBwdBlocks, f->wo, grads, nullptr, LossSum{}};
+  HIP_TRY(bin_scatter(w.plan, w.rec, src, f->lv, false, false, grads, nullptr, st, false, &wsum),
+          "table and weight gradients");
   return NSL_OK;
 }
 
@@ -701,8 +704,9 @@ int nsl_field_bwd_mixed(const nsl_field* f, const void* shadow, const float* xn,
   w.rec.de_bf16 = true;  // the mixed backward stores dL/de as BF16 pairs
   HIP_TRY(mixed_backward(f->shape, f->lv, shadow, src, kBwdBlocks, dsigma, drgb, w.rec, w.partial, f->wo, grads, st),
           "field backward (mixed)");
-  HIP_TRY(field_dw_reduce(f->shape, w.partial, kBwdBlocks, f->wo, grads, nullptr, nullptr, st), "weight gradient");
-  HIP_TRY(bin_scatter(w.plan, w.rec, src, f->lv, true, false, grads, nullptr, st), "table gradient");
+  const WeightSum wsum{f->shape, w.partial, kBwdBlocks, f->wo, grads, nullptr, LossSum{}};
+  HIP_TRY(bin_scatter(w.plan, w.rec, src, f->lv, true, false, grads, nullptr, st, false, &wsum),
+          "table and weight gradients");
   return NSL_OK;
 }
 

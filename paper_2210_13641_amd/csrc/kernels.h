@@ -95,6 +95,7 @@ struct BinPlan {
   int nbins, nunits, levels, stride, max_chunks;
   uint32_t chunk;  // corner additions per reduce workgroup: kChunk, or fewer for tables of few bins
   int64_t max_records;
+  int direct_parts;  // > 0: every level fits one bin and the samples are summed in this many parts, without records
   BinLevels bl;
 };
 // Records per reduce workgroup for FP32 or BF16 (paired) records, and whether
