@@ -538,7 +538,7 @@ def depth_covariance(C, Et, P, inv_depth=None, want_sigma_d=True):
     sT = torch.empty(c, c, dtype=torch.float64, device=dev)
     sd = torch.empty(p, dtype=torch.float64, device=dev) if want_sigma_d else None
     dv = torch.empty(p, dtype=torch.float32, device=dev) if inv_depth is not None else None
-    st = torch.zeros(1, dtype=torch.int32, device=dev)
+    st = torch.empty(1, dtype=torch.int32, device=dev)   # always written
     _check(_lib.nsl_depth_covariance(c, p, _dev(C, torch.float64), _dev(Et, torch.float64), _dev(P, torch.float64),
                                      _ptr(inv_depth), _ptr(sT), _ptr(sd), _ptr(dv), _ptr(st), _ptr(ws), ws.numel(),
                                      _stream()))

@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 import workloads as W
+from oracle import covariance as ocov
 from oracle import field as ofield
 from parity import check_mag
 
@@ -46,3 +47,34 @@ def test_scatter_of_single_bin_levels(nsl, gpu, spec, S):
             check_mag(f"single-bin scatter p{prec}", g[:nt], gt + before, gtm + before, tol)
             assert np.all(g[nt:] == 0.5)
             assert np.all(g[:nt][gtm == 0] == before)
+
+
+@pytest.mark.parametrize("c,p", [(1, 1), (15, 63), (16, 64), (17, 257), (48, 300), (60, 65), (60, 70001)])
+def test_covariance_at_tile_edges(nsl, gpu, c, p):
+    """nsl_depth_covariance around the 16x16 tiles, the 16-pixel groups, the
+    256-pixel chunks and the 256 partial sums, for any c (not only whole
+    keyframes), against the oracle in FP64: 1e-9, as the whole-window test."""
+    import torch
+    rng = np.random.default_rng(100 * c + p)
+    E = rng.normal(size=(c, p))
+    P = rng.uniform(0.5, 20.0, size=p)
+    A = rng.normal(size=(c, c))
+    C = (E / P) @ E.T + A @ A.T + 3.0 * np.eye(c)         # H_T = A A^T + 3 I
+    d = rng.uniform(0.2, 2.0, size=p)
+    sT, sd, dv, st = nsl.depth_covariance(_t(torch, gpu, C), _t(torch, gpu, E.T), _t(torch, gpu, P), _t(torch, gpu, d))
+    assert int(st.item()) == 0
+    oT, od = ocov.marginals(C, E, P)
+    got = sT.cpu().numpy()
+    assert np.allclose(got, oT, rtol=1e-9, atol=1e-12 * np.abs(oT).max())
+    assert np.array_equal(got, got.T)
+    assert np.allclose(sd.cpu().numpy(), od, rtol=1e-9)
+    assert np.allclose(dv.cpu().numpy(), ocov.depth_variance(od, d), rtol=1e-6)
+
+
+def test_covariance_refuses_a_negative_depth_hessian(nsl, gpu):
+    """A pixel whose P is negative makes the window indefinite: status 1 and NaN."""
+    import torch
+    C, E, P, d = W.ba_window(seed=5, n_kf=2, h=3, w=4)
+    P[7] = -P[7]
+    sT, sd, _, st = nsl.depth_covariance(_t(torch, gpu, C), _t(torch, gpu, E.T), _t(torch, gpu, P), _t(torch, gpu, d))
+    assert int(st.item()) == 1 and bool(torch.isnan(sT).all()) and bool(torch.isnan(sd).all())
