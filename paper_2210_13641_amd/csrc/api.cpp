@@ -1009,8 +1009,7 @@ static int render_image(const nsl_field* f, const float* params, const float* po
   r.var_z = var;
   r.opacity = opacity;
   HIP_TRY(store_request(&r, pose, intr, dev_req, st), "store request");
-  const int n_tiles = (H * W + NSL_RENDER_TILE - 1) / NSL_RENDER_TILE;
-  HIP_TRY(render_tiles(f->shape, f->lv, f->box, dev_req, 1, nullptr, n_tiles, render_params(c), st), "render");
+  HIP_TRY(render_one(f->shape, f->lv, f->box, dev_req, H, W, render_params(c), st), "render");
   return NSL_OK;
 }
 

@@ -454,103 +454,181 @@ __global__ __launch_bounds__(kFieldBwdWaves * kWave, 1) void field_bwd_kernel(Fi
 
 
 // ---------------------------------------------------------------------------
-// Fused rendering: one wave per ray, 16 consecutive samples of the ray per
-// MFMA tile, compositing by a row scan of the 16 sample lanes, and an early
-// exit once the transmittance left for the ray is below stop_T.
+// Fused rendering: a workgroup takes 16 pixels, the columns of the MFMA tiles,
+// and its four waves consecutive samples of all 16 rays, 16 a round: wave w
+// evaluates samples 16 q + 4 w + (0..3) of every ray, one tile each, and passes
+// their densities and colours through LDS so that lane group g holds tile g's;
+// then every lane composites one sample of one ray.  The waves exchange the optical depths
+// of the round through LDS (one barrier a round), and the rays leave together,
+// once the transmittance left for each is below stop_T.
+//
+// The gathers bound it.  Samples of one ray are several cells apart at the
+// fine levels, so a tile of 16 samples of a ray touched four lines of the
+// table per sample and level; 16 neighbouring pixels at one depth share most
+// of them.  And the samples of 16 rays spread over four waves keep a small
+// image (160x120: 1200 workgroups) from leaving one wave a SIMD to wait on its
+// own loads.  Against one ray a wave at a time, its samples 16 a tile: 640x480
+// pixels of 64 samples at paper scale 11.3 -> 4.3 ms, 160x120 of 32 samples
+// with the tiny field 105 -> 45 us (compositing four tiles at once, on every
+// lane instead of the 16 that hold a tile's outputs, 5.8 -> 4.3 ms of it).
 // ---------------------------------------------------------------------------
+constexpr int kRenderWaves = 4;
+constexpr int kRenderThreads = kRenderWaves * kWave;
+constexpr int kRenderRound = 4 * kRenderWaves;  // samples of a round
 
-// The weight and t of every composited sample wait in LDS (per wave, the
-// samples of its current ray) for the second pass of V*, so a ray may take up
-// to kRenderMaxSamples samples.
+// LDS of the weights of the 16 rays' samples, which wait for the second pass
+// of V* (d* first).
+constexpr int render_rounds(int n_samples) { return (n_samples + kRenderRound - 1) / kRenderRound; }
+constexpr size_t render_lds(int n_samples) { return (size_t)render_rounds(n_samples) * kRenderRound * 16 * sizeof(float); }
+
+// Workgroup -> pixels: with tiles, workgroup b of nblocks takes the group b % 4
+// of 16 consecutive pixels of tile b / 4; without, the 4x4 block b of request
+// 0's image (blocks_x blocks a row).  The grid is two-dimensional because the
+// largest images have more threads than one dimension of a launch may.
 template <class N>
-__global__ __launch_bounds__(256) void render_kernel(LevelInfo lv, Aabb box, const nsl_render_request* __restrict__ reqs,
-                                                     int n_req, const nsl_render_tile* __restrict__ tiles,
-                                                     RenderParams rp) {
+__global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(3))) void render_kernel(
+    LevelInfo lv, Aabb box, const nsl_render_request* __restrict__ reqs, int n_req,
+    const nsl_render_tile* __restrict__ tiles, uint32_t nblocks, int blocks_x, RenderParams rp) {
   __shared__ __attribute__((aligned(16))) float Af[N::FWD_FLOATS];
-  extern __shared__ float2 wt_lds[];  // [4 waves][16 * ntiles] (w, t), written by the lanes of row 0
-  nsl_render_tile tile;
+  __shared__ float4 tile_out[kRenderWaves][4][16];  // (o_0, z) of a wave's four tiles
+  __shared__ float tau_of[2][kRenderRound][16];
+  __shared__ float sums[kRenderWaves][5][16];
+  __shared__ float v_sums[kRenderWaves][16];
+  extern __shared__ float w_lds[];  // [sample][16]
+  const int wave = threadIdx.x / kWave, lane = lane_id(), g = lane >> 4, jc = lane & 15;
+  // consecutive workgroups go round the 8 XCDs: of each 512 blocks an XCD
+  // takes 64 consecutive ones, whose lines it finds in its L2 (4.33 -> 4.24 ms
+  // for 640x480 at paper scale)
+  uint32_t blk = blockIdx.y * gridDim.x + blockIdx.x;
+  if (blk >= nblocks) return;
+  if ((blk | 511u) < nblocks) blk = (blk & ~511u) | ((blk & 7u) << 6) | ((blk >> 3) & 63u);
+  int req = 0, u, v;
+  bool in;
   if (tiles) {
-    tile = tiles[blockIdx.x];
+    const nsl_render_tile tile = tiles[blk / 4];
+    req = tile.request;
+    if (req < 0 || req >= n_req) return;
+    const int npix = reqs[req].H * reqs[req].W;
+    const int first = max(tile.first_pixel, 0) + 16 * (int)(blk % 4);
+    const int last = min(tile.first_pixel + min(tile.n_pixels, NSL_RENDER_TILE), npix);
+    if (first >= last) return;
+    in = first + jc < last;
+    const int px = in ? first + jc : first;
+    v = px / reqs[req].W;
+    u = px - v * reqs[req].W;
   } else {
-    tile.request = 0;
-    tile.first_pixel = blockIdx.x * NSL_RENDER_TILE;
-    tile.n_pixels = NSL_RENDER_TILE;
+    const int by = (int)blk / blocks_x, bx = (int)blk - by * blocks_x;
+    u = 4 * bx + (jc & 3);
+    v = 4 * by + (jc >> 2);
+    in = u < reqs[0].W && v < reqs[0].H;
+    u = min(u, reqs[0].W - 1);
+    v = min(v, reqs[0].H - 1);
   }
-  if (tile.request < 0 || tile.request >= n_req) return;
-  const nsl_render_request& rq = reqs[tile.request];
-  const int npix = rq.H * rq.W;
-  const int first = max(tile.first_pixel, 0);
-  const int last = min(tile.first_pixel + min(tile.n_pixels, NSL_RENDER_TILE), npix);
-  if (first >= last) return;
+  const nsl_render_request& rq = reqs[req];
   load_operands<N>(Af, reinterpret_cast<const float*>(rq.prepared), N::FWD_FLOATS);
   __syncthreads();
-  const int wave = threadIdx.x / kWave, lane = lane_id(), g = lane >> 4, jc = lane & 15;
   LaneLevels<N> ll;
   lane_levels<N>(lv, g, ll);
-  const int ntiles = (rp.n_samples + 15) / 16;
-  float2* wt = wt_lds + (size_t)wave * 16 * ntiles;
-  for (int px = first + wave; px < last; px += 4) {
-    const int v = px / rq.W, u = px - v * rq.W;
-    float o[3], d[3], s;
-    camera_ray(rq.pose, rq.intr, u, v, o, d, s);
-    Acts<N> act;
-    sh_lane<N>(d, g, act.sh);
-    float carry = 0.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f, D = 0.0f, A = 0.0f;
-    int used = 0;  // tiles composited (the rest of the ray is not)
-    wave_lds_fence();  // the previous ray's V* reads are done before this ray's writes
-    for (int ti = 0; ti < ntiles; ++ti) {
-      const int j = ti * 16 + jc;
-      const bool valid = j < rp.n_samples;
-      float t;
-      {
+  float o[3], d[3], s;
+  camera_ray(rq.pose, rq.intr, u, v, o, d, s);
+  Acts<N> act;
+  sh_lane<N>(d, g, act.sh);
+  auto t_of = [&](int j) {
 #pragma clang fp contract(off)
-        t = rp.t_near + ((float)j + 0.5f) * rp.dt;
-      }
+    return rp.t_near + ((float)j + 0.5f) * rp.dt;
+  };
+  float carry = 0.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f, D = 0.0f, A = 0.0f;
+  bool done = !in;  // this lane's ray has stopped
+  const int rounds = render_rounds(rp.n_samples), mine = 4 * wave + g;  // this lane's sample of a round
+  int q = 0;
+  for (; q < rounds; ++q) {
+    for (int k = 0; k < 4; ++k) {
+      const int j = q * kRenderRound + 4 * wave + k;
+      if (j >= rp.n_samples) break;
+      const float t = t_of(j);
       float xn[3];
 #pragma unroll
       for (int i = 0; i < 3; ++i) xn[i] = normalise_axis(pos_axis(o[i], d[i], t), box.lo[i], box.inv[i]);
       encode<N>(rq.params, lv.table_mask, ll, xn, act.e);
       mlp_fwd<N>(Af, lane, act);
-      // lanes of row 0 hold sample jc's density and colour
-      const float tau = valid ? expf(act.o[0]) * rp.dt : 0.0f;
-      const float incl = row_incl_scan(tau);
-      const float T = expf(-(carry + (incl - tau)));
-      const bool on = valid && !(rp.stop_T > 0.0f && T < rp.stop_T);
-      const float w = on ? T * -expm1f(-tau) : 0.0f;
-      if (g == 0) wt[j] = make_float2(w, t);
-      used = ti + 1;
-      C0 += w * sigmoidf(act.z[0]);
-      C1 += w * sigmoidf(act.z[1]);
-      C2 += w * sigmoidf(act.z[2]);
+      // lanes of row 0 hold pixel jc's density and colour
+      if (g == 0) tile_out[wave][k][jc] = make_float4(act.o[0], act.z[0], act.z[1], act.z[2]);
+    }
+    wave_lds_fence();
+    const float4 oz = tile_out[wave][g][jc];
+    const int j = q * kRenderRound + mine;
+    const bool valid = j < rp.n_samples;
+    const float t = t_of(j);
+    const float tau = valid ? expf(oz.x) * rp.dt : 0.0f;
+    float(*tw)[16] = tau_of[q & 1];
+    tw[mine][jc] = tau;
+    __syncthreads();
+    float before = 0.0f, round = 0.0f;  // optical depth of the round before this sample, and of all of it
+#pragma unroll
+    for (int i = 0; i < kRenderRound; ++i) {
+      if (i == mine) before = round;
+      round += tw[i][jc];
+    }
+    const float T = expf(-(carry + before));
+    carry += round;
+    const bool on = valid && !done && !(rp.stop_T > 0.0f && T < rp.stop_T);
+    const float w = on ? T * -expm1f(-tau) : 0.0f;
+    w_lds[j * 16 + jc] = w;
+    if (on) {
+      C0 += w * sigmoidf(oz.y);
+      C1 += w * sigmoidf(oz.z);
+      C2 += w * sigmoidf(oz.w);
       D += w * t;
       A += w;
-      carry += __shfl(incl, 15, kWave);
-      if (rp.stop_T > 0.0f && expf(-carry) < rp.stop_T) break;
     }
-    C0 = row_sum(C0);
-    C1 = row_sum(C1);
-    C2 = row_sum(C2);
-    D = row_sum(D);
-    A = row_sum(A);
-    // V* = sum w (t - d*)^2, d* of row 0, over the composited samples
-    const float Dr = __shfl(D, 0, kWave);
-    wave_lds_fence();
-    float V = 0.0f;
-    for (int i = lane; i < 16 * used; i += kWave) {
-      const float2 p = wt[i];
-      V += p.x * (p.y - Dr) * (p.y - Dr);
-    }
-#pragma unroll
-    for (int o2 = 1; o2 < kWave; o2 <<= 1) V += __shfl_xor(V, o2, kWave);
-    if (lane == 0) {
-      rq.rgb[3 * (size_t)px] = C0;
-      rq.rgb[3 * (size_t)px + 1] = C1;
-      rq.rgb[3 * (size_t)px + 2] = C2;
-      rq.depth_z[px] = D / s;
-      rq.var_z[px] = V / (s * s);
-      if (rq.opacity) rq.opacity[px] = A;
+    if (rp.stop_T > 0.0f) {
+      done |= expf(-carry) < rp.stop_T;
+      if (__ballot(!done) == 0ull) {  // every wave holds the same sums, so all leave in one round
+        ++q;
+        break;
+      }
     }
   }
+  {
+    float s5[5] = {C0, C1, C2, D, A};
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+      s5[i] += __shfl_xor(s5[i], 16, kWave);
+      s5[i] += __shfl_xor(s5[i], 32, kWave);
+      if (g == 0) sums[wave][i][jc] = s5[i];
+    }
+  }
+  __syncthreads();
+  // V* = sum w (t - d*)^2 over the composited samples
+  float Dr = 0.0f;
+#pragma unroll
+  for (int w = 0; w < kRenderWaves; ++w) Dr += sums[w][3][jc];
+  float V = 0.0f;
+  for (int j = (int)threadIdx.x / 16; j < q * kRenderRound; j += kRenderThreads / 16) {
+    const float e = t_of(j) - Dr;
+    V += w_lds[j * 16 + jc] * e * e;
+  }
+  V += __shfl_xor(V, 16, kWave);
+  V += __shfl_xor(V, 32, kWave);
+  if (g == 0) v_sums[wave][jc] = V;
+  __syncthreads();
+  if (threadIdx.x >= 16 || !in) return;
+  V = C0 = C1 = C2 = A = 0.0f;
+#pragma unroll
+  for (int w = 0; w < kRenderWaves; ++w) {
+    C0 += sums[w][0][jc];
+    C1 += sums[w][1][jc];
+    C2 += sums[w][2][jc];
+    A += sums[w][4][jc];
+    V += v_sums[w][jc];
+  }
+  const size_t px = (size_t)v * rq.W + u;
+  rq.rgb[3 * px] = C0;
+  rq.rgb[3 * px + 1] = C1;
+  rq.rgb[3 * px + 2] = C2;
+  rq.depth_z[px] = Dr / s;
+  rq.var_z[px] = V / (s * s);
+  if (rq.opacity) rq.opacity[px] = A;
 }
 
 // ---------------------------------------------------------------------------
@@ -587,18 +665,29 @@ static hipError_t launch_bwd(const FieldArgs& a, const SampleSrc& src, int nbloc
 
 template <class N>
 static hipError_t launch_render(const LevelInfo& lv, const Aabb& box, const nsl_render_request* reqs, int n_req,
-                                const nsl_render_tile* tiles, int n_tiles, const RenderParams& rp, hipStream_t st) {
-  if (n_tiles <= 0) return hipSuccess;
-  const size_t lds = (size_t)4 * 16 * ((rp.n_samples + 15) / 16) * sizeof(float2);
-  hipLaunchKernelGGL(render_kernel<N>, dim3(n_tiles), dim3(256), lds, st, lv, box, reqs, n_req, tiles, rp);
+                                const nsl_render_tile* tiles, int64_t nblocks, int blocks_x, const RenderParams& rp,
+                                hipStream_t st) {
+  if (nblocks <= 0) return hipSuccess;
+  const int64_t gx = nblocks < (1 << 20) ? nblocks : (1 << 20);
+  hipLaunchKernelGGL(render_kernel<N>, dim3((unsigned)gx, (unsigned)((nblocks + gx - 1) / gx)), dim3(kRenderThreads),
+                     render_lds(rp.n_samples), st, lv, box, reqs, n_req, tiles, (uint32_t)nblocks, blocks_x, rp);
   return hipGetLastError();
 }
 
 hipError_t render_tiles(int shape, const LevelInfo& lv, const Aabb& box, const nsl_render_request* reqs,
                         int n_req, const nsl_render_tile* tiles, int n_tiles, const RenderParams& rp,
                         hipStream_t st) {
-  return shape == kShapeTiny ? launch_render<NetTiny>(lv, box, reqs, n_req, tiles, n_tiles, rp, st)
-                             : launch_render<NetFull>(lv, box, reqs, n_req, tiles, n_tiles, rp, st);
+  static_assert(NSL_RENDER_TILE == 64, "four groups of 16 pixels a tile");
+  const int64_t n = 4 * (int64_t)n_tiles;
+  return shape == kShapeTiny ? launch_render<NetTiny>(lv, box, reqs, n_req, tiles, n, 0, rp, st)
+                             : launch_render<NetFull>(lv, box, reqs, n_req, tiles, n, 0, rp, st);
+}
+
+hipError_t render_one(int shape, const LevelInfo& lv, const Aabb& box, const nsl_render_request* req, int H, int W,
+                      const RenderParams& rp, hipStream_t st) {
+  const int64_t bx = ((int64_t)W + 3) / 4, n = bx * (((int64_t)H + 3) / 4);
+  return shape == kShapeTiny ? launch_render<NetTiny>(lv, box, req, 1, nullptr, n, (int)bx, rp, st)
+                             : launch_render<NetFull>(lv, box, req, 1, nullptr, n, (int)bx, rp, st);
 }
 
 template <class N>

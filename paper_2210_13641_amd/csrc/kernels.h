@@ -174,8 +174,10 @@ struct RenderParams {
   int n_samples;  // at most kRenderMaxSamples
 };
 constexpr int kRenderMaxSamples = NSL_RENDER_MAX_SAMPLES;
-// Fused ray-major rendering of tiles (tiles == nullptr: tile t covers pixels
-// [64t, 64t+64) of request 0).
+// Fused rendering of the tiles of n_req requests, and of one whole image
+// (request *req, of H x W pixels).
+hipError_t render_one(int shape, const LevelInfo& lv, const Aabb& box, const nsl_render_request* req, int H, int W,
+                      const RenderParams& rp, hipStream_t st);
 hipError_t render_tiles(int shape, const LevelInfo& lv, const Aabb& box, const nsl_render_request* reqs,
                         int n_req, const nsl_render_tile* tiles, int n_tiles, const RenderParams& rp,
                         hipStream_t st);
