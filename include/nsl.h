@@ -203,13 +203,12 @@ int nsl_occupancy_set(nsl_mapper* m, const uint32_t* bits, int src_on_host,
  * applies bias-corrected Adam at step adam_step (>= 1) to every parameter
  * with gradient grads / loss scale and clears grads afterwards.
  *
- * keep_encoding: the backward needs the encoding e of every sample.  With 0
- * it gathers the table again (no per-sample activations are kept between the
- * forward and the backward; the MLP is always recomputed).  With 1 the
- * forward stores e in the workspace (2*levels values per sample, FP32, or
- * BF16 in mixed precision, exactly as the MLP consumes it) and the backward
- * reads it: the same results, about 128 (64) bytes per sample of traffic
- * instead of a second gather, whose random reads move whole cache lines.
+ * keep_encoding: the backward needs the encoding e of every sample (2*levels
+ * values per sample, FP32, or BF16 in mixed precision, exactly as the MLP
+ * consumes it; the MLP itself is always recomputed).  With 1 the workspace has
+ * room for it.  With 0 it has none: the 4-level field gathers the table again
+ * in the backward, the 16-level field keeps e in the space of the
+ * table-gradient records, which are written later.  The same results either way.
  *
  * precision: NSL_PRECISION_FP32, or NSL_PRECISION_MIXED: the step converts
  * the FP32 master parameters to an FP16 table copy and BF16 MLP operands,
@@ -274,8 +273,9 @@ int nsl_train_step(nsl_mapper* m, const nsl_field* f, float* params, float* grad
  *   0 gradient clearing (the MLP weights and padding; the table part is
  *   overwritten by the reduction of phase 6) and weight-operand preparation,
  *   1 rays + march +
- *   batch cut, 2 encoding of every sample (keep_encoding = 1 only),
- *   3 field forward (MLP; with keep_encoding = 0 also the table gather),
+ *   batch cut, 2 encoding of every sample (empty for the 4-level field with
+ *   keep_encoding = 0),
+ *   3 field forward (MLP; with keep_encoding = 0 and 4 levels also the table gather),
  *   4 compositing + loss + its adjoint, 5 field backward kernel (MLP
  *   recompute and adjoint, weight gradients per workgroup, dL/de),
  *   6 table gradient (bin count, scans, placement, reduction), with the
@@ -461,8 +461,8 @@ int nsl_depth_covariance(int c, int p, const double* C, const double* Et, const 
  * Rendering (Sec. 3.3: the mapping thread also renders for interactive
  * visualisation).  Uniform samples t_i = t_near + (i+1/2)*dt,
  * i < n_samples <= NSL_RENDER_MAX_SAMPLES; a ray stops before its first sample with
- * T_i < stop_T (0 disables), which also ends its work.  One wave renders
- * one ray; per pixel: rgb, depth_z, var_z (z units) and opacity.
+ * T_i < stop_T (0 disables), which also ends its work.  A workgroup
+ * renders 16 pixels; per pixel: rgb, depth_z, var_z (z units) and opacity.
  * ------------------------------------------------------------------------ */
 typedef struct nsl_render_config {
   float t_near, dt;

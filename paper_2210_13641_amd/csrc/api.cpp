@@ -101,6 +101,18 @@ struct nsl_field {
   WOffsets wo;
 };
 
+// Whether the encoding of the samples gets a launch of its own, level by level
+// (each XCD's L2 then holds one level's slice of the table), also where the
+// caller keeps no room for it: it then waits in the space of the
+// table-gradient records (80 L bytes a sample, the encoding takes at most
+// 8 L), which are written after its last reader.  The 16-level field: gathered
+// inside the MLP kernels, every XCD's L2 sees the whole table (24 or 49 MB),
+// and each wave waits on its own gathers: a mixed step of 60 007 samples took
+// 43 + 34 us in the MLP kernels and 18 us in the count and scans, against 45 us
+// for the same work and the encoding.  The tables of the 4-level field fit an
+// L2 and are gathered in place: a launch would cost more.
+static bool encodes_apart(const nsl_field* f) { return f->shape == kShapeFull; }
+
 struct nsl_mapper {
   int max_kf, H, W, grid_res;
   char* storage;
@@ -445,11 +457,12 @@ int nsl_train_step(nsl_mapper* m, const nsl_field* f, float* params, float* grad
   const bool prof = g_prof.on;
   auto mark = [&](int i) -> hipError_t { return prof ? hipEventRecord(g_prof.ev[i], st) : hipSuccess; };
   HIP_TRY(mark(0), "profile event");
-  // with the encoding kept, the encoding kernel also counts the
-  // table-gradient records per bin and unit
+  // the encoding, where it has a launch of its own
+  void* const encoding = c->keep_encoding ? b.ecache : encodes_apart(f) ? b.rec.sorted : nullptr;
+  // that launch also counts the table-gradient records per bin and unit
   // (unless the plan takes no records)
   const bool counted =
-      c->keep_encoding != 0 && b.plan.direct_parts == 0 && b.plan.bl.max_level_bins <= kEncodeLevelBins;
+      encoding && b.plan.direct_parts == 0 && b.plan.bl.max_level_bins <= kEncodeLevelBins;
   // the mixed step prepares (FP16 table copy, gradient clearing,
   // overflow-flag reset, BF16 operands) and counts the candidates' samples in
   // one launch; profiled steps keep them apart to time the two phases
@@ -483,7 +496,7 @@ int nsl_train_step(nsl_mapper* m, const nsl_field* f, float* params, float* grad
   FieldArgs fa{params, b.wprep, f->lv};
   SampleSrc src{};
   src.t = b.t; src.ray = b.ray; src.rays = b.rb.rays; src.box = f->box; src.n_dev = b.rb.stats + 1; src.n = 0;
-  src.ecache = b.ecache;
+  src.ecache = encoding;
   src.ecache_stride = c->max_samples;
   if (src.ecache) {
     uint32_t* hist = counted ? b.rec.hist : nullptr;
@@ -624,6 +637,11 @@ size_t nsl_field_workspace_bytes(const nsl_field* f, int S) {
   return field_carve(f, S, nullptr, nullptr);
 }
 
+// Whether the encoding launch counts the table-gradient records.
+static bool counts_apart(const nsl_field* f, const BinPlan& p) {
+  return encodes_apart(f) && p.direct_parts == 0 && p.bl.max_level_bins <= kEncodeLevelBins;
+}
+
 static int field_common(const nsl_field* f, const float* params, const float* xn, const float* dirs, int S,
                         void* ws, size_t ws_bytes, bool mixed, FieldWs& w, SampleSrc& src) {
   if (!f || !xn || !dirs || !ws) return fail(NSL_E_INVALID, "null argument");
@@ -647,6 +665,11 @@ int nsl_field_fwd(const nsl_field* f, const float* params, const float* xn, cons
   if (rc) return rc;
   HIP_TRY(field_prep(f->shape, params, f->wo, w.wprep, st), "prep weights");
   FieldArgs fa{params, w.wprep, f->lv};
+  if (encodes_apart(f)) {
+    src.ecache = w.rec.sorted;
+    src.ecache_stride = S;
+    HIP_TRY(field_encode(f->shape, fa, src, S, nullptr, w.plan.bl, st), "encoding");
+  }
   HIP_TRY(field_forward(f->shape, fa, src, S, sigma, rgb, st), "field forward");
   return NSL_OK;
 }
@@ -661,10 +684,16 @@ int nsl_field_bwd(const nsl_field* f, const float* params, const float* xn, cons
   if (rc) return rc;
   HIP_TRY(field_prep(f->shape, params, f->wo, w.wprep, st), "prep weights");
   FieldArgs fa{params, w.wprep, f->lv};
+  const bool counted = counts_apart(f, w.plan);
+  if (encodes_apart(f)) {
+    src.ecache = w.rec.sorted;
+    src.ecache_stride = S;
+    HIP_TRY(field_encode(f->shape, fa, src, S, counted ? w.rec.hist : nullptr, w.plan.bl, st), "encoding");
+  }
   HIP_TRY(field_backward(f->shape, fa, src, kBwdBlocks, dsigma, drgb, w.rec, w.partial, f->wo, grads, st),
           "field backward");
   const WeightSum wsum{f->shape, w.partial, kBwdBlocks, f->wo, grads, nullptr, LossSum{}};
-  HIP_TRY(bin_scatter(w.plan, w.rec, src, f->lv, false, false, grads, nullptr, st, false, &wsum),
+  HIP_TRY(bin_scatter(w.plan, w.rec, src, f->lv, false, false, grads, nullptr, st, counted, &wsum),
           "table and weight gradients");
   return NSL_OK;
 }
@@ -702,10 +731,16 @@ int nsl_field_bwd_mixed(const nsl_field* f, const void* shadow, const float* xn,
   int rc = field_common(f, nullptr, xn, dirs, S, ws, ws_bytes, true, w, src);
   if (rc) return rc;
   w.rec.de_bf16 = true;  // the mixed backward stores dL/de as BF16 pairs
+  const bool counted = counts_apart(f, w.plan);
+  if (encodes_apart(f)) {
+    src.ecache = w.rec.sorted;
+    src.ecache_stride = S;
+    HIP_TRY(mixed_encode(f->shape, f->lv, shadow, src, S, counted ? w.rec.hist : nullptr, w.plan.bl, st), "encoding");
+  }
   HIP_TRY(mixed_backward(f->shape, f->lv, shadow, src, kBwdBlocks, dsigma, drgb, w.rec, w.partial, f->wo, grads, st),
           "field backward (mixed)");
   const WeightSum wsum{f->shape, w.partial, kBwdBlocks, f->wo, grads, nullptr, LossSum{}};
-  HIP_TRY(bin_scatter(w.plan, w.rec, src, f->lv, true, false, grads, nullptr, st, false, &wsum),
+  HIP_TRY(bin_scatter(w.plan, w.rec, src, f->lv, true, false, grads, nullptr, st, counted, &wsum),
           "table and weight gradients");
   return NSL_OK;
 }
