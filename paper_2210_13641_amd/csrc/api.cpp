@@ -995,7 +995,7 @@ size_t nsl_field_prepared_bytes(const nsl_field* f) {
 int nsl_field_prepare(const nsl_field* f, const float* params, void* prepared, hipStream_t st) {
   if (!f || !params || !prepared) return fail(NSL_E_INVALID, "null argument");
   if (misaligned(params)) return fail(NSL_E_INVALID, "params must be 16-byte aligned");
-  HIP_TRY(field_prep(f->shape, params, f->wo, static_cast<float*>(prepared), st), "prepare");
+  HIP_TRY(render_prep(f->shape, params, f->wo, prepared, nullptr, nullptr, nullptr, nullptr, st), "prepare");
   return NSL_OK;
 }
 
@@ -1005,7 +1005,7 @@ int nsl_render_batch(const nsl_field* f, const nsl_render_request* reqs, int n_r
   if (n_req < 0 || n_tiles < 0) return fail(NSL_E_INVALID, "negative count");
   int rc = check_render_cfg(c);
   if (rc) return rc;
-  HIP_TRY(render_tiles(f->shape, f->lv, f->box, reqs, n_req, tiles, n_tiles, render_params(c), st), "render");
+  HIP_TRY(render_tiles(f->shape, f->lv, f->box, f->wo, reqs, n_req, tiles, n_tiles, render_params(c), st), "render");
   return NSL_OK;
 }
 
@@ -1030,8 +1030,7 @@ static int render_image(const nsl_field* f, const float* params, const float* po
   char* base = static_cast<char*>(ws);
   void* prepared = base;
   nsl_render_request* dev_req = reinterpret_cast<nsl_render_request*>(base + nsl_field_prepared_bytes(f));
-  int rc = nsl_field_prepare(f, params, prepared, st);
-  if (rc) return rc;
+  if (misaligned(params)) return fail(NSL_E_INVALID, "params must be 16-byte aligned");
   nsl_render_request r;
   r.params = params;
   r.prepared = prepared;
@@ -1043,8 +1042,8 @@ static int render_image(const nsl_field* f, const float* params, const float* po
   r.depth_z = depth;
   r.var_z = var;
   r.opacity = opacity;
-  HIP_TRY(store_request(&r, pose, intr, dev_req, st), "store request");
-  HIP_TRY(render_one(f->shape, f->lv, f->box, dev_req, H, W, render_params(c), st), "render");
+  HIP_TRY(render_prep(f->shape, params, f->wo, prepared, &r, pose, intr, dev_req, st), "prepare and store request");
+  HIP_TRY(render_one(f->shape, f->lv, f->box, f->wo, dev_req, H, W, render_params(c), st), "render");
   return NSL_OK;
 }
 

@@ -7,6 +7,9 @@
 // the first MFMA layer (net.h).  Nothing but sigma and colour leaves the
 // forward kernel; the backward kernel re-derives every activation from the
 // sample position instead of reading stored activations.
+#include <algorithm>
+
+#include "bf16_ops.h"
 #include "bins.h"
 #include "field_common.h"
 
@@ -29,31 +32,29 @@ struct Acts {
 
 template <class N>
 __device__ __forceinline__ void mlp_fwd(const float* __restrict__ Af, int lane, Acts<N>& a) {
+  auto w = [&](int j, int m, int s) { return Af[N::foff(j) + (m * N::fks(j) + s) * kWave + lane]; };
   constexpr f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
   // layer 0: encoding -> h1
   {
-    const float* A = Af + N::foff(0) + lane;
     f4 acc[N::HD / 16];
 #pragma unroll
     for (int m = 0; m < N::HD / 16; ++m) acc[m] = zero;
 #pragma unroll
     for (int s = 0; s < N::fks(0); ++s)
 #pragma unroll
-      for (int m = 0; m < N::HD / 16; ++m) acc[m] = mfma4(A[(m * N::fks(0) + s) * kWave], a.e[s], acc[m]);
+      for (int m = 0; m < N::HD / 16; ++m) acc[m] = mfma4(w(0, m, s), a.e[s], acc[m]);
 #pragma unroll
     for (int m = 0; m < N::HD / 16; ++m) a.h1[m] = relu4(acc[m]);
   }
   // layer 1: h1 -> o (geometry, 16)
   {
-    const float* A = Af + N::foff(1) + lane;
     f4 acc = zero;
 #pragma unroll
-    for (int s = 0; s < N::fks(1); ++s) acc = mfma4(A[s * kWave], a.h1[s >> 2][s & 3], acc);
+    for (int s = 0; s < N::fks(1); ++s) acc = mfma4(w(1, 0, s), a.h1[s >> 2][s & 3], acc);
     a.o = acc;
   }
   // layer 2: [o, sh] -> h3
   {
-    const float* A = Af + N::foff(2) + lane;
     f4 acc[N::HC / 16];
 #pragma unroll
     for (int m = 0; m < N::HC / 16; ++m) acc[m] = zero;
@@ -61,14 +62,13 @@ __device__ __forceinline__ void mlp_fwd(const float* __restrict__ Af, int lane, 
     for (int s = 0; s < 8; ++s) {
       const float b = s < 4 ? a.o[s & 3] : a.sh[s & 3];
 #pragma unroll
-      for (int m = 0; m < N::HC / 16; ++m) acc[m] = mfma4(A[(m * 8 + s) * kWave], b, acc[m]);
+      for (int m = 0; m < N::HC / 16; ++m) acc[m] = mfma4(w(2, m, s), b, acc[m]);
     }
 #pragma unroll
     for (int m = 0; m < N::HC / 16; ++m) a.h3[m] = relu4(acc[m]);
   }
   const f4* hl = a.h3;
   if constexpr (N::NCH == 2) {
-    const float* A = Af + N::foff(3) + lane;
     f4 acc[N::HC / 16];
 #pragma unroll
     for (int m = 0; m < N::HC / 16; ++m) acc[m] = zero;
@@ -76,17 +76,16 @@ __device__ __forceinline__ void mlp_fwd(const float* __restrict__ Af, int lane, 
     for (int s = 0; s < N::HC / 4; ++s)
 #pragma unroll
       for (int m = 0; m < N::HC / 16; ++m)
-        acc[m] = mfma4(A[(m * (N::HC / 4) + s) * kWave], a.h3[s >> 2][s & 3], acc[m]);
+        acc[m] = mfma4(w(3, m, s), a.h3[s >> 2][s & 3], acc[m]);
 #pragma unroll
     for (int m = 0; m < N::HC / 16; ++m) a.h4[m] = relu4(acc[m]);
     hl = a.h4;
   }
   // last layer -> z (rows 0..2 valid, held by lane group 0)
   {
-    const float* A = Af + N::foff(N::NW - 1) + lane;
     f4 acc = zero;
 #pragma unroll
-    for (int s = 0; s < N::HC / 4; ++s) acc = mfma4(A[s * kWave], hl[s >> 2][s & 3], acc);
+    for (int s = 0; s < N::HC / 4; ++s) acc = mfma4(w(N::NW - 1, 0, s), hl[s >> 2][s & 3], acc);
     a.z = acc;
   }
 }
@@ -96,9 +95,8 @@ __device__ __forceinline__ void mlp_fwd(const float* __restrict__ Af, int lane, 
 // ---------------------------------------------------------------------------
 
 template <class N>
-__global__ void prep_weights_kernel(const float* __restrict__ params, WOffsets wo,
-                                    float* __restrict__ out) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void prep_weight(const float* __restrict__ params, const WOffsets& wo,
+                                            float* __restrict__ out, int idx) {
   if (idx >= N::FWD_FLOATS + N::BWD_FLOATS) return;
   float v = 0.0f;
   if (idx < N::FWD_FLOATS) {
@@ -122,6 +120,12 @@ __global__ void prep_weights_kernel(const float* __restrict__ params, WOffsets w
     if (row >= 0 && row < N::kin(j) && col < N::kout(j)) v = params[wo.off[j] + row * N::kout(j) + col];
   }
   out[idx] = v;
+}
+
+template <class N>
+__global__ __launch_bounds__(256) void prep_weights_kernel(const float* __restrict__ params, WOffsets wo,
+                                                           float* __restrict__ out) {
+  prep_weight<N>(params, wo, out, (int)(blockIdx.x * 256 + threadIdx.x));
 }
 
 // ---------------------------------------------------------------------------
@@ -453,6 +457,107 @@ __global__ __launch_bounds__(kFieldBwdWaves * kWave, 1) void field_bwd_kernel(Fi
 
 
 
+// Networks whose rendering runs on the BF16 matrix cores in three parts
+// (bf16_ops.h): the 64-wide ones.  At 640x480 x 64 samples of the paper-scale map
+// 4.25 ms with FP32 products, bound by them (2.6 ms of matrix cycles), 3.76 ms so,
+// the errors against 64 bits the same 8e-8 to 9e-8.  (Training keeps FP32
+// products throughout: a table entry's gradient may be a small residue of its
+// terms, and the optimiser divides it by its own size.)
+template <class N>
+constexpr bool kSplitNet = N::HD >= 64;
+
+// The forward operands in three BF16 parts, each part laid out like the mixed
+// precision's (split_mlp).
+template <class N>
+__device__ __forceinline__ void prep_split(const float* __restrict__ params, const WOffsets& wo,
+                                           __bf16* __restrict__ out, int idx) {
+  using M = Mixed<N>;
+  if (idx >= M::FWD) return;
+  int j = 0;
+  while (j + 1 < N::NW && idx >= M::foff(j + 1)) ++j;
+  const int r = idx - M::foff(j);
+  const int u = r % 8, lane = (r / 8) % kWave, ms = r / M::BLK;
+  const int s = ms % M::fks(j), m = ms / M::fks(j);
+  const int row = mixed_fwd_feature<N>(j, s, lane >> 4, u), col = 16 * m + (lane & 15);
+  float v = row >= 0 && row < N::kin(j) && col < N::kout(j) ? params[wo.off[j] + row * N::kout(j) + col] : 0.0f;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const __bf16 h = (__bf16)v;
+    out[c * M::FWD + idx] = h;
+    v -= (float)h;
+  }
+}
+
+// The operands of the rendering, and (with dst) the request record, whose pose
+// and intrinsics come from device memory: one launch.
+template <class N>
+__global__ __launch_bounds__(256) void render_prep_kernel(const float* __restrict__ params, WOffsets wo,
+                                                          void* __restrict__ out, nsl_render_request r,
+                                                          const float* __restrict__ pose,
+                                                          const float* __restrict__ intr, nsl_render_request* dst) {
+  const int idx = (int)(blockIdx.x * 256 + threadIdx.x);
+  if constexpr (kSplitNet<N>)
+    prep_split<N>(params, wo, static_cast<__bf16*>(out), idx);
+  else
+    prep_weight<N>(params, wo, static_cast<float*>(out), idx);
+  if (!dst || blockIdx.x != gridDim.x - 1 || threadIdx.x != 255) return;
+#pragma unroll
+  for (int i = 0; i < 12; ++i) r.pose[i] = pose[i];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r.intr[i] = intr[i];
+  *dst = r;
+}
+
+// One tile with FP32 products, its weights from the parameter vector: for
+// tiles that split_mlp cannot represent (values that are not finite).  The
+// loops over a layer's tiles stay rolled: these tiles are rare, and the
+// registers are the fast path's.
+template <class N, int J>
+__device__ __forceinline__ void fp32_layer(const float* __restrict__ params, const WOffsets& wo, int lane,
+                                           const float (&x)[N::fks(J)], f4 (&out)[N::fmt(J)]) {
+  const float* w = params + wo.off[J];
+#pragma unroll 1
+  for (int m = 0; m < N::fmt(J); ++m) {
+    asm volatile("" : "+v"(lane));  // the addresses are formed here, not held in registers outside
+    const int col = 16 * m + (lane & 15);
+    f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int s = 0; s < N::fks(J); ++s) {
+      const int row = fwd_in_feature<N>(J, s, lane >> 4);
+      acc = mfma4(row >= 0 && col < N::kout(J) ? w[row * N::kout(J) + col] : 0.0f, x[s], acc);
+      __builtin_amdgcn_sched_barrier(0);  // (one weight at a time)
+    }
+#pragma unroll
+    for (int i = 0; i < N::fmt(J); ++i) out[i] = i == m ? acc : out[i];
+  }
+}
+template <int K>
+__device__ __forceinline__ void flat4(const f4 (&v)[K], bool relu, float (&x)[4 * K]) {
+#pragma unroll
+  for (int k = 0; k < 4 * K; ++k) x[k] = relu ? fmaxf(v[k >> 2][k & 3], 0.0f) : v[k >> 2][k & 3];
+}
+template <class N>
+__device__ __forceinline__ void fp32_tile(const float* __restrict__ params, const WOffsets& wo, int lane,
+                                          const float (&e)[N::NSLOT], f4 sh, f4& o, f4& z) {
+  f4 h[N::HC / 16], r[1];
+  float x[N::HC / 4];
+  fp32_layer<N, 0>(params, wo, lane, e, h);
+  flat4(h, true, x);
+  fp32_layer<N, 1>(params, wo, lane, x, r);
+  o = r[0];
+  {
+    const f4 c[2] = {o, sh};
+    float xc[8];
+    flat4(c, false, xc);
+    fp32_layer<N, 2>(params, wo, lane, xc, h);
+  }
+  flat4(h, true, x);
+  fp32_layer<N, 3>(params, wo, lane, x, h);
+  flat4(h, true, x);
+  fp32_layer<N, 4>(params, wo, lane, x, r);
+  z = r[0];
+}
+
 // ---------------------------------------------------------------------------
 // Fused rendering: a workgroup takes 16 pixels, the columns of the MFMA tiles,
 // and its four waves consecutive samples of all 16 rays, 16 a round: wave w
@@ -471,31 +576,59 @@ __global__ __launch_bounds__(kFieldBwdWaves * kWave, 1) void field_bwd_kernel(Fi
 // pixels of 64 samples at paper scale 11.3 -> 4.3 ms, 160x120 of 32 samples
 // with the tiny field 105 -> 45 us (compositing four tiles at once, on every
 // lane instead of the 16 that hold a tile's outputs, 5.8 -> 4.3 ms of it).
+//
+// V* = sum w (t - d*)^2 is formed without a second pass: each lane carries the
+// weight A, the weighted mean M of t and S = sum w (t - M)^2 of its samples
+// (every term non-negative), the parts of a ray are merged pair by pair, and
+// V* = S + A (M - d*)^2.
 // ---------------------------------------------------------------------------
-constexpr int kRenderWaves = 4;
-constexpr int kRenderThreads = kRenderWaves * kWave;
+constexpr int kRenderWaves = 4;                 // waves of a group of 16 pixels
 constexpr int kRenderRound = 4 * kRenderWaves;  // samples of a round
-
-// LDS of the weights of the 16 rays' samples, which wait for the second pass
-// of V* (d* first).
-constexpr int render_rounds(int n_samples) { return (n_samples + kRenderRound - 1) / kRenderRound; }
-constexpr size_t render_lds(int n_samples) { return (size_t)render_rounds(n_samples) * kRenderRound * 16 * sizeof(float); }
-
-// Workgroup -> pixels: with tiles, workgroup b of nblocks takes the group b % 4
-// of 16 consecutive pixels of tile b / 4; without, the 4x4 block b of request
-// 0's image (blocks_x blocks a row).  The grid is two-dimensional because the
-// largest images have more threads than one dimension of a launch may.
+// Pixel groups of a workgroup: two share one copy of the split operands (60 KB,
+// two workgroups a CU; with one group a workgroup, LDS would hold half the waves).
 template <class N>
-__global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(3))) void render_kernel(
-    LevelInfo lv, Aabb box, const nsl_render_request* __restrict__ reqs, int n_req,
+constexpr int kRenderGroups = kSplitNet<N> ? 2 : 1;
+template <class N>
+constexpr int kRenderThreads = kRenderGroups<N> * kRenderWaves * kWave;
+
+// Weight, weighted mean and weighted squared deviation of some samples' t.
+struct Moments {
+  float A, M, S;
+  __device__ __forceinline__ void add(float w, float t) {
+    if (w == 0.0f) return;
+    const float a = A + w, dt = t - M, r = dt * w * __builtin_amdgcn_rcpf(a);
+    M += r;
+    S += A * dt * r;
+    A = a;
+  }
+  __device__ __forceinline__ void merge(float A2, float M2, float S2) {
+    const float a = A + A2, dm = M2 - M, f = a == 0.0f ? 0.0f : A2 / a;
+    S += S2 + dm * dm * A * f;
+    M += dm * f;
+    A = a;
+  }
+};
+
+// Workgroup -> pixels: with tiles, group k of the launch (kRenderGroups a
+// workgroup) takes the quarter k % 4 of tile k / 4, 16 consecutive pixels;
+// without, the workgroup takes block b of request 0's image, a row of 4x4
+// pixels a group (blocks_x blocks a row).  The grid is two-dimensional because
+// the largest images have more threads than one dimension of a launch may.
+template <class N>
+__global__ __launch_bounds__(kRenderThreads<N>) __attribute__((amdgpu_waves_per_eu(4))) void render_kernel(
+    LevelInfo lv, Aabb box, WOffsets wo, const nsl_render_request* __restrict__ reqs, int n_req,
     const nsl_render_tile* __restrict__ tiles, uint32_t nblocks, int blocks_x, RenderParams rp) {
-  __shared__ __attribute__((aligned(16))) float Af[N::FWD_FLOATS];
-  __shared__ float4 tile_out[kRenderWaves][4][16];  // (o_0, z) of a wave's four tiles
-  __shared__ float tau_of[2][kRenderRound][16];
-  __shared__ float sums[kRenderWaves][5][16];
-  __shared__ float v_sums[kRenderWaves][16];
-  extern __shared__ float w_lds[];  // [sample][16]
-  const int wave = threadIdx.x / kWave, lane = lane_id(), g = lane >> 4, jc = lane & 15;
+  constexpr int GR = kRenderGroups<N>;
+  typedef typename std::conditional<kSplitNet<N>, __bf16, float>::type Op;
+  constexpr int kOps = kSplitNet<N> ? 3 * Mixed<N>::FWD : N::FWD_FLOATS;
+  __shared__ __attribute__((aligned(16))) Op Af[kOps];
+  __shared__ float4 tile_out[GR * kRenderWaves][4][16];  // (o_0, z) of a wave's four tiles
+  __shared__ float tau_of[2][GR][kRenderRound][16];
+  __shared__ float sums[GR][kRenderWaves][7][16];  // C, D and the moments
+  __shared__ int alive[2][GR];
+  const int gw = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  const int grp = gw / kRenderWaves, wave = gw % kRenderWaves;
+  const int lane = lane_id(), g = lane >> 4, jc = lane & 15;
   // consecutive workgroups go round the 8 XCDs: of each 512 blocks an XCD
   // takes 64 consecutive ones, whose lines it finds in its L2 (4.33 -> 4.24 ms
   // for 640x480 at paper scale)
@@ -505,130 +638,162 @@ __global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(
   int req = 0, u, v;
   bool in;
   if (tiles) {
-    const nsl_render_tile tile = tiles[blk / 4];
+    constexpr int per = 4 / GR;  // workgroups a tile
+    const nsl_render_tile tile = tiles[blk / per];
     req = tile.request;
     if (req < 0 || req >= n_req) return;
     const int npix = reqs[req].H * reqs[req].W;
-    const int first = max(tile.first_pixel, 0) + 16 * (int)(blk % 4);
+    const int first = max(tile.first_pixel, 0) + 16 * GR * (int)(blk % per);
     const int last = min(tile.first_pixel + min(tile.n_pixels, NSL_RENDER_TILE), npix);
     if (first >= last) return;
-    in = first + jc < last;
-    const int px = in ? first + jc : first;
+    in = first + 16 * grp + jc < last;
+    const int px = in ? first + 16 * grp + jc : first;
     v = px / reqs[req].W;
     u = px - v * reqs[req].W;
   } else {
     const int by = (int)blk / blocks_x, bx = (int)blk - by * blocks_x;
-    u = 4 * bx + (jc & 3);
+    u = 4 * (GR * bx + grp) + (jc & 3);
     v = 4 * by + (jc >> 2);
     in = u < reqs[0].W && v < reqs[0].H;
     u = min(u, reqs[0].W - 1);
     v = min(v, reqs[0].H - 1);
   }
   const nsl_render_request& rq = reqs[req];
-  load_operands<N>(Af, reinterpret_cast<const float*>(rq.prepared), N::FWD_FLOATS);
+  if constexpr (kSplitNet<N>)
+    load_bf16<N>(Af, static_cast<const __bf16*>(rq.prepared), kOps);
+  else
+    load_operands<N>(Af, static_cast<const float*>(rq.prepared), kOps);
   __syncthreads();
   LaneLevels<N> ll;
   lane_levels<N>(lv, g, ll);
-  float o[3], d[3], s;
+  float o[3], d[3], s, shv[4];
   camera_ray(rq.pose, rq.intr, u, v, o, d, s);
-  Acts<N> act;
-  sh_lane<N>(d, g, act.sh);
+  sh_lane<N>(d, g, shv);
   auto t_of = [&](int j) {
 #pragma clang fp contract(off)
     return rp.t_near + ((float)j + 0.5f) * rp.dt;
   };
-  float carry = 0.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f, D = 0.0f, A = 0.0f;
-  bool done = !in;  // this lane's ray has stopped
-  const int rounds = render_rounds(rp.n_samples), mine = 4 * wave + g;  // this lane's sample of a round
-  int q = 0;
-  for (; q < rounds; ++q) {
-    for (int k = 0; k < 4; ++k) {
-      const int j = q * kRenderRound + 4 * wave + k;
-      if (j >= rp.n_samples) break;
-      const float t = t_of(j);
-      float xn[3];
-#pragma unroll
-      for (int i = 0; i < 3; ++i) xn[i] = normalise_axis(pos_axis(o[i], d[i], t), box.lo[i], box.inv[i]);
-      encode<N>(rq.params, lv.table_mask, ll, xn, act.e);
-      mlp_fwd<N>(Af, lane, act);
-      // lanes of row 0 hold pixel jc's density and colour
-      if (g == 0) tile_out[wave][k][jc] = make_float4(act.o[0], act.z[0], act.z[1], act.z[2]);
-    }
-    wave_lds_fence();
-    const float4 oz = tile_out[wave][g][jc];
+  float carry = 0.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f, D = 0.0f;
+  Moments mo{0.0f, 0.0f, 0.0f};
+  bool done = !in;                          // this lane's ray has stopped
+  bool live = __ballot(!done) != 0ull;      // some ray of the group has not
+  const int rounds = (rp.n_samples + kRenderRound - 1) / kRenderRound;
+  const int mine = 4 * wave + g;            // this lane's sample of a round
+  for (int q = 0; q < rounds; ++q) {
     const int j = q * kRenderRound + mine;
     const bool valid = j < rp.n_samples;
     const float t = t_of(j);
-    const float tau = valid ? expf(oz.x) * rp.dt : 0.0f;
-    float(*tw)[16] = tau_of[q & 1];
-    tw[mine][jc] = tau;
+    float(*tw)[16] = tau_of[q & 1][grp];
+    float4 oz;
+    float tau = 0.0f;
+    if (live) {
+      for (int k = 0; k < 4; ++k) {
+        const int jk = q * kRenderRound + 4 * wave + k;
+        if (jk >= rp.n_samples) break;
+        const float tk = t_of(jk);
+        float xn[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) xn[i] = normalise_axis(pos_axis(o[i], d[i], tk), box.lo[i], box.inv[i]);
+        f4 oo, zz;
+        if constexpr (kSplitNet<N>) {
+          float e[1][N::NSLOT];
+          encode<N>(rq.params, lv.table_mask, ll, xn, e[0]);
+          const f4 sh[1] = {f4{shv[0], shv[1], shv[2], shv[3]}};
+          f4 o1[1], z1[1];
+          split_mlp<N, 1>(Af, lane, e, sh, o1, z1);
+          if (any_not_finite(o1[0], z1[0])) fp32_tile<N>(rq.params, wo, lane, e[0], sh[0], o1[0], z1[0]);
+          oo = o1[0];
+          zz = z1[0];
+        } else {
+          Acts<N> act;
+          encode<N>(rq.params, lv.table_mask, ll, xn, act.e);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) act.sh[i] = shv[i];
+          mlp_fwd<N>(Af, lane, act);
+          oo = act.o;
+          zz = act.z;
+        }
+        // lanes of row 0 hold pixel jc's density and colour
+        if (g == 0) tile_out[gw][k][jc] = make_float4(oo[0], zz[0], zz[1], zz[2]);
+      }
+      wave_lds_fence();
+      oz = tile_out[gw][g][jc];
+      tau = valid ? expf(oz.x) * rp.dt : 0.0f;
+      tw[mine][jc] = tau;
+    }
     __syncthreads();
+    if (GR > 1 && q > 0 && rp.stop_T > 0.0f) {  // the groups leave together
+      int any = 0;
+#pragma unroll
+      for (int k = 0; k < GR; ++k) any |= alive[(q - 1) & 1][k];
+      if (!any) break;
+    }
+    if (!live) {
+      if (GR > 1 && wave == 0 && lane == 0) alive[q & 1][grp] = 0;
+      continue;
+    }
     float before = 0.0f, round = 0.0f;  // optical depth of the round before this sample, and of all of it
 #pragma unroll
     for (int i = 0; i < kRenderRound; ++i) {
       if (i == mine) before = round;
       round += tw[i][jc];
     }
-    const float T = expf(-(carry + before));
+    const float T0 = expf(-(carry + before));
     carry += round;
-    const bool on = valid && !done && !(rp.stop_T > 0.0f && T < rp.stop_T);
-    const float w = on ? T * -expm1f(-tau) : 0.0f;
-    w_lds[j * 16 + jc] = w;
+    const bool on = valid && !done && !(rp.stop_T > 0.0f && T0 < rp.stop_T);
     if (on) {
+      const float w = T0 * -expm1f(-tau);
       C0 += w * sigmoidf(oz.y);
       C1 += w * sigmoidf(oz.z);
       C2 += w * sigmoidf(oz.w);
       D += w * t;
-      A += w;
+      mo.add(w, t);
     }
     if (rp.stop_T > 0.0f) {
       done |= expf(-carry) < rp.stop_T;
-      if (__ballot(!done) == 0ull) {  // every wave holds the same sums, so all leave in one round
-        ++q;
-        break;
-      }
+      live = __ballot(!done) != 0ull;  // every wave of the group holds the same sums
+      if (GR == 1 && !live) break;
+      if (GR > 1 && wave == 0 && lane == 0) alive[q & 1][grp] = live;
     }
   }
   {
-    float s5[5] = {C0, C1, C2, D, A};
+    float s4[4] = {C0, C1, C2, D};
 #pragma unroll
-    for (int i = 0; i < 5; ++i) {
-      s5[i] += __shfl_xor(s5[i], 16, kWave);
-      s5[i] += __shfl_xor(s5[i], 32, kWave);
-      if (g == 0) sums[wave][i][jc] = s5[i];
+    for (int i = 0; i < 4; ++i) {
+      s4[i] += __shfl_xor(s4[i], 16, kWave);
+      s4[i] += __shfl_xor(s4[i], 32, kWave);
+      if (g == 0) sums[grp][wave][i][jc] = s4[i];
+    }
+#pragma unroll
+    for (int x = 16; x <= 32; x <<= 1)
+      mo.merge(__shfl_xor(mo.A, x, kWave), __shfl_xor(mo.M, x, kWave), __shfl_xor(mo.S, x, kWave));
+    if (g == 0) {
+      sums[grp][wave][4][jc] = mo.A;
+      sums[grp][wave][5][jc] = mo.M;
+      sums[grp][wave][6][jc] = mo.S;
     }
   }
   __syncthreads();
-  // V* = sum w (t - d*)^2 over the composited samples
-  float Dr = 0.0f;
-#pragma unroll
-  for (int w = 0; w < kRenderWaves; ++w) Dr += sums[w][3][jc];
-  float V = 0.0f;
-  for (int j = (int)threadIdx.x / 16; j < q * kRenderRound; j += kRenderThreads / 16) {
-    const float e = t_of(j) - Dr;
-    V += w_lds[j * 16 + jc] * e * e;
-  }
-  V += __shfl_xor(V, 16, kWave);
-  V += __shfl_xor(V, 32, kWave);
-  if (g == 0) v_sums[wave][jc] = V;
-  __syncthreads();
-  if (threadIdx.x >= 16 || !in) return;
-  V = C0 = C1 = C2 = A = 0.0f;
+  if (wave != 0 || g != 0 || !in) return;
+  C0 = C1 = C2 = D = 0.0f;
+  mo = Moments{0.0f, 0.0f, 0.0f};
 #pragma unroll
   for (int w = 0; w < kRenderWaves; ++w) {
-    C0 += sums[w][0][jc];
-    C1 += sums[w][1][jc];
-    C2 += sums[w][2][jc];
-    A += sums[w][4][jc];
-    V += v_sums[w][jc];
+    const float(*p)[16] = sums[grp][w];
+    C0 += p[0][jc];
+    C1 += p[1][jc];
+    C2 += p[2][jc];
+    D += p[3][jc];
+    mo.merge(p[4][jc], p[5][jc], p[6][jc]);
   }
+  const float e = mo.M - D, V = mo.S + mo.A * e * e;
   const size_t px = (size_t)v * rq.W + u;
   rq.rgb[3 * px] = C0;
   rq.rgb[3 * px + 1] = C1;
   rq.rgb[3 * px + 2] = C2;
-  rq.depth_z[px] = Dr / s;
+  rq.depth_z[px] = D / s;
   rq.var_z[px] = V / (s * s);
-  if (rq.opacity) rq.opacity[px] = A;
+  if (rq.opacity) rq.opacity[px] = mo.A;
 }
 
 // ---------------------------------------------------------------------------
@@ -640,6 +805,26 @@ static hipError_t launch_prep(const float* params, const WOffsets& wo, float* ou
   const int n = N::FWD_FLOATS + N::BWD_FLOATS;
   hipLaunchKernelGGL(prep_weights_kernel<N>, dim3((n + 255) / 256), dim3(256), 0, st, params, wo, out);
   return hipGetLastError();
+}
+
+template <class N>
+static hipError_t launch_render_prep(const float* params, const WOffsets& wo, void* out, const nsl_render_request* r,
+                                     const float* pose, const float* intr, nsl_render_request* dst, hipStream_t st) {
+  int n = N::FWD_FLOATS + N::BWD_FLOATS;
+  if constexpr (kSplitNet<N>) {
+    n = Mixed<N>::FWD;
+    static_assert(3 * sizeof(__bf16) * Mixed<N>::FWD <= sizeof(float) * (N::FWD_FLOATS + N::BWD_FLOATS),
+                  "they fit the space of the FP32 operands");
+  }
+  hipLaunchKernelGGL(render_prep_kernel<N>, dim3((n + 255) / 256), dim3(256), 0, st, params, wo, out,
+                     r ? *r : nsl_render_request{}, pose, intr, dst);
+  return hipGetLastError();
+}
+
+hipError_t render_prep(int shape, const float* params, const WOffsets& wo, void* out, const nsl_render_request* r,
+                       const float* pose, const float* intr, nsl_render_request* dst, hipStream_t st) {
+  return shape == kShapeTiny ? launch_render_prep<NetTiny>(params, wo, out, r, pose, intr, dst, st)
+                             : launch_render_prep<NetFull>(params, wo, out, r, pose, intr, dst, st);
 }
 
 template <class N>
@@ -664,30 +849,31 @@ static hipError_t launch_bwd(const FieldArgs& a, const SampleSrc& src, int nbloc
 }
 
 template <class N>
-static hipError_t launch_render(const LevelInfo& lv, const Aabb& box, const nsl_render_request* reqs, int n_req,
-                                const nsl_render_tile* tiles, int64_t nblocks, int blocks_x, const RenderParams& rp,
-                                hipStream_t st) {
+static hipError_t launch_render(const LevelInfo& lv, const Aabb& box, const WOffsets& wo,
+                                const nsl_render_request* reqs, int n_req, const nsl_render_tile* tiles, int n_tiles,
+                                int H, int W, const RenderParams& rp, hipStream_t st) {
+  static_assert(NSL_RENDER_TILE == 64, "four groups of 16 pixels a tile");
+  constexpr int GR = kRenderGroups<N>;
+  const int64_t bx = ((int64_t)W + 4 * GR - 1) / (4 * GR);
+  const int64_t nblocks = tiles ? (int64_t)n_tiles * (4 / GR) : bx * (((int64_t)H + 3) / 4);
   if (nblocks <= 0) return hipSuccess;
-  const int64_t gx = nblocks < (1 << 20) ? nblocks : (1 << 20);
-  hipLaunchKernelGGL(render_kernel<N>, dim3((unsigned)gx, (unsigned)((nblocks + gx - 1) / gx)), dim3(kRenderThreads),
-                     render_lds(rp.n_samples), st, lv, box, reqs, n_req, tiles, (uint32_t)nblocks, blocks_x, rp);
+  const int64_t gx = std::min<int64_t>(nblocks, 1 << 20);
+  hipLaunchKernelGGL(render_kernel<N>, dim3((unsigned)gx, (unsigned)((nblocks + gx - 1) / gx)),
+                     dim3(kRenderThreads<N>), 0, st, lv, box, wo, reqs, n_req, tiles, (uint32_t)nblocks, (int)bx, rp);
   return hipGetLastError();
 }
 
-hipError_t render_tiles(int shape, const LevelInfo& lv, const Aabb& box, const nsl_render_request* reqs,
-                        int n_req, const nsl_render_tile* tiles, int n_tiles, const RenderParams& rp,
-                        hipStream_t st) {
-  static_assert(NSL_RENDER_TILE == 64, "four groups of 16 pixels a tile");
-  const int64_t n = 4 * (int64_t)n_tiles;
-  return shape == kShapeTiny ? launch_render<NetTiny>(lv, box, reqs, n_req, tiles, n, 0, rp, st)
-                             : launch_render<NetFull>(lv, box, reqs, n_req, tiles, n, 0, rp, st);
+hipError_t render_tiles(int shape, const LevelInfo& lv, const Aabb& box, const WOffsets& wo,
+                        const nsl_render_request* reqs, int n_req, const nsl_render_tile* tiles, int n_tiles,
+                        const RenderParams& rp, hipStream_t st) {
+  return shape == kShapeTiny ? launch_render<NetTiny>(lv, box, wo, reqs, n_req, tiles, n_tiles, 0, 0, rp, st)
+                             : launch_render<NetFull>(lv, box, wo, reqs, n_req, tiles, n_tiles, 0, 0, rp, st);
 }
 
-hipError_t render_one(int shape, const LevelInfo& lv, const Aabb& box, const nsl_render_request* req, int H, int W,
-                      const RenderParams& rp, hipStream_t st) {
-  const int64_t bx = ((int64_t)W + 3) / 4, n = bx * (((int64_t)H + 3) / 4);
-  return shape == kShapeTiny ? launch_render<NetTiny>(lv, box, req, 1, nullptr, n, (int)bx, rp, st)
-                             : launch_render<NetFull>(lv, box, req, 1, nullptr, n, (int)bx, rp, st);
+hipError_t render_one(int shape, const LevelInfo& lv, const Aabb& box, const WOffsets& wo,
+                      const nsl_render_request* req, int H, int W, const RenderParams& rp, hipStream_t st) {
+  return shape == kShapeTiny ? launch_render<NetTiny>(lv, box, wo, req, 1, nullptr, 0, H, W, rp, st)
+                             : launch_render<NetFull>(lv, box, wo, req, 1, nullptr, 0, H, W, rp, st);
 }
 
 template <class N>
@@ -721,8 +907,6 @@ hipError_t field_dw_reduce(int shape, const float* partial, int nblocks, const W
   return shape == kShapeTiny ? launch_dw_reduce<NetTiny>(partial, nblocks, wo, grads, overflow, ls, st)
                              : launch_dw_reduce<NetFull>(partial, nblocks, wo, grads, overflow, ls, st);
 }
-
-size_t field_fwd_floats(int shape) { return shape == kShapeTiny ? NetTiny::FWD_FLOATS : NetFull::FWD_FLOATS; }
 
 size_t field_prep_floats(int shape) {
   return shape == kShapeTiny ? NetTiny::FWD_FLOATS + NetTiny::BWD_FLOATS

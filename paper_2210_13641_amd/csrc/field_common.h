@@ -70,6 +70,11 @@ struct Corner8 {
   uint32_t cell[3];  // integer coordinates of the cell's lower corner
 };
 
+// uniform: every lane of the wave is at the same level; else the dense and the
+// hashed index of a corner are both formed and one is selected bitwise (a
+// select of whole expressions became a branch a corner, fifty of them a tile of
+// the 16-level field).
+template <bool uniform = true>
 __device__ __forceinline__ void corners(float x, float y, float z, int n, bool dense,
                                         uint32_t mask, uint32_t off, Corner8& c) {
   float fx, fy, fz, ux, uy, uz;
@@ -84,24 +89,32 @@ __device__ __forceinline__ void corners(float x, float y, float z, int n, bool d
   // index is x + m y + m^2 z, a hashed one (x ^ P1 y ^ P2 z) & mask, and the
   // upper corner's term is the lower one's plus m, m^2, P1 or P2 (all mod 2^32)
   uint32_t ty[2], tz[2];
-  if (dense) {
-    const uint32_t m = (uint32_t)n + 1u, m2 = m * m;
-    ty[0] = iy * m;
-    tz[0] = iz * m2;
-    ty[1] = ty[0] + m;
-    tz[1] = tz[0] + m2;
+  const uint32_t m = (uint32_t)n + 1u;
+  const uint32_t py = dense ? m : kPrime1, pz = dense ? m * m : kPrime2;
+  ty[0] = iy * py;
+  tz[0] = iz * pz;
+  ty[1] = ty[0] + py;
+  tz[1] = tz[0] + pz;
+  if constexpr (uniform) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const uint32_t cx = k & 1, cy = (k >> 1) & 1, cz = (k >> 2) & 1;
+      c.idx[k] = off + (dense ? (ix + cx) + ty[cy] + tz[cz] : ((ix + cx) ^ ty[cy] ^ tz[cz]) & mask);
+    }
   } else {
-    ty[0] = iy * kPrime1;
-    tz[0] = iz * kPrime2;
-    ty[1] = ty[0] + kPrime1;
-    tz[1] = tz[0] + kPrime2;
+    const uint32_t dm = dense ? 0xFFFFFFFFu : 0u;
+    auto pick = [dm](uint32_t d, uint32_t h) { return (d & dm) | (h & ~dm); };  // v_bfi_b32
+#pragma unroll
+    for (int k = 0; k < 8; k += 2) {
+      const uint32_t cy = (k >> 1) & 1, cz = (k >> 2) & 1;
+      const uint32_t yz = pick(ty[cy] + tz[cz], ty[cy] ^ tz[cz]);
+#pragma unroll
+      for (uint32_t cx = 0; cx < 2; ++cx)
+        c.idx[k + cx] = off + (pick(yz + (ix + cx), yz ^ (ix + cx)) & (mask | dm));
+    }
   }
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const uint32_t cx = k & 1, cy = (k >> 1) & 1, cz = (k >> 2) & 1;
-    c.idx[k] = off + (dense ? (ix + cx) + ty[cy] + tz[cz] : ((ix + cx) ^ ty[cy] ^ tz[cz]) & mask);
-    c.w[k] = (gx[cx] * gy[cy]) * gz[cz];
-  }
+  for (int k = 0; k < 8; ++k) c.w[k] = (gx[k & 1] * gy[(k >> 1) & 1]) * gz[(k >> 2) & 1];
 }
 
 // Two features of table entry idx as floats (FP32 or FP16 storage).
@@ -112,13 +125,26 @@ __device__ __forceinline__ float2 load_entry(const _Float16* __restrict__ t, uin
   const h2 v = *reinterpret_cast<const h2*>(t + 2 * (size_t)idx);
   return make_float2((float)v[0], (float)v[1]);
 }
+// The same through a 32-bit byte offset (at most 2^25 entries of 8 bytes): the
+// load takes the table's address from scalar registers and one vector register
+// of offset, two or three vector instructions fewer each.
+static_assert(kMaxTableEntries * 8 <= ((int64_t)1 << 32), "32-bit byte offsets");
+__device__ __forceinline__ float2 load_entry32(const float* __restrict__ t, uint32_t idx) {
+  return *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(t) + (uint32_t)(idx << 3));
+}
+__device__ __forceinline__ float2 load_entry32(const _Float16* __restrict__ t, uint32_t idx) {
+  const h2 v = *reinterpret_cast<const h2*>(reinterpret_cast<const char*>(t) + (uint32_t)(idx << 2));
+  return make_float2((float)v[0], (float)v[1]);
+}
 
-// The trilinear blend of a cell's eight corners, in corner order.
-template <class T>
+// The trilinear blend of a cell's eight corners, in corner order.  kOffset32:
+// loads through 32-bit offsets, except where they measured slower (the FP32
+// level-by-level encoding: 115 against 106 us at 2^18 samples).
+template <bool kOffset32, class T>
 __device__ __forceinline__ float2 blend_corners(const T* __restrict__ table, const Corner8& c) {
   float2 v[8];
 #pragma unroll
-  for (int k = 0; k < 8; ++k) v[k] = load_entry(table, c.idx[k]);
+  for (int k = 0; k < 8; ++k) v[k] = kOffset32 ? load_entry32(table, c.idx[k]) : load_entry(table, c.idx[k]);
   float a0 = 0.0f, a1 = 0.0f;
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
@@ -128,13 +154,13 @@ __device__ __forceinline__ float2 blend_corners(const T* __restrict__ table, con
   return make_float2(a0, a1);
 }
 
-// Trilinear blend of one level's two features at xn.
+// Trilinear blend of one level's two features at xn (lanes at levels of their own).
 template <class T>
 __device__ __forceinline__ float2 encode_level(const T* __restrict__ table, uint32_t mask, int res, bool dense,
                                                uint32_t off, const float xn[3]) {
   Corner8 c;
-  corners(xn[0], xn[1], xn[2], res, dense, mask, off, c);
-  return blend_corners(table, c);
+  corners<false>(xn[0], xn[1], xn[2], res, dense, mask, off, c);
+  return blend_corners<true>(table, c);
 }
 
 template <class N, class T>
@@ -304,7 +330,7 @@ __global__ __launch_bounds__(256) void encode_levels_kernel(LevelInfo lv, const 
   for (int k = 0; k < U; ++k) corners(xn[k][0], xn[k][1], xn[k][2], lv.res[l], dense, lv.table_mask, lv.offset[l], c[k]);
 #pragma unroll
   for (int k = 0; k < U; ++k)
-    if (valid[k]) store_encoding(out + (size_t)l * stride + s[k], blend_corners(table, c[k]));
+    if (valid[k]) store_encoding(out + (size_t)l * stride + s[k], blend_corners<sizeof(T) == 2>(table, c[k]));
   if (!hist) return;
   __shared__ uint32_t cnt[U][kEncodeLevelBins];
   for (int i = threadIdx.x; i < U * kEncodeLevelBins; i += 256) (&cnt[0][0])[i] = 0u;

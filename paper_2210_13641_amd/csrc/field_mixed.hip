@@ -8,17 +8,12 @@
 // columns): a 16x16x32 k-step takes 8 consecutive k-slots per lane group,
 // filled from two 16-row output tiles of the previous layer (rows 4g..4g+3
 // of each), and the weights are laid out for that permutation.
+#include "bf16_ops.h"
 #include "bins.h"
 #include "field_common.h"
 #include "march_common.h"
 
 namespace nsl {
-
-typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
-
-__device__ __forceinline__ f4 mfma32(bf8 a, bf8 b, f4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
 
 typedef float f16v __attribute__((ext_vector_type(16)));
 
@@ -26,61 +21,13 @@ __device__ __forceinline__ f16v mfma32x32(bf8 a, bf8 b, f16v c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 typedef short s8v __attribute__((ext_vector_type(8)));
-
-// Two floats as BF16 (round to nearest even), a in the low half; one
-// v_cvt_pk_bf16_f32.
-__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
-  const bf2 v = {(__bf16)a, (__bf16)b};
-  return __builtin_bit_cast(uint32_t, v);
-}
-
-__device__ __forceinline__ bf8 pack8(f4 lo, f4 hi) {
-  return __builtin_bit_cast(bf8, make_uint4(bf16_pair(lo[0], lo[1]), bf16_pair(lo[2], lo[3]),
-                                            bf16_pair(hi[0], hi[1]), bf16_pair(hi[2], hi[3])));
-}
 
 // Element u of a as 16 bits.  The whole vector is reinterpreted first: the
 // gfx950 compiler lowers a bit cast of one extracted __bf16 element to
 // element 0 whatever the index.
 __device__ __forceinline__ uint32_t bf_bits(bf8 a, int u) {
   return (uint32_t)(uint16_t)__builtin_bit_cast(s8v, a)[u];
-}
-
-// Layout of the BF16 operands (one block = 64 lanes x 8 values per (m, k-step)).
-template <class N>
-struct Mixed {
-  static_assert(N::HD % 32 == 0 && N::HC % 32 == 0, "hidden widths must be multiples of 32");
-  static constexpr int BLK = kWave * 8;
-  static constexpr int fks(int j) { return j == 0 || j == 2 ? 1 : j == 1 ? N::HD / 32 : N::HC / 32; }
-  static constexpr int fsize(int j) { return fks(j) * N::fmt(j) * BLK; }
-  static constexpr int foff(int j) {
-    int o = 0;
-    for (int i = 0; i < j; ++i) o += fsize(i);
-    return o;
-  }
-  static constexpr int FWD = foff(N::NW);
-  static constexpr int bks(int j) { return j == N::NW - 1 || j == 1 ? 1 : j == 0 ? N::HD / 32 : N::HC / 32; }
-  static constexpr int bsize(int j) { return bks(j) * N::bmt(j) * BLK; }
-  static constexpr int boff(int j) {
-    int o = 0;
-    for (int i = 0; i < j; ++i) o += bsize(i);
-    return o;
-  }
-  static constexpr int BWD = boff(N::NW);
-};
-
-// Input feature of forward k-slot (s, lane group g, value u) of layer j; -1 = pad.
-template <class N>
-__host__ __device__ constexpr int mixed_fwd_feature(int j, int s, int g, int u) {
-  if (j == 0) return u < N::NSLOT ? 2 * (g + 4 * (u >> 1)) + (u & 1) : -1;
-  if (j == 2) {
-    if (u < 4) return 4 * g + u;
-    const int k = 4 * g + (u - 4);
-    return k < N::NSH ? N::GEO + k : -1;
-  }
-  return 32 * s + 16 * (u >> 2) + 4 * g + (u & 3);
 }
 
 // Output feature consumed by backward k-slot (s, g, u) of layer j; -1 = pad.
@@ -185,17 +132,6 @@ __global__ __launch_bounds__(256) void mixed_prepare_count_kernel(
     return;
   }
   prepare_block<N>(params, wo, ops, t16, tf, g, total, tblocks, clear_flag, (int)blockIdx.x - ncount);
-}
-
-template <class N>
-__device__ __forceinline__ bf8 lds_bf8(const __bf16* A, int block, int lane) {
-  return *reinterpret_cast<const bf8*>(A + (size_t)block * Mixed<N>::BLK + lane * 8);
-}
-
-template <class N>
-__device__ __forceinline__ void load_bf16(__bf16* dst, const __bf16* __restrict__ src, int n) {
-  for (int i = threadIdx.x * 8; i < n; i += blockDim.x * 8)
-    *reinterpret_cast<float4*>(dst + i) = *reinterpret_cast<const float4*>(src + i);
 }
 
 // ---------------------------------------------------------------------------

@@ -146,6 +146,11 @@ hipError_t bin_scatter(const BinPlan& p, const RecordBuffers& rb, const SampleSr
 size_t field_prep_floats(int shape);
 size_t field_nweights(int shape);
 hipError_t field_prep(int shape, const float* params, const WOffsets& wo, float* out, hipStream_t st);
+// The operands of the rendering to out (field_prep_floats floats at most) and,
+// with dst, the request record *r (taken by value at launch) to device memory,
+// its pose [12] and intrinsics [4] read from there.
+hipError_t render_prep(int shape, const float* params, const WOffsets& wo, void* out, const nsl_render_request* r,
+                       const float* pose, const float* intr, nsl_render_request* dst, hipStream_t st);
 hipError_t field_forward(int shape, const FieldArgs& a, const SampleSrc& src, int max_samples,
                          float* sigma, float* rgb, hipStream_t st, const BinPrep* bp = nullptr);
 constexpr int kFieldBwdWaves = 4;             // waves per workgroup of the FP32 backward
@@ -176,12 +181,11 @@ struct RenderParams {
 constexpr int kRenderMaxSamples = NSL_RENDER_MAX_SAMPLES;
 // Fused rendering of the tiles of n_req requests, and of one whole image
 // (request *req, of H x W pixels).
-hipError_t render_one(int shape, const LevelInfo& lv, const Aabb& box, const nsl_render_request* req, int H, int W,
-                      const RenderParams& rp, hipStream_t st);
-hipError_t render_tiles(int shape, const LevelInfo& lv, const Aabb& box, const nsl_render_request* reqs,
-                        int n_req, const nsl_render_tile* tiles, int n_tiles, const RenderParams& rp,
-                        hipStream_t st);
-size_t field_fwd_floats(int shape);
+hipError_t render_one(int shape, const LevelInfo& lv, const Aabb& box, const WOffsets& wo,
+                      const nsl_render_request* req, int H, int W, const RenderParams& rp, hipStream_t st);
+hipError_t render_tiles(int shape, const LevelInfo& lv, const Aabb& box, const WOffsets& wo,
+                        const nsl_render_request* reqs, int n_req, const nsl_render_tile* tiles, int n_tiles,
+                        const RenderParams& rp, hipStream_t st);
 
 // field_mixed.hip: FP16 table, BF16 MLP on MFMA, FP32 accumulation.  The
 // shadow buffer holds the BF16 operands and the FP16 table copy.
@@ -320,9 +324,4 @@ hipError_t scale_end(float* state, hipStream_t st);
 // p[0, n) = 0 and, in the same launch, q[0, m) = 0 (q nullable); both
 // 16-byte aligned.
 hipError_t fill_zero(float* p, int64_t n, hipStream_t st);
-// Writes one request record to device memory (taken by value at launch),
-// with its pose [12] and intrinsics [4] read from device memory.
-hipError_t store_request(const nsl_render_request* r, const float* pose, const float* intr,
-                         nsl_render_request* dst, hipStream_t st);
-
 }  // namespace nsl

@@ -84,13 +84,6 @@ __global__ void scale_end_kernel(float* state) {
   }
 }
 
-__global__ void store_request_kernel(nsl_render_request r, const float* __restrict__ pose,
-                                     const float* __restrict__ intr, nsl_render_request* dst) {
-  for (int i = 0; i < 12; ++i) r.pose[i] = pose[i];
-  for (int i = 0; i < 4; ++i) r.intr[i] = intr[i];
-  *dst = r;
-}
-
 }  // namespace
 
 hipError_t adam_update(float* p, float* g, float* m, float* v, int64_t n, float lr, float b1,
@@ -118,12 +111,6 @@ hipError_t scale_begin(float* state, hipStream_t st) {
 
 hipError_t scale_end(float* state, hipStream_t st) {
   hipLaunchKernelGGL(scale_end_kernel, dim3(1), dim3(1), 0, st, state);
-  return hipGetLastError();
-}
-
-hipError_t store_request(const nsl_render_request* r, const float* pose, const float* intr,
-                         nsl_render_request* dst, hipStream_t st) {
-  hipLaunchKernelGGL(store_request_kernel, dim3(1), dim3(1), 0, st, *r, pose, intr, dst);
   return hipGetLastError();
 }
 

@@ -103,3 +103,83 @@ def test_render_at_block_and_round_edges(nsl, gpu, spec, n, H, Wd):
         got = a.cpu().numpy()
         assert np.all(got[px:] == -9.0), k
         check_mag(f"render edge {k}", got[:px], o[k], o[f"{k}_mag"], 1e-5)
+
+
+@pytest.mark.parametrize("stop_T", [0.0, 0.3])
+@pytest.mark.parametrize("spec", [W.C1_FIELD, W.C2_FIELD], ids=["tiny", "full"])
+def test_render_tiles_equal_the_whole_image(nsl, gpu, spec, stop_T):
+    """Ragged tiles of 1 to 64 pixels (groups of 16 that are full, partial and
+    empty, groups that stop in different rounds) give the pixels of nsl_render,
+    bit for bit."""
+    import torch
+    f = nsl.Field(spec)
+    H, Wd, n = 23, 31, 40
+    flat, _, _ = params_for(spec, f.layout, seed=2, table_range=2.0)
+    P = _t(torch, gpu, flat)
+    pose = W.look_at_pose((1.5, 0.3, 0.2)).astype(np.float32)
+    intr = np.array([0.9375 * Wd, 0.9375 * Wd, Wd / 2, H / 2], np.float32)
+    cfg = nsl.render_config(0.5, 2.0 / n, n, stop_T)
+    new = lambda: [torch.full((H * Wd, 3), -9.0, device=gpu)] + [torch.full((H * Wd,), -9.0, device=gpu) for _ in range(3)]
+    whole, tiled = new(), new()
+    ws = torch.empty(nsl.render_workspace_bytes(f, H, Wd, cfg), dtype=torch.uint8, device=gpu)
+    nsl.render(f, P, _t(torch, gpu, pose.reshape(12)), _t(torch, gpu, intr), H, Wd, cfg, ws, *whole)
+    prep = nsl.prepare(f, P)
+    rng = np.random.default_rng(3)
+    tiles, p = [], 0
+    while p < H * Wd:
+        k = int(rng.choice([1, 15, 16, 17, 31, 33, 48, 49, 64]))
+        tiles.append(nsl.RenderTile(0, p, k))
+        p += k
+    rq = nsl.records_to_device([nsl.render_request(P, prep, pose.reshape(12), intr, H, Wd, *tiled)],
+                               nsl.RenderRequest, gpu)
+    nsl.render_batch(f, rq, 1, nsl.records_to_device(tiles, nsl.RenderTile, gpu), len(tiles), cfg)
+    for a, b in zip(whole, tiled):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan, 3.4e38])
+@pytest.mark.parametrize("where", ["table", "first", "hidden"])
+def test_render_of_values_that_are_not_finite(nsl, gpu, bad, where):
+    """One value of the 16-level field that is not finite (or above the largest
+    BF16), in the table or in a weight: the rendered pixels have the same
+    finite, infinite and NaN pattern, and the same finite values within 1e-4, as
+    compositing the FP32 field's own densities and colours."""
+    import torch
+    spec = W.C2_FIELD
+    f = nsl.Field(spec)
+    lay = f.layout
+    H, Wd, n = 12, 16, 24
+    flat, _, _ = params_for(spec, lay, seed=9, table_range=0.5)
+    at = {"table": 2 * (lay["level_offset"][1] + 23 * 23 * 11 + 23 * 11 + 11), "first": lay["w_offsets"][0] + 5,
+          "hidden": lay["w_offsets"][3] + 77}[where]
+    if where == "table":
+        flat[at - 2:at + 4] = bad                       # vertices in the middle of the scene
+    else:
+        flat[at] = bad
+    P = _t(torch, gpu, flat)
+    pose = W.look_at_pose((1.5, 0.2, 0.1)).astype(np.float32)
+    intr = np.array([0.9375 * Wd, 0.9375 * Wd, Wd / 2, H / 2], np.float32)
+    dt = np.float32(2.0 / n)
+    cfg = nsl.render_config(0.5, float(dt), n, 0.0)
+    ws = torch.empty(nsl.render_workspace_bytes(f, H, Wd, cfg), dtype=torch.uint8, device=gpu)
+    op = torch.empty(H * Wd, device=gpu)
+    rgb, _, _, _ = nsl.render(f, P, _t(torch, gpu, pose.reshape(12)), _t(torch, gpu, intr), H, Wd, cfg, ws, opacity=op)
+    from oracle import rays as orays
+    o32, d32, _ = orays.rays_fp32(pose[None], intr[None], np.arange(H * Wd, dtype=np.uint32), H, Wd)
+    t = np.float32(0.5) + (np.arange(n, dtype=np.float32) + np.float32(0.5)) * dt
+    x = o32[:, None] + t[None, :, None] * d32[:, None]
+    xn = np.clip((x + np.float32(1)) * np.float32(0.5), 0, 1).astype(np.float32).reshape(-1, 3)
+    S = len(xn)
+    fw = torch.empty(f.workspace_bytes(S), dtype=torch.uint8, device=gpu)
+    sg, col = f.fwd(P, _t(torch, gpu, xn), _t(torch, gpu, np.repeat(d32, n, 0).astype(np.float32)), fw)
+    with np.errstate(all="ignore"):
+        tau = sg.cpu().numpy().reshape(-1, n).astype(np.float64) * float(dt)
+        before = np.concatenate([np.zeros((len(tau), 1)), np.cumsum(tau, 1)[:, :-1]], 1)
+        w = np.exp(-before) * -np.expm1(-tau)
+        want = (w[..., None] * col.cpu().numpy().reshape(-1, n, 3)).sum(1)
+        opw = w.sum(1)
+    for got, ref in ((rgb.cpu().numpy(), want), (op.cpu().numpy(), opw)):
+        assert np.array_equal(np.isnan(got), np.isnan(ref))
+        ok = np.isfinite(ref)
+        assert ok.any() or where != "table"
+        assert np.allclose(got[ok], ref[ok], rtol=1e-4, atol=1e-6)
