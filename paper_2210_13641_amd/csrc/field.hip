@@ -881,7 +881,7 @@ static hipError_t launch_encode(const FieldArgs& a, const SampleSrc& src, int ma
                                 const BinLevels& bl, hipStream_t st) {
   const int grid = encode_grid<N>(max_samples);
   if (grid > 0)
-    hipLaunchKernelGGL((encode_levels_kernel<N, float, float2>), dim3(grid), dim3(256), 0, st, a.lv, a.table, src,
+    hipLaunchKernelGGL((encode_levels_kernel<N, float, float2>), dim3(grid), dim3(256), kEncodeLds<N>, st, a.lv, a.table, src,
                        static_cast<float2*>(src.ecache), src.ecache_stride, hist, bl);
   return hipGetLastError();
 }

@@ -208,10 +208,21 @@ __device__ __forceinline__ void read_encoding(const E* __restrict__ ec, int stri
 // the dependent loads of its samples (ray index and t, the ray, the corners)
 // are in flight together.  Workgroups are dispatched round-robin over the 8
 // XCDs, in order; with 16 levels, the workgroups of XCD x evaluate level x
-// for every sample and then level x + 8, so at any time each XCD's L2 holds
+// for every sample and then level 15 - x, so at any time each XCD's L2 holds
 // the table slice of one level (2 MB in FP16) instead of seeing the whole
-// table, and the random corner reads hit in L2.
+// table, and the random corner reads hit in L2.  The cost of a level grows with
+// its resolution (at 2^18 samples on one XCD 17 us for level 0, 35 for level 7,
+// 41 to 49 for levels 8 to 15: its lines from L2, about 70 % of what an L2
+// returns), which is why the second eight go backwards: the dearest XCD takes
+// 77 us instead of 82.
+// At a fine level the four lines a sample touches fill the 32 KB L1 within one
+// wave; more waves a CU evict each other's lines between the two x-neighbour
+// loads.  kEncodeLds bytes of unused LDS hold a CU to three workgroups, 12
+// waves: FP16 88 -> 80 us and 10 % fewer L2 requests against eight workgroups, FP32
+// 106 -> 103 us (two workgroups: 87 and 117).
 constexpr int kEncodeUnits = 2;
+template <class N>
+constexpr size_t kEncodeLds = N::L >= 16 ? 52000 : 0;
 template <class N>
 __host__ __device__ constexpr int encode_grid(int max_samples) {
   return N::L * ((max_samples + 256 * kEncodeUnits - 1) / (256 * kEncodeUnits));
@@ -221,15 +232,17 @@ __host__ __device__ constexpr int encode_grid(int max_samples) {
 // with 16 levels, the record counting and placement), unit u being samples
 // [u * kUnitSamples, (u + 1) * kUnitSamples) of level l.  Workgroups are
 // dispatched round-robin over the 8 XCDs, in order: with a multiple of 8
-// levels, XCD x takes level x for every unit, then level x + 8, and so on, so
-// that consecutive units of a level run on one XCD; with other level counts
-// consecutive workgroups take consecutive levels.
+// levels, XCD x takes level x for every unit, then level 15 - x (then 16 + x,
+// and so on), so that consecutive units of a level run on one XCD and the fine
+// levels spread evenly; with other level counts consecutive workgroups take
+// consecutive levels.
 // wg: the workgroup's index among those of the kernel (a launch that puts
 // other work in its first workgroups passes blockIdx.x less a multiple of 8).
+__device__ __forceinline__ int xcd_level(int x, int round) { return 8 * round + (round % 2 ? 7 - x : x); }
 __device__ __forceinline__ void level_unit(int levels, int nunits, int& l, int& u, uint32_t wg) {
   if (levels % 8 == 0) {
     const int x = (int)(wg % 8u), j = (int)(wg / 8u);
-    l = x + 8 * (j / nunits);
+    l = xcd_level(x, j / nunits);
     u = j % nunits;
   } else {
     l = (int)(wg % (uint32_t)levels);
@@ -241,7 +254,7 @@ __device__ __forceinline__ void level_unit(int levels, int nunits, int& l, int& 
 }
 
 // As level_unit, but with a multiple of 8 levels the workgroups of XCD x
-// alternate between its levels x, x + 8, ... unit by unit, so that the
+// alternate between its levels x, 15 - x, ... unit by unit, so that the
 // samples' inputs that every level reads are fetched into that XCD's L2
 // once for all of its levels (for kernels that gather no table, whose L2
 // need not hold one level's slice at a time).
@@ -249,7 +262,7 @@ __device__ __forceinline__ void level_unit_interleaved(int levels, int nunits, i
   if (levels % 8 == 0) {
     const int m = levels / 8;
     const int x = (int)(wg % 8u), j = (int)(wg / 8u);
-    l = x + 8 * (j % m);
+    l = xcd_level(x, j % m);
     u = j / m;
   } else {
     level_unit(levels, nunits, l, u, wg);

@@ -879,7 +879,7 @@ static hipError_t encode_impl(const LevelInfo& lv, const void* shadow, const Sam
   const _Float16* t16 = reinterpret_cast<const _Float16*>(static_cast<const char*>(shadow) + mixed_ops_bytes<N>());
   const int grid = encode_grid<N>(max_samples);
   if (grid > 0)
-    hipLaunchKernelGGL((encode_levels_kernel<N, _Float16, uint32_t>), dim3(grid), dim3(256), 0, st, lv, t16, src,
+    hipLaunchKernelGGL((encode_levels_kernel<N, _Float16, uint32_t>), dim3(grid), dim3(256), kEncodeLds<N>, st, lv, t16, src,
                        static_cast<uint32_t*>(src.ecache), src.ecache_stride, hist, bl);
   return hipGetLastError();
 }
