@@ -66,12 +66,6 @@ __device__ __forceinline__ bf8 lds_bf8(const __bf16* A, int block, int lane) {
   return *reinterpret_cast<const bf8*>(A + (size_t)block * Mixed<N>::BLK + lane * 8);
 }
 
-template <class N>
-__device__ __forceinline__ void load_bf16(__bf16* dst, const __bf16* __restrict__ src, int n) {
-  for (int i = threadIdx.x * 8; i < n; i += blockDim.x * 8)
-    *reinterpret_cast<float4*>(dst + i) = *reinterpret_cast<const float4*>(src + i);
-}
-
 // ---------------------------------------------------------------------------
 // FP32 products on the BF16 matrix cores.  An FP32 value is the sum of three
 // BF16 values, x = h + m + l, each the nearest to what the ones before leave

@@ -242,6 +242,30 @@ __device__ __forceinline__ unsigned long long add_pair_bits(unsigned long long v
   return (unsigned long long)__float_as_uint(x) | ((unsigned long long)__float_as_uint(y) << 32);
 }
 
+// Copies BYTES (a multiple of 16) from memory to LDS with the workgroup's
+// THREADS threads, eight 16-byte loads of a thread in flight at a time.  (The
+// compiler leaves a loop of one load and its wait as it is, a memory latency a
+// pass: at 49999 samples of the 64-wide network the forward, ten passes, then
+// took 17.6 us instead of 15.9 and the backward, nineteen, 66.3 instead of 62.9.)
+template <int THREADS, int BYTES>
+__device__ __forceinline__ void copy_to_lds(void* dst, const void* __restrict__ src) {
+  static_assert(BYTES % 16 == 0, "whole 16-byte pieces");
+  constexpr int n = BYTES / 16, full = n / THREADS, kBatch = 8;
+  const f4* s = static_cast<const f4*>(src) + threadIdx.x;
+  f4* d = static_cast<f4*>(dst) + threadIdx.x;
+#pragma unroll
+  for (int p = 0; p < full; p += kBatch) {
+    f4 v[kBatch];
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k)
+      if (p + k < full) v[k] = s[(p + k) * THREADS];
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k)
+      if (p + k < full) d[(p + k) * THREADS] = v[k];
+  }
+  if (full * THREADS + (int)threadIdx.x < n) d[full * THREADS] = s[full * THREADS];
+}
+
 __device__ __forceinline__ f4 mfma4(float a, float b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }

@@ -183,7 +183,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
     return;
   }
   __shared__ __attribute__((aligned(16))) float Af[N::FWD_FLOATS];
-  load_operands<N>(Af, a.wprep, N::FWD_FLOATS);
+  copy_to_lds<256, sizeof(Af)>(Af, a.wprep);
   __syncthreads();
   const int S = src.n_dev ? (int)*src.n_dev : src.n;
   const int ntiles = (S + 15) / 16;
@@ -270,8 +270,8 @@ __global__ __launch_bounds__(kFieldBwdWaves * kWave, 1) void field_bwd_kernel(Fi
   __shared__ __attribute__((aligned(16))) float Ab[N::BWD_FLOATS];
   __shared__ __attribute__((aligned(16))) float dW[N::NWEIGHTS];
   __shared__ __attribute__((aligned(16))) float stage_all[kFieldBwdWaves * N::STAGE_FLOATS];
-  load_operands<N>(Af, a.wprep, N::FWD_FLOATS);
-  load_operands<N>(Ab, a.wprep + N::FWD_FLOATS, N::BWD_FLOATS);
+  copy_to_lds<kFieldBwdWaves * kWave, sizeof(Af)>(Af, a.wprep);
+  copy_to_lds<kFieldBwdWaves * kWave, sizeof(Ab)>(Ab, a.wprep + N::FWD_FLOATS);
   for (int i = threadIdx.x; i < N::NWEIGHTS; i += blockDim.x) dW[i] = 0.0f;
   __syncthreads();
 
@@ -659,10 +659,7 @@ __global__ __launch_bounds__(kRenderThreads<N>) __attribute__((amdgpu_waves_per_
     v = min(v, reqs[0].H - 1);
   }
   const nsl_render_request& rq = reqs[req];
-  if constexpr (kSplitNet<N>)
-    load_bf16<N>(Af, static_cast<const __bf16*>(rq.prepared), kOps);
-  else
-    load_operands<N>(Af, static_cast<const float*>(rq.prepared), kOps);
+  copy_to_lds<kRenderThreads<N>, sizeof(Af)>(Af, rq.prepared);
   __syncthreads();
   LaneLevels<N> ll;
   lane_levels<N>(lv, g, ll);

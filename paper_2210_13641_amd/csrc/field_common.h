@@ -550,10 +550,4 @@ __host__ inline hipError_t launch_dw_reduce(const float* partial, int nblocks, c
   return hipGetLastError();
 }
 
-template <class N>
-__device__ __forceinline__ void load_operands(float* dst, const float* __restrict__ src, int n) {
-  for (int i = threadIdx.x * 4; i < n; i += blockDim.x * 4)
-    *reinterpret_cast<float4*>(dst + i) = *reinterpret_cast<const float4*>(src + i);
-}
-
 }  // namespace nsl

@@ -672,8 +672,8 @@ __global__ __launch_bounds__(kBwdWaves8 * kWave, 1) void mixed_bwd8_kernel(
   __shared__ __attribute__((aligned(16))) __bf16 Af[M::FWD];
   __shared__ __attribute__((aligned(16))) __bf16 Ab[M::BWD];
   __shared__ __attribute__((aligned(16))) __bf16 stage[2 * SBUF];
-  load_bf16<N>(Af, prep, M::FWD);
-  load_bf16<N>(Ab, prep + M::FWD, M::BWD);
+  copy_to_lds<kBwdWaves8 * kWave, sizeof(Af)>(Af, prep);
+  copy_to_lds<kBwdWaves8 * kWave, sizeof(Ab)>(Ab, prep + M::FWD);
   __syncthreads();
 
   const int S = src.n_dev ? (int)*src.n_dev : src.n;
@@ -766,7 +766,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void m
     return;
   }
   __shared__ __attribute__((aligned(16))) __bf16 Af[M::FWD];
-  load_bf16<N>(Af, prep, M::FWD);
+  copy_to_lds<256, sizeof(Af)>(Af, prep);
   __syncthreads();
   const int S = src.n_dev ? (int)*src.n_dev : src.n;
   const int ntiles = (S + 15) / 16;
