@@ -233,202 +233,253 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
 // Backward
 // ---------------------------------------------------------------------------
 
-// acc[in][out] += sum over the wave's 16 samples of X[in] * dY[out], with X
-// and dY staged [feature][sample] (stride SROW) in this wave's LDS area.
-template <class N, int KIN, int KOUT>
-__device__ __forceinline__ void dw_accumulate(const float* Xs, const float* Ys, DWAcc<KIN, KOUT>& acc, int lane) {
-  constexpr int MI = DWAcc<KIN, KOUT>::MI, NJ = DWAcc<KIN, KOUT>::NJ;
-  const int gk = lane >> 4, i = lane & 15;
-  f4 xa[MI], yb[NJ];
-#pragma unroll
-  for (int m = 0; m < MI; ++m) xa[m] = *reinterpret_cast<const f4*>(Xs + (16 * m + i) * N::SROW + 4 * gk);
-#pragma unroll
-  for (int n = 0; n < NJ; ++n) yb[n] = *reinterpret_cast<const f4*>(Ys + (16 * n + i) * N::SROW + 4 * gk);
-#pragma unroll
-  for (int m = 0; m < MI; ++m)
-#pragma unroll
-    for (int n = 0; n < NJ; ++n)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) acc.v[m * NJ + n] = mfma4(xa[m][s], yb[n][s], acc.v[m * NJ + n]);
-}
+constexpr int kBwdStep = 16 * kFieldBwdWaves;  // samples of a workgroup's step
+constexpr int kBwdRow = kBwdStep + 4;          // floats of a staged row (the pad steps rows through the LDS banks)
 
-// Stage a D-layout activation block (tiles of 16 rows) as rows [row0, ...).
-template <class N, int TILES>
-__device__ __forceinline__ void stage_d(float* S, const f4* v, int g, int jc) {
+// Weight gradient of layer J, kin x kout in 16x16 tiles: the workgroup's waves
+// own consecutive tiles, or with fewer tiles than waves share one, each taking
+// its part of a step's samples.  Tile (m, n), lane (gk, i) holds
+// dW[16m + 4gk + r][16n + i], in two sums so that products in a row are independent.
+template <class N, int J>
+struct OwnedDW {
+  static constexpr int W = kFieldBwdWaves;
+  static constexpr int MI = (N::kin(J) + 15) / 16, NJ = (N::kout(J) + 15) / 16, TILES = MI * NJ;
+  static_assert(TILES % W == 0 || W % TILES == 0, "whole tiles a wave or whole waves a tile");
+  static constexpr int SLOTS = TILES >= W ? TILES / W : 1, SPLIT = TILES >= W ? 1 : W / TILES;
+  static constexpr int CHUNKS = W / SPLIT;  // 16-sample pieces of a step a wave takes
+  f4 v[SLOTS][2];
+  __device__ __forceinline__ void zero() {
+#pragma unroll
+    for (int k = 0; k < SLOTS; ++k) v[k][0] = v[k][1] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+  }
+  static __device__ __forceinline__ int tile(int w, int k) { return SPLIT == 1 ? w * SLOTS + k : w % TILES; }
+  __device__ __forceinline__ void chunk(const float* Xs, const float* Ys, int w, int lane, int c, int odd) {
+    const int gk = lane >> 4, i = lane & 15;
+#pragma unroll
+    for (int k = 0; k < SLOTS; ++k) {
+      const int t = tile(w, k), m = t / NJ, n = t % NJ;
+      const f4 x = *reinterpret_cast<const f4*>(Xs + (16 * m + i) * kBwdRow + 16 * c + 4 * gk);
+      const f4 y = *reinterpret_cast<const f4*>(Ys + (16 * n + i) * kBwdRow + 16 * c + 4 * gk);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[k][odd] = mfma4(x[q], y[q], v[k][odd]);
+    }
+  }
+  // += X^T dY over the step's first nt pieces of 16 samples, staged
+  // [feature][sample]
+  __device__ __forceinline__ void add(const float* Xs, const float* Ys, int w, int lane, int nt) {
+    const int c0 = SPLIT == 1 ? 0 : w / TILES * CHUNKS;
+    if (nt == W) {
+#pragma unroll
+      for (int c = 0; c < CHUNKS; ++c) chunk(Xs, Ys, w, lane, c0 + c, c & 1);
+    } else {
+#pragma unroll 1
+      for (int c = c0; c < min(nt, c0 + CHUNKS); ++c) chunk(Xs, Ys, w, lane, c, 0);
+    }
+  }
+  // The workgroup's sums to out (row-major kin x kout); waves that share a
+  // tile meet in LDS.
+  __device__ __forceinline__ void store(float* lds, float* __restrict__ out, int w, int lane) const {
+    const int gk = lane >> 4, i = lane & 15;
+    if constexpr (SPLIT > 1) {
+      __syncthreads();
+      *reinterpret_cast<f4*>(lds + (w * kWave + lane) * 4) = v[0][0] + v[0][1];
+      __syncthreads();
+      if (w >= TILES) return;
+    }
+#pragma unroll
+    for (int k = 0; k < SLOTS; ++k) {
+      const int t = tile(w, k), m = t / NJ, n = t % NJ, col = 16 * n + i;
+      f4 sum = v[k][0] + v[k][1];
+      if constexpr (SPLIT > 1) {
+#pragma unroll
+        for (int p = 1; p < SPLIT; ++p) sum += *reinterpret_cast<const f4*>(lds + ((w + p * TILES) * kWave + lane) * 4);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * m + 4 * gk + r;
+        if (row < N::kin(J) && col < N::kout(J)) out[row * N::kout(J) + col] = sum[r];
+      }
+    }
+  }
+};
+
+// Stage a D-layout activation block (tiles of 16 rows) from row S on.
+template <int TILES>
+__device__ __forceinline__ void stage_d(float* S, const f4* v, int g) {
 #pragma unroll
   for (int m = 0; m < TILES; ++m)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) S[(16 * m + 4 * g + r) * N::SROW + jc] = v[m][r];
+    for (int r = 0; r < 4; ++r) S[(16 * m + 4 * g + r) * kBwdRow] = v[m][r];
 }
 
+// out[m] = sum over the k-steps s of W (tile m, step s; 64 floats each from A
+// on) times x(s).
+template <int MT, int KS, class X>
+__device__ __forceinline__ void bwd_products(const float* A, int lane, const X& x, f4 (&out)[MT]) {
+#pragma unroll
+  for (int m = 0; m < MT; ++m) out[m] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int s = 0; s < KS; ++s)
+#pragma unroll
+    for (int m = 0; m < MT; ++m) out[m] = mfma4(A[(m * KS + s) * kWave + lane], x(s), out[m]);
+}
+
+// acc where the ReLU output h is above zero, else 0.
+template <int K>
+__device__ __forceinline__ void relu_mask(f4 (&acc)[K], const f4 (&h)[K]) {
+#pragma unroll
+  for (int m = 0; m < K; ++m)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc[m][r] = h[m][r] > 0.0f ? acc[m][r] : 0.0f;
+}
+
+// Eight waves a workgroup, two a SIMD.  Each wave recomputes the forward and
+// runs the input-gradient chain of 16 samples; the 128 samples of the
+// workgroup's step are staged a layer at a time, and each wave adds the
+// products of its own weight-gradient tiles over all of them.  It then holds
+// six of the 40 tiles instead of all, which leaves the registers for a second wave
+// on the SIMD: bound by the FP32 matrix instructions, and a lone wave idles them
+// whenever it waits for its own operands (60% busy, also with two tiles of 16
+// samples at a time).  At 262k samples of the 64-wide network 177 us with four
+// waves that hold all tiles, 148 so, of which 98 are matrix cycles; at 49999 samples
+// 51.8 and 42; the 32-wide network at 131072 samples 36.3 and 30.7.
 template <class N>
-__global__ __launch_bounds__(kFieldBwdWaves * kWave, 1) void field_bwd_kernel(FieldArgs a, SampleSrc src,
+__global__ __launch_bounds__(kFieldBwdWaves * kWave, 2) void field_bwd_kernel(FieldArgs a, SampleSrc src,
                                                            const float* __restrict__ dsigma,
                                                            const float* __restrict__ drgb, RecordBuffers rec,
                                                            float* __restrict__ dw_partial) {
-  __shared__ __attribute__((aligned(16))) float Af[N::FWD_FLOATS];
-  __shared__ __attribute__((aligned(16))) float Ab[N::BWD_FLOATS];
-  __shared__ __attribute__((aligned(16))) float dW[N::NWEIGHTS];
-  __shared__ __attribute__((aligned(16))) float stage_all[kFieldBwdWaves * N::STAGE_FLOATS];
-  copy_to_lds<kFieldBwdWaves * kWave, sizeof(Af)>(Af, a.wprep);
-  copy_to_lds<kFieldBwdWaves * kWave, sizeof(Ab)>(Ab, a.wprep + N::FWD_FLOATS);
-  for (int i = threadIdx.x; i < N::NWEIGHTS; i += blockDim.x) dW[i] = 0.0f;
+  constexpr int kOps = N::FWD_FLOATS + N::BWD_FLOATS, H = N::HC / 16, D = N::HD / 16;
+  __shared__ __attribute__((aligned(16))) float ops[kOps];
+  __shared__ __attribute__((aligned(16))) float stage[(N::XROWS + N::YROWS) * kBwdRow];
+  const float *Af = ops, *Ab = ops + N::FWD_FLOATS;
+  copy_to_lds<kFieldBwdWaves * kWave, (int)sizeof(ops)>(ops, a.wprep);
   __syncthreads();
 
-  const int S = src.n_dev ? (int)*src.n_dev : src.n;
-  const int ntiles = (S + 15) / 16;
-  const int wave = threadIdx.x / kWave;
+  const uint32_t S = src.n_dev ? *src.n_dev : (uint32_t)src.n;
+  const int w = threadIdx.x / kWave;
   const int lane = lane_id(), g = lane >> 4, jc = lane & 15;
-  float* Xs = stage_all + wave * N::STAGE_FLOATS;
-  float* Ys = Xs + N::XROWS * N::SROW;
+  const float *Xs = stage, *Ys = stage + N::XROWS * kBwdRow;
+  float *Xw = stage + 16 * w + jc, *Yw = Xw + N::XROWS * kBwdRow;  // this lane's column
   LaneLevels<N> ll;
   lane_levels<N>(a.lv, g, ll);
-  constexpr f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-  const int region = blockIdx.x * kFieldBwdWaves + wave;
-  // weight gradients of the wave, summed over its tiles in registers
-  DWAcc<N::ENC, N::HD> dw0;
-  DWAcc<N::HD, 16> dw1;
-  DWAcc<N::CIN, N::HC> dw2;
-  DWAcc<N::HC, N::HC> dw3;  // second colour hidden layer (unused with one)
-  DWAcc<N::HC, 3> dwl;
+  OwnedDW<N, 0> dw0;
+  OwnedDW<N, 1> dw1;
+  OwnedDW<N, 2> dw2;
+  OwnedDW<N, N::NCH == 2 ? 3 : 2> dw3;  // second colour hidden layer (unused with one)
+  OwnedDW<N, N::NW - 1> dwl;
   dw0.zero(); dw1.zero(); dw2.zero(); dwl.zero();
   if constexpr (N::NCH == 2) dw3.zero();
 
-  for (int tile = region; tile < ntiles; tile += gridDim.x * kFieldBwdWaves) {
-    const int s = tile * 16 + jc;
+  // inputs of a tile: encoding slots, direction and (lane group 0) seeds; with
+  // the encoding given, those of the next step are fetched while this one is
+  // computed (ray indices two steps ahead)
+  struct In {
+    float e[N::NSLOT], d[3], ds, dr[3];
+  };
+  auto rid = [&](uint32_t s) -> uint32_t { return src.t && s < S ? src.ray[s] : 0u; };
+  auto seeds = [&](uint32_t s, In& in) {
+    in.ds = in.dr[0] = in.dr[1] = in.dr[2] = 0.0f;
+    if (g != 0 || s >= S) return;
+    in.ds = dsigma[s];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) in.dr[r] = drgb[3 * (size_t)s + r];
+  };
+  const uint32_t stride = kBwdStep * gridDim.x;  // samples
+  In in;
+  uint32_t rid1 = 0u;
+  if (src.ecache) {
+    const uint32_t s0 = kBwdStep * blockIdx.x + 16 * w + jc;
+    fetch_kept<N>(src, g, s0, s0 < S, rid(s0), in.e, in.d);
+    seeds(s0, in);
+    rid1 = rid(s0 + stride);
+  }
+  for (uint32_t p = kBwdStep * blockIdx.x; p < S; p += stride) {
+    const uint32_t s = p + 16 * w + jc;
     const bool valid = s < S;
-    float xn[3] = {0.5f, 0.5f, 0.5f}, d[3] = {0.0f, 0.0f, 1.0f};
-    if (valid) {
-      if (src.ecache)
-        load_direction(src, s, d);  // the position is not needed with the encoding given
-      else
-        load_sample(src, s, xn, d);
-    }
-    Acts<N> act;
+    const int nt = (int)min((uint32_t)kFieldBwdWaves, (S - p + 15) / 16);  // tiles of 16 samples in this step
+    In next;
     if (src.ecache) {
-      read_encoding<N>(static_cast<const float2*>(src.ecache), src.ecache_stride, g, s, valid, act.e);
+      const uint32_t s1 = s + stride;
+      fetch_kept<N>(src, g, s1, s1 < S, rid1, next.e, next.d);
+      seeds(s1, next);
+      rid1 = rid(s1 + stride);
     } else {
-      encode<N>(a.table, a.lv.table_mask, ll, xn, act.e);
+      float xn[3] = {0.5f, 0.5f, 0.5f};
+      in.d[0] = in.d[1] = 0.0f;
+      in.d[2] = 1.0f;
+      if (valid) load_sample(src, s, xn, in.d);
+      encode<N>(a.table, a.lv.table_mask, ll, xn, in.e);
       if (!valid) {
 #pragma unroll
-        for (int k = 0; k < N::NSLOT; ++k) act.e[k] = 0.0f;
+        for (int k = 0; k < N::NSLOT; ++k) in.e[k] = 0.0f;
       }
+      seeds(s, in);
+      next = in;
     }
-    sh_lane<N>(d, g, act.sh);
+    Acts<N> act;
+#pragma unroll
+    for (int k = 0; k < N::NSLOT; ++k) act.e[k] = in.e[k];
+    sh_lane<N>(in.d, g, act.sh);
     mlp_fwd<N>(Af, lane, act);
 
     // seeds: dz = dc * c (1 - c) and dsigma, on lane group 0
-    float ds = 0.0f;
-    f4 dz = zero;
-    if (g == 0 && valid) {
-      ds = dsigma[s];
+    f4 dz = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (g == 0) {
 #pragma unroll
       for (int r = 0; r < 3; ++r) {
         const float c = sigmoidf(act.z[r]);
-        dz[r] = drgb[3 * s + r] * c * (1.0f - c);
+        dz[r] = in.dr[r] * c * (1.0f - c);
       }
     }
     // last layer: dh_last = W_last dz, masked
-    const f4* hl = (N::NCH == 2) ? act.h4 : act.h3;
-    f4 dhl[N::HC / 16];
-    {
-      const float* A = Ab + N::boff(N::NW - 1) + lane;
-#pragma unroll
-      for (int m = 0; m < N::HC / 16; ++m) {
-        f4 acc = zero;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) acc = mfma4(A[(m * 3 + k) * kWave], dz[k], acc);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[r] = hl[m][r] > 0.0f ? acc[r] : 0.0f;
-        dhl[m] = acc;
-      }
-    }
-    // dW of the last layer
-    stage_d<N, N::HC / 16>(Xs, hl, g, jc);
-    stage_d<N, 1>(Ys, &dz, g, jc);
-    wave_lds_fence();
-    dw_accumulate<N, N::HC, 3>(Xs, Ys, dwl, lane);
-    wave_lds_fence();
-
-    f4 dh3[N::HC / 16];
+    const f4(&hl)[H] = N::NCH == 2 ? act.h4 : act.h3;
+    f4 dhl[H];
+    bwd_products<H, 3>(Ab + N::boff(N::NW - 1), lane, [&](int k) { return dz[k]; }, dhl);
+    relu_mask(dhl, hl);
+    // Between the two barriers of a layer, the weight-gradient products of
+    // the step's samples and the next input-gradient product, which are independent.
+    __syncthreads();
+    stage_d<H>(Xw, hl, g);
+    stage_d<1>(Yw, &dz, g);
+    __syncthreads();
+    dwl.add(Xs, Ys, w, lane, nt);
+    f4 dh3[H];
     if constexpr (N::NCH == 2) {
-      const float* A = Ab + N::boff(3) + lane;
-#pragma unroll
-      for (int m = 0; m < N::HC / 16; ++m) {
-        f4 acc = zero;
-#pragma unroll
-        for (int k = 0; k < N::HC / 4; ++k) acc = mfma4(A[(m * (N::HC / 4) + k) * kWave], dhl[k >> 2][k & 3], acc);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[r] = act.h3[m][r] > 0.0f ? acc[r] : 0.0f;
-        dh3[m] = acc;
-      }
-      stage_d<N, N::HC / 16>(Xs, act.h3, g, jc);
-      stage_d<N, N::HC / 16>(Ys, dhl, g, jc);
-      wave_lds_fence();
-      dw_accumulate<N, N::HC, N::HC>(Xs, Ys, dw3, lane);
-      wave_lds_fence();
+      bwd_products<H, N::HC / 4>(Ab + N::boff(3), lane, [&](int k) { return dhl[k >> 2][k & 3]; }, dh3);
+      relu_mask(dh3, act.h3);
+      __syncthreads();
+      stage_d<H>(Xw, act.h3, g);
+      stage_d<H>(Yw, dhl, g);
+      __syncthreads();
+      dw3.add(Xs, Ys, w, lane, nt);
     } else {
 #pragma unroll
-      for (int m = 0; m < N::HC / 16; ++m) dh3[m] = dhl[m];
+      for (int m = 0; m < H; ++m) dh3[m] = dhl[m];
     }
     // colour input layer: d(geo) = W3[geo rows] dh3; dW3 with X = [o, sh]
-    f4 dgeo = zero;
-    {
-      const float* A = Ab + N::boff(2) + lane;
+    f4 dgeo[1];
+    bwd_products<1, N::HC / 4>(Ab + N::boff(2), lane, [&](int k) { return dh3[k >> 2][k & 3]; }, dgeo);
+    __syncthreads();
+    stage_d<1>(Xw, &act.o, g);
 #pragma unroll
-      for (int k = 0; k < N::HC / 4; ++k) dgeo = mfma4(A[k * kWave], dh3[k >> 2][k & 3], dgeo);
-    }
-    stage_d<N, 1>(Xs, &act.o, g, jc);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) Xs[(16 + 4 * g + r) * N::SROW + jc] = act.sh[r];
-    stage_d<N, N::HC / 16>(Ys, dh3, g, jc);
-    wave_lds_fence();
-    dw_accumulate<N, N::CIN, N::HC>(Xs, Ys, dw2, lane);
-    wave_lds_fence();
+    for (int r = 0; r < 4; ++r) Xw[(16 + 4 * g + r) * kBwdRow] = act.sh[r];
+    stage_d<H>(Yw, dh3, g);
+    __syncthreads();
+    dw2.add(Xs, Ys, w, lane, nt);
     // density output: do = dgeo, do_0 += sigma * dsigma
-    if (g == 0) dgeo[0] += __expf(act.o[0]) * ds;
-    f4 dh1[N::HD / 16];
-    {
-      const float* A = Ab + N::boff(1) + lane;
-#pragma unroll
-      for (int m = 0; m < N::HD / 16; ++m) {
-        f4 acc = zero;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) acc = mfma4(A[(m * 4 + k) * kWave], dgeo[k], acc);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[r] = act.h1[m][r] > 0.0f ? acc[r] : 0.0f;
-        dh1[m] = acc;
-      }
-    }
-    stage_d<N, N::HD / 16>(Xs, act.h1, g, jc);
-    stage_d<N, 1>(Ys, &dgeo, g, jc);
-    wave_lds_fence();
-    dw_accumulate<N, N::HD, 16>(Xs, Ys, dw1, lane);
-    wave_lds_fence();
+    if (g == 0) dgeo[0][0] += __expf(act.o[0]) * in.ds;
+    f4 dh1[D];
+    bwd_products<D, 4>(Ab + N::boff(1), lane, [&](int k) { return dgeo[0][k]; }, dh1);
+    relu_mask(dh1, act.h1);
+    __syncthreads();
+    stage_d<D>(Xw, act.h1, g);
+    stage_d<1>(Yw, dgeo, g);
+    __syncthreads();
+    dw1.add(Xs, Ys, w, lane, nt);
     // encoding gradient: de = W1 dh1 (rows = this lane group's slots)
     constexpr int MT0 = N::bmt(0);
     f4 de[MT0];
-    {
-      const float* A = Ab + N::boff(0) + lane;
-#pragma unroll
-      for (int m = 0; m < MT0; ++m) {
-        f4 acc = zero;
-#pragma unroll
-        for (int k = 0; k < N::HD / 4; ++k) acc = mfma4(A[(m * (N::HD / 4) + k) * kWave], dh1[k >> 2][k & 3], acc);
-        de[m] = acc;
-      }
-    }
-    // dW1 with X = e (slots -> features)
-#pragma unroll
-    for (int k = 0; k < N::NSLOT; ++k) Xs[fwd_in_feature<N>(0, k, g) * N::SROW + jc] = act.e[k];
-    if constexpr (N::ENC < 16) {
-#pragma unroll
-      for (int k = 0; k < 2; ++k) Xs[(N::ENC + 2 * g + k) * N::SROW + jc] = 0.0f;
-    }
-    stage_d<N, N::HD / 16>(Ys, dh1, g, jc);
-    wave_lds_fence();
-    dw_accumulate<N, N::ENC, N::HD>(Xs, Ys, dw0, lane);
-    wave_lds_fence();
+    bwd_products<MT0, N::HD / 4>(Ab + N::boff(0), lane, [&](int k) { return dh1[k >> 2][k & 3]; }, de);
     // dL/de of this lane's levels g + 4q, level-major: the 16 lanes of a row
     // store 16 consecutive samples of one level
     if (valid) {
@@ -438,24 +489,22 @@ __global__ __launch_bounds__(kFieldBwdWaves * kWave, 1) void field_bwd_kernel(Fi
         rec.de[(size_t)(g + 4 * q) * rec.stride + s] = make_float2(de[k0 >> 2][k0 & 3], de[k1 >> 2][k1 & 3]);
       }
     }
-  }
-  // workgroup sum of the weight gradients: waves add in turn (no atomics)
-  for (int w = 0; w < kFieldBwdWaves; ++w) {
+    // dW1 with X = e (slots -> features; rows past the features feed no weight)
     __syncthreads();
-    if (wave == w) {
-      dw0.flush(dW + N::woff(0), lane);
-      dw1.flush(dW + N::woff(1), lane);
-      dw2.flush(dW + N::woff(2), lane);
-      if constexpr (N::NCH == 2) dw3.flush(dW + N::woff(3), lane);
-      dwl.flush(dW + N::woff(N::NW - 1), lane);
-    }
+#pragma unroll
+    for (int k = 0; k < N::NSLOT; ++k) Xw[fwd_in_feature<N>(0, k, g) * kBwdRow] = act.e[k];
+    stage_d<D>(Yw, dh1, g);
+    __syncthreads();
+    dw0.add(Xs, Ys, w, lane, nt);
+    in = next;
   }
-  __syncthreads();
   float* out = dw_partial + (size_t)blockIdx.x * N::NWEIGHTS;
-  for (int i = threadIdx.x; i < N::NWEIGHTS; i += blockDim.x) out[i] = dW[i];
+  dw0.store(stage, out + N::woff(0), w, lane);
+  dw1.store(stage, out + N::woff(1), w, lane);
+  dw2.store(stage, out + N::woff(2), w, lane);
+  if constexpr (N::NCH == 2) dw3.store(stage, out + N::woff(3), w, lane);
+  dwl.store(stage, out + N::woff(N::NW - 1), w, lane);
 }
-
-
 
 // Networks whose rendering runs on the BF16 matrix cores in three parts
 // (bf16_ops.h): the 64-wide ones.  At 640x480 x 64 samples of the paper-scale map

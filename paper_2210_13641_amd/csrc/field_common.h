@@ -414,35 +414,6 @@ __device__ __forceinline__ float row_sum(float v) {
   return v;
 }
 
-// Weight-gradient tile set of one layer (KIN x KOUT, padded to 16 x 16
-// tiles), kept as MFMA accumulators in registers across all tiles a wave
-// processes: tile (m, n), lane (gk, i) holds dW[16m + 4gk + r][16n + i].
-template <int KIN, int KOUT>
-struct DWAcc {
-  static constexpr int MI = (KIN + 15) / 16, NJ = (KOUT + 15) / 16;
-  f4 v[MI * NJ];
-  __device__ __forceinline__ void zero() {
-#pragma unroll
-    for (int t = 0; t < MI * NJ; ++t) v[t] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-  }
-  // dW (LDS, row-major KIN x KOUT) += this wave's sums; plain read-modify-
-  // write, so the waves of a workgroup call it one at a time.
-  __device__ __forceinline__ void flush(float* dW, int lane) const {
-    const int gk = lane >> 4, i = lane & 15;
-#pragma unroll
-    for (int m = 0; m < MI; ++m)
-#pragma unroll
-      for (int n = 0; n < NJ; ++n) {
-        const int col = 16 * n + i;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = 16 * m + 4 * gk + r;
-          if (row < KIN && col < KOUT) dW[row * KOUT + col] += v[m * NJ + n][r];
-        }
-      }
-  }
-};
-
 // LDS scratch of the sums below (floats), passed in by the kernel, which may
 // lend memory it uses otherwise.
 constexpr int kSumScratchFloats = 512;

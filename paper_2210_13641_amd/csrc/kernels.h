@@ -153,7 +153,7 @@ hipError_t render_prep(int shape, const float* params, const WOffsets& wo, void*
                        const float* pose, const float* intr, nsl_render_request* dst, hipStream_t st);
 hipError_t field_forward(int shape, const FieldArgs& a, const SampleSrc& src, int max_samples,
                          float* sigma, float* rgb, hipStream_t st, const BinPrep* bp = nullptr);
-constexpr int kFieldBwdWaves = 4;             // waves per workgroup of the FP32 backward
+constexpr int kFieldBwdWaves = 8;             // waves per workgroup of the FP32 backward
 // Writes dL/de of every sample to rec.de and the weight gradients of each
 // workgroup to partial[nblocks][weights]; field_dw_reduce then adds them
 // into grads and bin_scatter the table gradient.

@@ -77,12 +77,10 @@ struct Net {
   }
   static constexpr int NWEIGHTS = woff(NW - 1) + wsize(NW - 1);
 
-  // staging rows for the dW transposes (X rows then dY rows), 20-float stride
+  // staging rows for the dW transposes (X rows then dY rows)
   static constexpr int cmax(int a, int b) { return a > b ? a : b; }
   static constexpr int XROWS = cmax(cmax((ENC + 15) / 16 * 16, HD), cmax(32, HC));
   static constexpr int YROWS = cmax(HD, HC);
-  static constexpr int SROW = 20;
-  static constexpr int STAGE_FLOATS = (XROWS + YROWS) * SROW;
 };
 
 using NetTiny = Net<4, 32, 1, 32, 3>;

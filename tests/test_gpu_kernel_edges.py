@@ -9,7 +9,7 @@ import workloads as W
 from oracle import covariance as ocov
 from oracle import field as ofield
 from oracle import step as ostep
-from parity import check_mag, params_for
+from parity import check_mag, params_for, split_grads
 
 pytestmark = pytest.mark.gpu
 
@@ -48,6 +48,35 @@ def test_scatter_of_single_bin_levels(nsl, gpu, spec, S):
             check_mag(f"single-bin scatter p{prec}", g[:nt], gt + before, gtm + before, tol)
             assert np.all(g[nt:] == 0.5)
             assert np.all(g[:nt][gtm == 0] == before)
+
+
+@pytest.mark.parametrize("spec", [W.C1_FIELD, W.C2_FIELD], ids=["tiny", "full"])
+@pytest.mark.parametrize("S", [1, 16, 17, 113, 128, 129, 32768, 32897, 65553])
+def test_mlp_backward_at_step_edges(nsl, gpu, spec, S):
+    """nsl_mlp_bwd around its tiles of 16 samples, steps of 128 and rounds of
+    256 workgroups: dL/de and the weight gradients at 1e-5 of their magnitudes,
+    as the entry-point test."""
+    import torch
+    f = nsl.Field(spec)
+    L = spec.levels
+    flat, _, w64 = params_for(spec, f.layout, seed=6, table_range=0.5)
+    rng = np.random.default_rng(S)
+    e = rng.normal(scale=0.3, size=(S, 2 * L)).astype(np.float32)
+    d = rng.normal(size=(S, 3))
+    d = (d / np.linalg.norm(d, axis=1, keepdims=True)).astype(np.float32)
+    dsig = rng.normal(size=S).astype(np.float32)
+    drgb = rng.normal(size=(S, 3)).astype(np.float32)
+    ws = torch.empty(f.workspace_bytes(S), dtype=torch.uint8, device=gpu)
+    G = torch.full((f.layout["total"],), 0.5, device=gpu)
+    de = nsl.mlp_bwd(f, _t(torch, gpu, flat), _t(torch, gpu, e.reshape(S, L, 2).transpose(1, 0, 2)), _t(torch, gpu, d),
+                     _t(torch, gpu, dsig), _t(torch, gpu, drgb), G, ws).cpu().numpy()
+    e64, ds64, dc64 = e.astype(np.float64), dsig.astype(np.float64), drgb.astype(np.float64)
+    cache = ofield.mlp_fwd(spec, w64, e64, np.abs(e64), ofield.sh_basis(d.astype(np.float64), spec.sh_bands))
+    dWs, dWm, de_o, dem = ofield.mlp_bwd(spec, w64, cache, ds64, np.abs(ds64), dc64, np.abs(dc64))
+    check_mag("step-edge dL/de", de.transpose(1, 0, 2).reshape(S, 2 * L), de_o, dem, 1e-5)
+    _, gws = split_grads(G.cpu().numpy().astype(np.float64), f.layout, spec)
+    for j, (a, b, m) in enumerate(zip(gws, dWs, dWm)):
+        check_mag(f"step-edge grad W{j}", a, b + 0.5, m + 0.5, 1e-5)
 
 
 @pytest.mark.parametrize("c,p", [(1, 1), (15, 63), (16, 64), (17, 257), (48, 300), (60, 65), (60, 70001)])
