@@ -1,8 +1,6 @@
 // Mixed-precision hash-grid field on gfx950: FP16 tables, BF16 weights and
 // activations on v_mfma_f32_16x16x32_bf16 with FP32 accumulation (weight
-// gradients too, with samples on the contraction axis, on 32x32x16 tiles
-// where a layer's widths allow),
-// FP32 trilinear blending, FP32 table-gradient accumulation.
+// gradients too, with samples on the contraction axis), FP32 trilinear blending, FP32 table-gradient accumulation.
 //
 // Operand layouts follow the FP32 kernels (features as rows, 16 samples as
 // columns): a 16x16x32 k-step takes 8 consecutive k-slots per lane group,
@@ -15,20 +13,8 @@
 
 namespace nsl {
 
-typedef float f16v __attribute__((ext_vector_type(16)));
-
-__device__ __forceinline__ f16v mfma32x32(bf8 a, bf8 b, f16v c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-
-typedef short s8v __attribute__((ext_vector_type(8)));
-
-// Element u of a as 16 bits.  The whole vector is reinterpreted first: the
-// gfx950 compiler lowers a bit cast of one extracted __bf16 element to
-// element 0 whatever the index.
-__device__ __forceinline__ uint32_t bf_bits(bf8 a, int u) {
-  return (uint32_t)(uint16_t)__builtin_bit_cast(s8v, a)[u];
-}
+typedef short s4 __attribute__((ext_vector_type(4)));
+typedef short s8 __attribute__((ext_vector_type(8)));
 
 // Output feature consumed by backward k-slot (s, g, u) of layer j; -1 = pad.
 template <class N>
@@ -243,37 +229,24 @@ __device__ __forceinline__ uint32_t ray_of(const SampleSrc& src, int s, int S) {
   return src.t && s < S ? src.ray[s] : 0u;
 }
 
-// K consecutive weight-operand blocks of one layer.
-template <class N, int K>
-__device__ __forceinline__ void load_ops(const __bf16* A, int lane, bf8 (&w)[K]) {
-#pragma unroll
-  for (int k = 0; k < K; ++k) w[k] = lds_bf8<N>(A, k, lane);
-}
-
-// Forward of T tiles, interleaved layer by layer; each layer's weight
-// operands are read from LDS one layer ahead, so the reads overlap the
-// previous layer's MFMAs instead of each waiting in front of its own.
+// Forward of T tiles, interleaved layer by layer.
 template <class N, int T>
 __device__ __forceinline__ void fwd_tiles(const __bf16* __restrict__ Af, int lane, const f4 (&sh)[T],
                                           PActs<N> (&a)[T]) {
   using M = Mixed<N>;
   constexpr f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-  constexpr int K3 = N::NCH == 2 ? (N::HC / 16) * (N::HC / 32) : 1;
-  bf8 w0[N::HD / 16], w1[N::HD / 32], w2[N::HC / 16], w3[K3], w4[N::HC / 32];
-  load_ops<N>(Af + M::foff(0), lane, w0);
-  load_ops<N>(Af + M::foff(1), lane, w1);
+  auto wf = [&](int j, int k) { return lds_bf8<N>(Af + M::foff(j), k, lane); };
   {
     f4 h[T][N::HD / 16];
 #pragma unroll
     for (int m = 0; m < N::HD / 16; ++m)
 #pragma unroll
-      for (int t = 0; t < T; ++t) h[t][m] = mfma32(w0[m], a[t].e, zero);
+      for (int t = 0; t < T; ++t) h[t][m] = mfma32(wf(0, m), a[t].e, zero);
 #pragma unroll
     for (int t = 0; t < T; ++t)
 #pragma unroll
       for (int s = 0; s < N::HD / 32; ++s) a[t].h1[s] = relu8(pack8(h[t][2 * s], h[t][2 * s + 1]));
   }
-  load_ops<N>(Af + M::foff(2), lane, w2);
   {
     f4 acc[T];
 #pragma unroll
@@ -281,28 +254,25 @@ __device__ __forceinline__ void fwd_tiles(const __bf16* __restrict__ Af, int lan
 #pragma unroll
     for (int s = 0; s < N::HD / 32; ++s)
 #pragma unroll
-      for (int t = 0; t < T; ++t) acc[t] = mfma32(w1[s], a[t].h1[s], acc[t]);
+      for (int t = 0; t < T; ++t) acc[t] = mfma32(wf(1, s), a[t].h1[s], acc[t]);
 #pragma unroll
     for (int t = 0; t < T; ++t) {
       a[t].o = acc[t];
       a[t].osh = pack8(acc[t], sh[t]);
     }
   }
-  if constexpr (N::NCH == 2) load_ops<N>(Af + M::foff(3), lane, w3);
-  else load_ops<N>(Af + M::foff(N::NW - 1), lane, w4);
   {
     f4 h[T][N::HC / 16];
 #pragma unroll
     for (int m = 0; m < N::HC / 16; ++m)
 #pragma unroll
-      for (int t = 0; t < T; ++t) h[t][m] = mfma32(w2[m], a[t].osh, zero);
+      for (int t = 0; t < T; ++t) h[t][m] = mfma32(wf(2, m), a[t].osh, zero);
 #pragma unroll
     for (int t = 0; t < T; ++t)
 #pragma unroll
       for (int s = 0; s < N::HC / 32; ++s) a[t].h3[s] = relu8(pack8(h[t][2 * s], h[t][2 * s + 1]));
   }
   if constexpr (N::NCH == 2) {
-    load_ops<N>(Af + M::foff(N::NW - 1), lane, w4);
     f4 acc[T][N::HC / 16];
 #pragma unroll
     for (int t = 0; t < T; ++t)
@@ -313,7 +283,7 @@ __device__ __forceinline__ void fwd_tiles(const __bf16* __restrict__ Af, int lan
 #pragma unroll
       for (int m = 0; m < N::HC / 16; ++m)
 #pragma unroll
-        for (int t = 0; t < T; ++t) acc[t][m] = mfma32(w3[m * (N::HC / 32) + s], a[t].h3[s], acc[t][m]);
+        for (int t = 0; t < T; ++t) acc[t][m] = mfma32(wf(3, m * (N::HC / 32) + s), a[t].h3[s], acc[t][m]);
 #pragma unroll
     for (int t = 0; t < T; ++t)
 #pragma unroll
@@ -326,7 +296,7 @@ __device__ __forceinline__ void fwd_tiles(const __bf16* __restrict__ Af, int lan
 #pragma unroll
     for (int s = 0; s < N::HC / 32; ++s)
 #pragma unroll
-      for (int t = 0; t < T; ++t) acc[t] = mfma32(w4[s], N::NCH == 2 ? a[t].h4[s] : a[t].h3[s], acc[t]);
+      for (int t = 0; t < T; ++t) acc[t] = mfma32(wf(N::NW - 1, s), N::NCH == 2 ? a[t].h4[s] : a[t].h3[s], acc[t]);
 #pragma unroll
     for (int t = 0; t < T; ++t) a[t].z = acc[t];
   }
@@ -346,212 +316,157 @@ __device__ __forceinline__ void tile_operands(const TileIn<N>& in, int g, PActs<
 }
 
 // ---------------------------------------------------------------------------
-// Backward, eight waves a workgroup (two per SIMD).  Each wave runs the
-// forward recompute and the input-gradient chain of one 16-sample tile; the
-// 128 samples of the workgroup's step are staged into a shared
-// [feature][sample] buffer, two or one layers at a time (three groups a tile;
-// two buffers, used alternately, so one barrier a group suffices), and each
-// wave adds the products of its share of the group's weight-gradient tiles
-// over the 128 samples.  A wave then holds
-// a few weight-gradient tiles instead of all of them, which leaves room for
-// two waves on a SIMD.
+// Backward.  A workgroup of kBwdWaves waves takes steps of 16 samples a wave.
+// Each wave runs the forward recompute and the input-gradient chain of its 16
+// samples; the step's samples are staged into LDS two or one layers at a time
+// (three groups a step), and each wave adds the products of its share of the group's
+// weight-gradient tiles over all of them, so that it holds a few tiles
+// instead of all.
+//
+// A sample's staged values lie next to each other, in the order in which the
+// lanes hold them (one 16-byte store of a lane for 32 features), and the
+// products' operands, which run along the samples, come from LDS reads that
+// transpose 4 x 16 values a 16-lane row.
 // ---------------------------------------------------------------------------
-constexpr int kBwdWaves8 = 8;
-constexpr int kStepSamples = 16 * kBwdWaves8;  // samples of a workgroup step
-constexpr int kSRow = kStepSamples + 8;        // bf16 per staged row (the pad staggers rows over the banks)
-
-// The weight-gradient tiles of layer J (16x16, numbered m * NJ + n) go
-// round-robin over the waves, continuing from the tiles of the layers that
-// come before J in backward order, so that every wave owns about as many.
-template <class N, int J>
-struct OwnAcc {
-  static constexpr int MI = (N::kin(J) + 15) / 16, NJ = (N::kout(J) + 15) / 16, TILES = MI * NJ;
-  static constexpr int before() {
-    int o = 0;
-    for (int i = N::NW - 1; i > J; --i) o += ((N::kin(i) + 15) / 16) * ((N::kout(i) + 15) / 16);
-    return o;
-  }
-  static constexpr int SLOTS = (TILES + kBwdWaves8 - 1) / kBwdWaves8;
-  f4 v[SLOTS];
-  __device__ __forceinline__ void zero() {
-#pragma unroll
-    for (int k = 0; k < SLOTS; ++k) v[k] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-  }
-  // tile of slot k of wave w, or -1
-  static __device__ __forceinline__ int tile(int w, int k) {
-    const int t = (w - before() % kBwdWaves8 + kBwdWaves8) % kBwdWaves8 + k * kBwdWaves8;
-    return t < TILES ? t : -1;
-  }
-  // v += X^T dY over the staged samples, for the tiles wave w owns
-  __device__ __forceinline__ void add(const __bf16* Xs, const __bf16* Ys, int w, int lane) {
-    const int gk = lane >> 4, i = lane & 15;
-#pragma unroll
-    for (int k = 0; k < SLOTS; ++k) {
-      const int t = tile(w, k);
-      if (t < 0) continue;
-      const int m = t / NJ, n = t % NJ;
-      const __bf16* xr = Xs + (16 * m + i) * kSRow + 8 * gk;
-      const __bf16* yr = Ys + (16 * n + i) * kSRow + 8 * gk;
-#pragma unroll
-      for (int c = 0; c < kStepSamples / 32; ++c)
-        v[k] = mfma32(*reinterpret_cast<const bf8*>(xr + 32 * c), *reinterpret_cast<const bf8*>(yr + 32 * c), v[k]);
-    }
-  }
-  static constexpr int SPLIT = 1;
-  // dW (LDS, row-major kin x kout, zeroed) += the owned tiles (disjoint over
-  // the waves, so all waves write at once, in phase 0)
-  __device__ __forceinline__ void flush(float* dW, int w, int lane, int phase) const {
-    if (phase != 0) return;
-    const int gk = lane >> 4, i = lane & 15;
-#pragma unroll
-    for (int k = 0; k < SLOTS; ++k) {
-      const int t = tile(w, k);
-      if (t < 0) continue;
-      const int m = t / NJ, n = t % NJ, col = 16 * n + i;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = 16 * m + 4 * gk + r;
-        if (row < N::kin(J) && col < N::kout(J)) dW[row * N::kout(J) + col] += v[k][r];
-      }
-    }
-  }
-};
-
-// The weight-gradient products of a layer whose input and output widths are
-// multiples of 32, on 32x32x16 tiles: each tile goes to kBwdWaves8 / TILES
-// waves, each of which adds the products over its own share of the staged
-// samples (the operand reads per product are half those of 16x16 tiles).
-template <class N, int J>
-struct OwnAcc32 {
-  static constexpr int MI = N::kin(J) / 32, NJ = N::kout(J) / 32, TILES = MI * NJ;
-  static constexpr int SPLIT = kBwdWaves8 / TILES, KSTEPS = kStepSamples / SPLIT / 16;
-  f16v v;
-  __device__ __forceinline__ void zero() {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) v[r] = 0.0f;
-  }
-  __device__ __forceinline__ void add(const __bf16* Xs, const __bf16* Ys, int w, int lane) {
-    const int t = w % TILES, sp = w / TILES, m = t / NJ, n = t % NJ;
-    const int i = lane & 31, c0 = sp * (kStepSamples / SPLIT) + 8 * (lane >> 5);
-    const __bf16* xr = Xs + (32 * m + i) * kSRow + c0;
-    const __bf16* yr = Ys + (32 * n + i) * kSRow + c0;
-#pragma unroll
-    for (int c = 0; c < KSTEPS; ++c)
-      v = mfma32x32(*reinterpret_cast<const bf8*>(xr + 16 * c), *reinterpret_cast<const bf8*>(yr + 16 * c), v);
-  }
-  // dW += this wave's partial tile; the waves sharing a tile write in
-  // different phases
-  __device__ __forceinline__ void flush(float* dW, int w, int lane, int phase) const {
-    const int t = w % TILES, sp = w / TILES, m = t / NJ, n = t % NJ;
-    if (sp != phase) return;
-    const int col = 32 * n + (lane & 31);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = 32 * m + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-      dW[row * N::kout(J) + col] += v[r];
-    }
-  }
-};
-
-template <class N, int J>
-constexpr bool kWideTiles = N::kin(J) % 32 == 0 && N::kout(J) % 32 == 0 &&
-                            kBwdWaves8 % ((N::kin(J) / 32) * (N::kout(J) / 32)) == 0;
-template <class N, int J>
-using LayerAcc = typename std::conditional<kWideTiles<N, J>, OwnAcc32<N, J>, OwnAcc<N, J>>::type;
-
+constexpr int kBwdWaves = 16;
+// Networks whose backward may gather the encoding itself: the four-level
+// ones.  The larger ones are always given it.
 template <class N>
-struct OwnAll {
-  LayerAcc<N, 0> w0;
-  LayerAcc<N, 1> w1;
-  LayerAcc<N, 2> w2;
-  LayerAcc<N, N::NCH == 2 ? 3 : 2> w3;  // second colour hidden layer (unused with one)
-  LayerAcc<N, N::NW - 1> wl;
-  static constexpr int cmax(int a, int b) { return a > b ? a : b; }
-  static constexpr int PHASES =
-      cmax(cmax(LayerAcc<N, 0>::SPLIT, LayerAcc<N, 1>::SPLIT),
-           cmax(cmax(LayerAcc<N, 2>::SPLIT, LayerAcc<N, N::NCH == 2 ? 3 : 2>::SPLIT), LayerAcc<N, N::NW - 1>::SPLIT));
-};
-
-// One tile's staged values: rows 16m + 4g + r of column c (lane group g).
-template <int MB>
-__device__ __forceinline__ void stage1_packed(uint16_t* S, const bf8* a, int g, int c) {
-#pragma unroll
-  for (int m = 0; m < MB; ++m)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) S[(16 * m + 4 * g + r) * kSRow + c] = (uint16_t)bf_bits(a[m >> 1], 4 * (m & 1) + r);
-}
-
-// dL/de of one tile held back one step, stored after the next tile's
-// forward; as BF16 pairs (the table-gradient records it feeds are BF16 too).
-template <class N>
-struct PendingDe1 {
-  f4 de[N::bmt(0)];
-  int s;
-  bool valid;
-  __device__ __forceinline__ void store(const RecordBuffers& rec, int g) const {
-    if (!valid) return;
-#pragma unroll
-    for (int q = 0; q < N::LPL; ++q) {
-      const int k0 = 2 * q, k1 = 2 * q + 1;
-      reinterpret_cast<uint32_t*>(rec.de)[(size_t)(g + 4 * q) * rec.stride + s] =
-          bf16_pair(de[k0 >> 2][k0 & 3], de[k1 >> 2][k1 & 3]);
-    }
-  }
-};
+constexpr bool kGathers = N::LPL == 1;
+constexpr int kStepSamples = 16 * kBwdWaves;  // samples of a workgroup step
 
 // Staging groups: the layers whose weight-gradient products follow one
 // barrier together (the colour layers; the geometry-feature layer and the
 // second density layer; the first density layer).  Within a group each layer
-// has its X rows (16 per input tile) and then its dY rows (16 per output
-// tile), layers in backward order; a buffer holds the largest group.
+// has its X columns (32 per k-step of its forward product) and then its dY
+// columns (16 where the layer has at most 16 outputs), layers in backward order.
 template <class N>
-struct StageRows {
-  static constexpr int xr(int j) { return (N::kin(j) + 15) / 16 * 16; }
-  static constexpr int yr(int j) { return (N::kout(j) + 15) / 16 * 16; }
+struct StageCols {
+  static constexpr int xc(int j) { return 32 * Mixed<N>::fks(j); }
+  static constexpr int yc(int j) { return j == 1 || j == N::NW - 1 ? 16 : N::kout(j); }
   static constexpr int group(int j) { return j >= 3 || j == N::NW - 1 ? 0 : j >= 1 ? 1 : 2; }
   static constexpr int x(int j) {
     int o = 0;
     for (int i = N::NW - 1; i > j; --i)
-      if (group(i) == group(j)) o += xr(i) + yr(i);
+      if (group(i) == group(j)) o += xc(i) + yc(i);
     return o;
   }
-  static constexpr int y(int j) { return x(j) + xr(j); }
-  static constexpr int rows(int gr) {
+  static constexpr int y(int j) { return x(j) + xc(j); }
+  static constexpr int cols(int gr) {
     int o = 0;
     for (int i = 0; i < N::NW; ++i)
-      if (group(i) == gr) o += xr(i) + yr(i);
+      if (group(i) == gr) o += xc(i) + yc(i);
     return o;
   }
-  static constexpr int ROWS = N::cmax(rows(0), N::cmax(rows(1), rows(2)));
+  // BF16 values of a staged sample: an odd number of 32-byte pieces, so that
+  // eight samples' pieces lie in different LDS banks
+  static constexpr int COLS = N::cmax(cols(0), N::cmax(cols(1), cols(2)));
+  static constexpr int ROW = COLS / 16 % 2 ? COLS : COLS + 16;
 };
 
-// Row r of staging buffer b.
-template <class N>
-__device__ __forceinline__ __bf16* srow(__bf16* stage, int b, int r) {
-  return stage + (b * StageRows<N>::ROWS + r) * kSRow;
-}
-template <class N>
-__device__ __forceinline__ uint16_t* srow16(__bf16* stage, int b, int r) {
-  return reinterpret_cast<uint16_t*>(srow<N>(stage, b, r));
+// Four rows (from p, this lane's 8-byte quarter of one) of 16 columns,
+// transposed: lane i of a 16-lane row gets the four values of column i.
+__device__ __forceinline__ s4 read_transposed(const __bf16* p) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+      (__attribute__((address_space(3))) s4*)(reinterpret_cast<const s4*>(p)));
 }
 
-// Forward recompute, backward chain and dL/de of this wave's tile (samples
-// s = 128 p + 16 w + jc), with the workgroup's weight-gradient products of
-// each staging group in between; the previous tile's dL/de (pend) is stored after the
-// forward and replaced by this tile's.
+// Weight gradient of layer J in 16x16 tiles: the workgroup's waves own one
+// each, or with fewer tiles than waves share one, each taking its part of a
+// step's samples.  Tile (m, n), lane (gk, i): rows 16m + 4gk + r of the staged X
+// columns, column 16n + i of the dY ones.
+template <class N, int J>
+struct OwnedDW16 {
+  using SC = StageCols<N>;
+  static constexpr int W = kBwdWaves, NJ = SC::yc(J) / 16, TILES = SC::xc(J) / 16 * NJ;
+  static_assert(W % TILES == 0, "whole waves a tile");
+  static constexpr int SPLIT = W / TILES, CHUNKS = kStepSamples / 32 / SPLIT;  // 32 samples a product
+  static_assert(CHUNKS >= 1, "a product a wave");
+  f4 v;
+  __device__ __forceinline__ void zero() { v = f4{0.0f, 0.0f, 0.0f, 0.0f}; }
+  __device__ __forceinline__ void chunk(const __bf16* x, const __bf16* y, int c) {
+    constexpr int R = SC::ROW;
+    auto rd = [&](const __bf16* p) {
+      const s4 lo = read_transposed(p + 32 * c * R), hi = read_transposed(p + (32 * c + 16) * R);
+      return __builtin_bit_cast(bf8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    v = mfma32(rd(x), rd(y), v);
+  }
+  // v += X^T dY over the step's first nc pieces of 32 samples
+  __device__ __forceinline__ void add(const __bf16* stage, int w, int lane, int nc) {
+    const int t = w % TILES, c0 = w / TILES * CHUNKS;
+    const __bf16* row = stage + (lane >> 2) * SC::ROW + 4 * (lane & 3);
+    const __bf16 *x = row + SC::x(J) + 16 * (t / NJ), *y = row + SC::y(J) + 16 * (t % NJ);
+    if (nc == kStepSamples / 32) {
+#pragma unroll
+      for (int c = 0; c < CHUNKS; ++c) chunk(x, y, c0 + c);
+    } else {
+#pragma unroll 1
+      for (int c = c0; c < min(nc, c0 + CHUNKS); ++c) chunk(x, y, c);
+    }
+  }
+  // The workgroup's sums to out (row-major kin x kout); waves that share a
+  // tile meet in LDS.
+  __device__ __forceinline__ void store(float* lds, float* __restrict__ out, int w, int lane) const {
+    f4 sum = v;
+    if constexpr (SPLIT > 1) {
+      __syncthreads();
+      *reinterpret_cast<f4*>(lds + (w * kWave + lane) * 4) = v;
+      __syncthreads();
+      if (w >= TILES) return;
+#pragma unroll
+      for (int p = 1; p < SPLIT; ++p) sum += *reinterpret_cast<const f4*>(lds + ((w + p * TILES) * kWave + lane) * 4);
+    }
+    const int t = w % TILES, cy = 16 * (t % NJ) + (lane & 15);
+    const int col = NJ == 1 ? cy : mixed_fwd_feature<N>(1, cy >> 5, (cy >> 3) & 3, cy & 7);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int cx = 16 * (t / NJ) + 4 * (lane >> 4) + r;
+      const int row = mixed_fwd_feature<N>(J, cx >> 5, (cx >> 3) & 3, cx & 7);
+      if (row >= 0 && row < N::kin(J) && col < N::kout(J)) out[row * N::kout(J) + col] = sum[r];
+    }
+  }
+};
+
 template <class N>
-__device__ __forceinline__ void bwd_tile8(const __bf16* __restrict__ Af, const __bf16* __restrict__ Ab,
-                                          __bf16* stage, int& buf, const TileIn<N>& in, int s, bool valid,
-                                          const RecordBuffers& rec, OwnAll<N>& dw, PendingDe1<N>& pend, int w,
-                                          int lane) {
+struct OwnAll {
+  OwnedDW16<N, 0> w0;
+  OwnedDW16<N, 1> w1;
+  OwnedDW16<N, 2> w2;
+  OwnedDW16<N, N::NCH == 2 ? 3 : 2> w3;  // second colour hidden layer (unused with one)
+  OwnedDW16<N, N::NW - 1> wl;
+};
+
+// This lane's values of columns c on of its sample (S: the sample's row plus
+// the lane group's place): 32 columns a bf8, or 16 (its first half).
+template <int K>
+__device__ __forceinline__ void stage32(__bf16* S, const bf8 (&a)[K], int g) {
+#pragma unroll
+  for (int k = 0; k < K; ++k) *reinterpret_cast<bf8*>(S + 32 * k + 8 * g) = a[k];
+}
+__device__ __forceinline__ void stage16(__bf16* S, const bf8& a, int g) {
+  const s8 v = __builtin_bit_cast(s8, a);
+  *reinterpret_cast<s4*>(S + 4 * g) = __builtin_shufflevector(v, v, 0, 1, 2, 3);
+}
+
+// Forward recompute, backward chain and dL/de of this wave's tile, with the
+// workgroup's weight-gradient products of each staging group in between.
+// fetch (of the next step's inputs into in) is called where the colour layers'
+// activations are no longer held.
+template <class N, class Fetch>
+__device__ __forceinline__ void bwd_tile(const __bf16* __restrict__ Af, const __bf16* __restrict__ Ab, __bf16* stage,
+                                         const TileIn<N>& in, int s, bool valid, int nc, const RecordBuffers& rec,
+                                         OwnAll<N>& dw, int w, int lane, const Fetch& fetch) {
   using M = Mixed<N>;
+  using SC = StageCols<N>;
   constexpr f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-  const int g = lane >> 4, jc = lane & 15, c = 16 * w + jc;
+  constexpr int H = N::HC / 32, D = N::HD / 32;
+  const int g = lane >> 4;
+  __bf16* mine = stage + (16 * w + (lane & 15)) * SC::ROW;  // this lane's sample
   PActs<N> a[1];
   f4 sh[1];
   tile_operands<N>(in, g, a[0], sh[0]);
   fwd_tiles<N, 1>(Af, lane, sh, a);
-  pend.store(rec, g);
 
   f4 dz = zero;
   if (g == 0) {
@@ -561,119 +476,113 @@ __device__ __forceinline__ void bwd_tile8(const __bf16* __restrict__ Af, const _
       dz[r] = in.dr[r] * cc * (1.0f - cc);
     }
   }
-  constexpr int K3 = N::NCH == 2 ? (N::HC / 16) * (N::HC / 32) : 1;
-  constexpr int MT0 = N::bmt(0);
-  bf8 w4[N::HC / 16], w3[K3], w2[N::HC / 32], w1[N::HD / 16], w0[MT0 * (N::HD / 32)];
-  using SR = StageRows<N>;
-  load_ops<N>(Ab + M::boff(N::NW - 1), lane, w4);
-  const bf8* hl = N::NCH == 2 ? a[0].h4 : a[0].h3;
-  // colour layers: the last one, then (with two) the second hidden one
+  // W (m, k) of a layer's input-gradient product
+  auto w_of = [&](int j, int m, int k) { return lds_bf8<N>(Ab + M::boff(j), m * M::bks(j) + k, lane); };
   // the hidden-layer gradients are used only as BF16 (MFMA operands and
   // staged values), so they are rounded once and masked on their bits
-  bf8 dhl[N::HC / 32];
+  const bf8(&hl)[H] = N::NCH == 2 ? a[0].h4 : a[0].h3;
+  bf8 dhl[H];
   const bf8 dzp = pack8(dz, zero);
   {
-    f4 raw[N::HC / 16];
+    f4 raw[2 * H];
 #pragma unroll
-    for (int m = 0; m < N::HC / 16; ++m) raw[m] = mfma32(w4[m], dzp, zero);
+    for (int m = 0; m < 2 * H; ++m) raw[m] = mfma32(w_of(N::NW - 1, m, 0), dzp, zero);
 #pragma unroll
-    for (int k = 0; k < N::HC / 32; ++k) dhl[k] = relu_mask8(pack8(raw[2 * k], raw[2 * k + 1]), hl[k]);
+    for (int k = 0; k < H; ++k) dhl[k] = relu_mask8(pack8(raw[2 * k], raw[2 * k + 1]), hl[k]);
   }
-  if constexpr (N::NCH == 2) load_ops<N>(Ab + M::boff(3), lane, w3);
-  else load_ops<N>(Ab + M::boff(2), lane, w2);
-  stage1_packed<N::HC / 16>(srow16<N>(stage, buf, SR::x(N::NW - 1)), hl, g, c);
-  stage1_packed<1>(srow16<N>(stage, buf, SR::y(N::NW - 1)), &dzp, g, c);
-  bf8 dh3[N::HC / 32];
+  // colour layers: the last one, then (with two) the second hidden one
+  __syncthreads();  // the step before has been added
+  stage32(mine + SC::x(N::NW - 1), hl, g);
+  stage16(mine + SC::y(N::NW - 1), dzp, g);
   if constexpr (N::NCH == 2) {
-    f4 acc[N::HC / 16];
-#pragma unroll
-    for (int m = 0; m < N::HC / 16; ++m) acc[m] = zero;
-#pragma unroll
-    for (int k = 0; k < N::HC / 32; ++k)
-#pragma unroll
-      for (int m = 0; m < N::HC / 16; ++m) acc[m] = mfma32(w3[m * (N::HC / 32) + k], dhl[k], acc[m]);
-#pragma unroll
-    for (int k = 0; k < N::HC / 32; ++k) dh3[k] = relu_mask8(pack8(acc[2 * k], acc[2 * k + 1]), a[0].h3[k]);
-    load_ops<N>(Ab + M::boff(2), lane, w2);
-    stage1_packed<N::HC / 16>(srow16<N>(stage, buf, SR::x(3)), a[0].h3, g, c);
-    stage1_packed<N::HC / 16>(srow16<N>(stage, buf, SR::y(3)), dhl, g, c);
-  } else {
-#pragma unroll
-    for (int k = 0; k < N::HC / 32; ++k) dh3[k] = dhl[k];
+    stage32(mine + SC::x(3), a[0].h3, g);
+    stage32(mine + SC::y(3), dhl, g);
   }
   __syncthreads();
-  dw.wl.add(srow<N>(stage, buf, SR::x(N::NW - 1)), srow<N>(stage, buf, SR::y(N::NW - 1)), w, lane);
-  if constexpr (N::NCH == 2) dw.w3.add(srow<N>(stage, buf, SR::x(3)), srow<N>(stage, buf, SR::y(3)), w, lane);
-  buf ^= 1;
+  dw.wl.add(stage, w, lane, nc);
+  if constexpr (N::NCH == 2) dw.w3.add(stage, w, lane, nc);
+  bf8 dh3[H];
+  if constexpr (N::NCH == 2) {
+    f4 acc[2 * H];
+#pragma unroll
+    for (int m = 0; m < 2 * H; ++m) acc[m] = zero;
+#pragma unroll
+    for (int k = 0; k < H; ++k)
+#pragma unroll
+      for (int m = 0; m < 2 * H; ++m) acc[m] = mfma32(w_of(3, m, k), dhl[k], acc[m]);
+#pragma unroll
+    for (int k = 0; k < H; ++k) dh3[k] = relu_mask8(pack8(acc[2 * k], acc[2 * k + 1]), a[0].h3[k]);
+  } else {
+#pragma unroll
+    for (int k = 0; k < H; ++k) dh3[k] = dhl[k];
+  }
   // first colour layer (gradient of the geometry features), second density layer
   f4 dgeo = zero;
 #pragma unroll
-  for (int k = 0; k < N::HC / 32; ++k) dgeo = mfma32(w2[k], dh3[k], dgeo);
-  load_ops<N>(Ab + M::boff(1), lane, w1);
-  stage1_packed<2>(srow16<N>(stage, buf, SR::x(2)), &a[0].osh, g, c);
-  stage1_packed<N::HC / 16>(srow16<N>(stage, buf, SR::y(2)), dh3, g, c);
+  for (int k = 0; k < H; ++k) dgeo = mfma32(w_of(2, 0, k), dh3[k], dgeo);
   if (g == 0) dgeo[0] += __expf(a[0].o[0]) * in.ds;  // rounded to BF16 next
-  bf8 dh1[N::HD / 32];
+  bf8 dh1[D];
   const bf8 dgp = pack8(dgeo, zero);
   {
-    f4 raw[N::HD / 16];
+    f4 raw[2 * D];
 #pragma unroll
-    for (int m = 0; m < N::HD / 16; ++m) raw[m] = mfma32(w1[m], dgp, zero);
+    for (int m = 0; m < 2 * D; ++m) raw[m] = mfma32(w_of(1, m, 0), dgp, zero);
 #pragma unroll
-    for (int k = 0; k < N::HD / 32; ++k) dh1[k] = relu_mask8(pack8(raw[2 * k], raw[2 * k + 1]), a[0].h1[k]);
+    for (int k = 0; k < D; ++k) dh1[k] = relu_mask8(pack8(raw[2 * k], raw[2 * k + 1]), a[0].h1[k]);
   }
-  load_ops<N>(Ab + M::boff(0), lane, w0);
-  stage1_packed<N::HD / 16>(srow16<N>(stage, buf, SR::x(1)), a[0].h1, g, c);
-  stage1_packed<1>(srow16<N>(stage, buf, SR::y(1)), &dgp, g, c);
   __syncthreads();
-  dw.w2.add(srow<N>(stage, buf, SR::x(2)), srow<N>(stage, buf, SR::y(2)), w, lane);
-  dw.w1.add(srow<N>(stage, buf, SR::x(1)), srow<N>(stage, buf, SR::y(1)), w, lane);
-  buf ^= 1;
-  // first density layer: dL/de
+  *reinterpret_cast<bf8*>(mine + SC::x(2) + 8 * g) = a[0].osh;
+  stage32(mine + SC::y(2), dh3, g);
+  stage32(mine + SC::x(1), a[0].h1, g);
+  stage16(mine + SC::y(1), dgp, g);
+  fetch();
+  __syncthreads();
+  dw.w2.add(stage, w, lane, nc);
+  dw.w1.add(stage, w, lane, nc);
+  // first density layer: dL/de, as BF16 pairs (the table-gradient records it
+  // feeds are BF16 too)
+  constexpr int MT0 = N::bmt(0);
   f4 de[MT0];
 #pragma unroll
   for (int m = 0; m < MT0; ++m) de[m] = zero;
 #pragma unroll
-  for (int k = 0; k < N::HD / 32; ++k)
+  for (int k = 0; k < D; ++k)
 #pragma unroll
-    for (int m = 0; m < MT0; ++m) de[m] = mfma32(w0[m * (N::HD / 32) + k], dh1[k], de[m]);
-  {
-    uint16_t* X = srow16<N>(stage, buf, SR::x(0));
+    for (int m = 0; m < MT0; ++m) de[m] = mfma32(w_of(0, m, k), dh1[k], de[m]);
+  if (valid) {
 #pragma unroll
-    for (int k = 0; k < N::NSLOT; ++k) X[fwd_in_feature<N>(0, k, g) * kSRow + c] = (uint16_t)bf_bits(a[0].e, k);
-    if constexpr (N::ENC < 16) {
-#pragma unroll
-      for (int k = 0; k < 2; ++k) X[(N::ENC + 2 * g + k) * kSRow + c] = 0;
+    for (int q = 0; q < N::LPL; ++q) {
+      const int k0 = 2 * q, k1 = 2 * q + 1;
+      reinterpret_cast<uint32_t*>(rec.de)[(size_t)(g + 4 * q) * rec.stride + s] =
+          bf16_pair(de[k0 >> 2][k0 & 3], de[k1 >> 2][k1 & 3]);
     }
   }
-  stage1_packed<N::HD / 16>(srow16<N>(stage, buf, SR::y(0)), dh1, g, c);
   __syncthreads();
-  dw.w0.add(srow<N>(stage, buf, SR::x(0)), srow<N>(stage, buf, SR::y(0)), w, lane);
-  buf ^= 1;
-  pend.s = s;
-  pend.valid = valid;
-#pragma unroll
-  for (int m = 0; m < MT0; ++m) pend.de[m] = de[m];
+  *reinterpret_cast<bf8*>(mine + SC::x(0) + 8 * g) = a[0].e;
+  stage32(mine + SC::y(0), dh1, g);
+  __syncthreads();
+  dw.w0.add(stage, w, lane, nc);
 }
 
-// kBwdWaves8 waves per workgroup, two per SIMD; the workgroup takes steps
-// (128 samples) blockIdx.x, blockIdx.x + gridDim.x, ...  With the kept
-// encoding, a wave fetches its next tile's inputs while it computes the
-// current one (ray indices two steps ahead).
+// Sixteen waves, four a SIMD.  The matrix instructions are a fifth of the
+// time; a wave waits at each step of its serial chain (operands from LDS, product, rounding,
+// barriers), so what counts is how many waves share a SIMD and how few LDS accesses
+// a tile takes.  At 262k samples of the 64-wide network 46.8 us with eight
+// waves of up to 256 registers, two-byte stores to [feature][sample] rows and
+// the weights read a layer ahead, 38.6 so; at 100003 samples 26.4 and 21.6; the
+// 32-wide network at 1M samples 75.7 and 54.7.  (Eight waves with two
+// tiles each and 32x32 products, which halve the LDS reads: 48.1, 26.8, 75.0.)
 template <class N>
-__global__ __launch_bounds__(kBwdWaves8 * kWave, 1) void mixed_bwd8_kernel(
+__global__ __launch_bounds__(kBwdWaves * kWave) void mixed_bwd8_kernel(
     LevelInfo lv, const _Float16* __restrict__ table, const __bf16* __restrict__ prep, SampleSrc src,
     const float* __restrict__ dsigma, const float* __restrict__ drgb, RecordBuffers rec,
     float* __restrict__ dw_partial) {
   using M = Mixed<N>;
-  constexpr int SBUF = StageRows<N>::ROWS * kSRow;
-  static_assert(2 * SBUF * (int)sizeof(__bf16) >= N::NWEIGHTS * (int)sizeof(float),
-                "the weight-gradient sums reuse the staging buffers");
-  __shared__ __attribute__((aligned(16))) __bf16 Af[M::FWD];
-  __shared__ __attribute__((aligned(16))) __bf16 Ab[M::BWD];
-  __shared__ __attribute__((aligned(16))) __bf16 stage[2 * SBUF];
-  copy_to_lds<kBwdWaves8 * kWave, sizeof(Af)>(Af, prep);
-  copy_to_lds<kBwdWaves8 * kWave, sizeof(Ab)>(Ab, prep + M::FWD);
+  __shared__ __attribute__((aligned(16))) __bf16 ops[M::FWD + M::BWD];
+  __shared__ __attribute__((aligned(16))) __bf16 stage[kStepSamples * StageCols<N>::ROW];
+  static_assert(sizeof(stage) >= kBwdWaves * kWave * sizeof(f4), "the sums' last step reuses it");
+  const __bf16 *Af = ops, *Ab = ops + M::FWD;
+  copy_to_lds<kBwdWaves * kWave, sizeof(ops)>(ops, prep);
   __syncthreads();
 
   const int S = src.n_dev ? (int)*src.n_dev : src.n;
@@ -683,52 +592,37 @@ __global__ __launch_bounds__(kBwdWaves8 * kWave, 1) void mixed_bwd8_kernel(
   if constexpr (N::NCH == 2) dw.w3.zero();
   LaneLevels<N> ll;
   lane_levels<N>(lv, g, ll);
-  PendingDe1<N> pend;
-  pend.valid = false;
-  pend.s = 0;
-  int buf = 0;
   const int nsteps = (S + kStepSamples - 1) / kStepSamples, step = gridDim.x;
   const int off = 16 * w + jc;
-  if (src.ecache) {
-    const int p0 = blockIdx.x;
-    TileIn<N> cur;
-    const int s0 = kStepSamples * p0 + off;
-    fetch_tile<N, true>(src, table, lv, ll, dsigma, drgb, s0, s0 < S, g, ray_of<N>(src, s0, S), cur);
-    uint32_t rid1 = ray_of<N>(src, kStepSamples * (p0 + step) + off, S);
-    for (int p = p0; p < nsteps; p += step) {
+  // pieces of 32 samples in step p
+  auto pieces = [&](int p) { return min(kStepSamples / 32, (S - kStepSamples * p + 31) / 32); };
+  TileIn<N> in;
+  if (!kGathers<N> || src.ecache) {
+    uint32_t rid = ray_of<N>(src, kStepSamples * (int)blockIdx.x + off, S);
+    auto fetch = [&](int p) {  // the inputs of step p, and the ray index of the one after
       const int s = kStepSamples * p + off;
-      TileIn<N> nxt;
-      const int s1 = s + kStepSamples * step;
-      fetch_tile<N, true>(src, table, lv, ll, dsigma, drgb, s1, s1 < S, g, rid1, nxt);
-      const uint32_t rid2 = ray_of<N>(src, s1 + kStepSamples * step, S);
-      bwd_tile8<N>(Af, Ab, stage, buf, cur, s, s < S, rec, dw, pend, w, lane);
-      cur = nxt;
-      rid1 = rid2;
-    }
-  } else {
+      fetch_tile<N, true>(src, table, lv, ll, dsigma, drgb, s, s < S, g, rid, in);
+      rid = ray_of<N>(src, s + kStepSamples * step, S);
+    };
+    fetch(blockIdx.x);
     for (int p = blockIdx.x; p < nsteps; p += step) {
       const int s = kStepSamples * p + off;
-      TileIn<N> cur;
-      fetch_tile<N, false>(src, table, lv, ll, dsigma, drgb, s, s < S, g, 0u, cur);
-      bwd_tile8<N>(Af, Ab, stage, buf, cur, s, s < S, rec, dw, pend, w, lane);
+      bwd_tile<N>(Af, Ab, stage, in, s, s < S, pieces(p), rec, dw, w, lane, [&] { fetch(p + step); });
+    }
+  } else if constexpr (kGathers<N>) {
+    for (int p = blockIdx.x; p < nsteps; p += step) {
+      const int s = kStepSamples * p + off;
+      fetch_tile<N, false>(src, table, lv, ll, dsigma, drgb, s, s < S, g, 0u, in);
+      bwd_tile<N>(Af, Ab, stage, in, s, s < S, pieces(p), rec, dw, w, lane, [] {});
     }
   }
-  pend.store(rec, g);
-  // the workgroup's weight-gradient sums, in the staging space
-  __syncthreads();
-  float* dW = reinterpret_cast<float*>(stage);
-  for (int i = threadIdx.x; i < N::NWEIGHTS; i += blockDim.x) dW[i] = 0.0f;
-  __syncthreads();
-  for (int ph = 0; ph < OwnAll<N>::PHASES; ++ph) {
-    dw.w0.flush(dW + N::woff(0), w, lane, ph);
-    dw.w1.flush(dW + N::woff(1), w, lane, ph);
-    dw.w2.flush(dW + N::woff(2), w, lane, ph);
-    if constexpr (N::NCH == 2) dw.w3.flush(dW + N::woff(3), w, lane, ph);
-    dw.wl.flush(dW + N::woff(N::NW - 1), w, lane, ph);
-    __syncthreads();
-  }
+  float* sums = reinterpret_cast<float*>(stage);
   float* out = dw_partial + (size_t)blockIdx.x * N::NWEIGHTS;
-  for (int i = threadIdx.x; i < N::NWEIGHTS; i += blockDim.x) out[i] = dW[i];
+  dw.w0.store(sums, out + N::woff(0), w, lane);
+  dw.w1.store(sums, out + N::woff(1), w, lane);
+  dw.w2.store(sums, out + N::woff(2), w, lane);
+  if constexpr (N::NCH == 2) dw.w3.store(sums, out + N::woff(3), w, lane);
+  dw.wl.store(sums, out + N::woff(N::NW - 1), w, lane);
 }
 
 // Forward: density and colour of 16-sample tiles, one tile per wave at a
@@ -866,9 +760,10 @@ template <class N>
 static hipError_t bwd_impl(const LevelInfo& lv, const void* shadow, const SampleSrc& src, int nblocks,
                            const float* dsigma, const float* drgb, const RecordBuffers& rec, float* partial,
                            const WOffsets& wo, float* grads, hipStream_t st) {
+  if (!kGathers<N> && !src.ecache) return hipErrorInvalidValue;
   const __bf16* ops = static_cast<const __bf16*>(shadow);
   const _Float16* t16 = reinterpret_cast<const _Float16*>(static_cast<const char*>(shadow) + mixed_ops_bytes<N>());
-  hipLaunchKernelGGL(mixed_bwd8_kernel<N>, dim3(nblocks), dim3(kBwdWaves8 * kWave), 0, st, lv, t16, ops, src,
+  hipLaunchKernelGGL(mixed_bwd8_kernel<N>, dim3(nblocks), dim3(kBwdWaves * kWave), 0, st, lv, t16, ops, src,
                      dsigma, drgb, rec, partial);
   return hipGetLastError();
 }

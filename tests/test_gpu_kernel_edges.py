@@ -79,6 +79,41 @@ def test_mlp_backward_at_step_edges(nsl, gpu, spec, S):
         check_mag(f"step-edge grad W{j}", a, b + 0.5, m + 0.5, 1e-5)
 
 
+@pytest.mark.parametrize("spec", [W.C1_FIELD, W.C2_FIELD], ids=["tiny", "full"])
+@pytest.mark.parametrize("S,k", [(16, 1), (33, 32), (255, 17), (257, 256), (300, 65), (65553, 32769)])
+def test_mixed_backward_at_step_edges(nsl, gpu, spec, S, k):
+    """nsl_field_bwd_mixed around its tiles of 16 samples, products of 32, steps
+    of 256 and rounds of 256 workgroups: the weight gradients of S samples
+    against the oracle at 2e-2 of their magnitudes, and against the sum of
+    those of the first k and of the others, which differs in the order of FP32
+    additions only (1e-5)."""
+    import torch
+    f = nsl.Field(spec)
+    flat, t64, w64 = params_for(spec, f.layout, seed=7, table_range=0.5)
+    rng = np.random.default_rng(S)
+    xn = rng.uniform(size=(S, 3)).astype(np.float32)
+    d = rng.normal(size=(S, 3))
+    d = (d / np.linalg.norm(d, axis=1, keepdims=True)).astype(np.float32)
+    dsig = rng.normal(size=S).astype(np.float32)
+    drgb = rng.normal(size=(S, 3)).astype(np.float32)
+    shadow = f.prepare_mixed(_t(torch, gpu, flat))
+
+    def grads(lo, hi):
+        G = torch.zeros(f.layout["total"], device=gpu)
+        ws = torch.empty(f.workspace_bytes(hi - lo), dtype=torch.uint8, device=gpu)
+        f.bwd_mixed(shadow, *(_t(torch, gpu, a[lo:hi]) for a in (xn, d, dsig, drgb)), G, ws)
+        return split_grads(G.cpu().numpy().astype(np.float64), f.layout, spec)[1]
+
+    e, em, _ = ofield.encode_fwd(spec, t64, xn)
+    cache = ofield.mlp_fwd(spec, w64, e, em, ofield.sh_basis(d.astype(np.float64), spec.sh_bands), band=2e-2)
+    ds64, dc64 = dsig.astype(np.float64), drgb.astype(np.float64)
+    dWs, dWm, _, _ = ofield.mlp_bwd(spec, w64, cache, ds64, np.abs(ds64), dc64, np.abs(dc64), band_tol=2e-2)
+    whole, first, rest = grads(0, S), grads(0, k), grads(k, S)
+    for j, (g, a, b, want, m) in enumerate(zip(whole, first, rest, dWs, dWm)):
+        check_mag(f"mixed step-edge grad W{j}", g, want, m, 2e-2)
+        check_mag(f"mixed step-edge parts W{j}", a + b, g, m, 1e-5)
+
+
 @pytest.mark.parametrize("c,p", [(1, 1), (15, 63), (16, 64), (17, 257), (48, 300), (60, 65), (60, 70001)])
 def test_covariance_at_tile_edges(nsl, gpu, c, p):
     """nsl_depth_covariance around the 16x16 tiles, the 16-pixel groups, the
