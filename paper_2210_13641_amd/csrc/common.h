@@ -141,16 +141,6 @@ __device__ __forceinline__ float wave_incl_scan(float v) {
   return v;
 }
 
-__device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
-  const int l = lane_id();
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const uint32_t n = __shfl_up(v, o, kWave);
-    if (l >= o) v += n;
-  }
-  return v;
-}
-
 // DPP row shift towards lower lanes: lane i of each 16-lane row receives the
 // value of lane i+N of the same row (0 when i+N leaves the row).
 template <int N>
@@ -165,6 +155,20 @@ __device__ __forceinline__ float row_from_above(float v) {
 template <int N>
 __device__ __forceinline__ int row_from_below(int v) {
   return __builtin_amdgcn_update_dpp(0, v, 0x110 + N, 0xF, 0xF, true);
+}
+
+// Inclusive prefix sum over the wave: within each row by DPP shifts, then the
+// totals of the rows before.  Every lane is active.
+__device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
+  v += (uint32_t)row_from_below<1>((int)v);
+  v += (uint32_t)row_from_below<2>((int)v);
+  v += (uint32_t)row_from_below<4>((int)v);
+  v += (uint32_t)row_from_below<8>((int)v);
+  const uint32_t t0 = (uint32_t)__builtin_amdgcn_readlane((int)v, 15);
+  const uint32_t t1 = t0 + (uint32_t)__builtin_amdgcn_readlane((int)v, 31);
+  const uint32_t t2 = t1 + (uint32_t)__builtin_amdgcn_readlane((int)v, 47);
+  const int row = lane_id() >> 4;
+  return v + (row == 0 ? 0u : row == 1 ? t0 : row == 2 ? t1 : t2);
 }
 
 // Whether this lane starts a run of row_cell_runs below (a valid lane whose

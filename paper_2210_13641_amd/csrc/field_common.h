@@ -96,10 +96,12 @@ __device__ __forceinline__ void corners(float x, float y, float z, int n, bool d
   ty[1] = ty[0] + py;
   tz[1] = tz[0] + pz;
   if constexpr (uniform) {
+    if (dense) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const uint32_t cx = k & 1, cy = (k >> 1) & 1, cz = (k >> 2) & 1;
-      c.idx[k] = off + (dense ? (ix + cx) + ty[cy] + tz[cz] : ((ix + cx) ^ ty[cy] ^ tz[cz]) & mask);
+      for (uint32_t k = 0; k < 8; ++k) c.idx[k] = off + (ix + (k & 1)) + ty[(k >> 1) & 1] + tz[k >> 2];
+    } else {
+#pragma unroll
+      for (uint32_t k = 0; k < 8; ++k) c.idx[k] = off + (((ix + (k & 1)) ^ ty[(k >> 1) & 1] ^ tz[k >> 2]) & mask);
     }
   } else {
     const uint32_t dm = dense ? 0xFFFFFFFFu : 0u;
@@ -241,9 +243,11 @@ __host__ __device__ constexpr int encode_grid(int max_samples) {
 __device__ __forceinline__ int xcd_level(int x, int round) { return 8 * round + (round % 2 ? 7 - x : x); }
 __device__ __forceinline__ void level_unit(int levels, int nunits, int& l, int& u, uint32_t wg) {
   if (levels % 8 == 0) {
-    const int x = (int)(wg % 8u), j = (int)(wg / 8u);
-    l = xcd_level(x, j / nunits);
-    u = j % nunits;
+    // (a few subtractions: a division is twenty vector instructions)
+    const int x = (int)(wg % 8u);
+    int round = 0;
+    for (u = (int)(wg / 8u); u >= nunits; u -= nunits) ++round;
+    l = xcd_level(x, round);
   } else {
     l = (int)(wg % (uint32_t)levels);
     u = (int)(wg / (uint32_t)levels);
@@ -258,9 +262,10 @@ __device__ __forceinline__ void level_unit(int levels, int nunits, int& l, int& 
 // samples' inputs that every level reads are fetched into that XCD's L2
 // once for all of its levels (for kernels that gather no table, whose L2
 // need not hold one level's slice at a time).
-__device__ __forceinline__ void level_unit_interleaved(int levels, int nunits, int& l, int& u, uint32_t wg) {
-  if (levels % 8 == 0) {
-    const int m = levels / 8;
+template <int levels>
+__device__ __forceinline__ void level_unit_interleaved(int nunits, int& l, int& u, uint32_t wg) {
+  if constexpr (levels % 8 == 0) {
+    constexpr int m = levels / 8;
     const int x = (int)(wg % 8u), j = (int)(wg / 8u);
     l = xcd_level(x, j % m);
     u = j / m;

@@ -221,6 +221,13 @@ __global__ __launch_bounds__(1024) void bin_start_kernel(RecordBuffers rb, int n
 // and the loss of ws instead (dw_reduce_block, in the stage's memory), beside
 // the placement; the placement starts at workgroup nskip, a multiple of 8 not
 // below nsum, so that its units keep their XCDs.
+//
+// With paired records it is bound by vector instructions, 380 a wave (64
+// samples of a level): 456 with a branch a corner pair for the record's form, a pair
+// code a corner pair also on hashed levels, the bins' prefix sums on all four waves
+// and divisions for the unit, and then 57.5 us instead of 48.9 at 262k samples of
+// 16 levels, 30.0 instead of 26.3 at 100003.  With FP32 records the stores of
+// 228 MB in short runs bound it (89 us at 262k samples either way).
 template <class R, class N>
 __global__ __launch_bounds__(kUnitSamples) void bin_place_kernel(SampleSrc src, LevelInfo lv, BinLevels bl,
                                                                 RecordBuffers rb, float* __restrict__ zero_table,
@@ -250,9 +257,9 @@ __global__ __launch_bounds__(kUnitSamples) void bin_place_kernel(SampleSrc src, 
   const int t = (int)threadIdx.x, wave = t / kWave, lane = lane_id();
   int l, u;
   if (R::kInterleaveLevels)
-    level_unit_interleaved(bl.levels, bl.nunits, l, u, wg);
+    level_unit_interleaved<N::L>(bl.nunits, l, u, wg);
   else
-    level_unit(bl.levels, bl.nunits, l, u, wg);
+    level_unit(N::L, bl.nunits, l, u, wg);
   const int nb = (int)(bl.first[l + 1] - bl.first[l]);
   for (int k = t; k < nb; k += kUnitSamples) cnt[k] = 0u;
   if (zero_table) {
@@ -265,13 +272,21 @@ __global__ __launch_bounds__(kUnitSamples) void bin_place_kernel(SampleSrc src, 
       for (uint32_t e = t; e < ne; e += kUnitSamples) g[e] = make_float2(0.0f, 0.0f);
     }
   }
+  // levels of at most a wave of bins: the first slot of the unit's records in
+  // each, fetched before it is needed
+  const bool few = nb <= kWave;
+  uint32_t first_slot = 0u;
+  if (few && t < nb) {
+    const uint32_t b = bl.first[l] + (uint32_t)t;
+    first_slot = rb.bin_start[b] + rb.off[(size_t)b * bl.nunits + u];
+  }
   int s;
   float xn[3];
   const bool valid = unit_sample(src, u, s, xn);
   const float2 d = valid ? load_de(rb, l, s) : make_float2(0.0f, 0.0f);
   Corner8 c;
-  const uint32_t loff = lv.offset[l];
-  corners(xn[0], xn[1], xn[2], lv.res[l], (lv.dense_bits >> l) & 1u, lv.table_mask, loff, c);
+  const bool dense = (lv.dense_bits >> l) & 1u;
+  corners(xn[0], xn[1], xn[2], lv.res[l], dense, lv.table_mask, 0u, c);  // offsets in the level
   float v[16];
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
@@ -279,68 +294,86 @@ __global__ __launch_bounds__(kUnitSamples) void bin_place_kernel(SampleSrc src, 
     v[2 * k + 1] = c.w[k] * d.y;
   }
   const bool on = row_cell_runs<16>(c.cell, valid, v) && valid;
-  // records k (and k + 1 unless the pair shares record k): the key is
-  // the bin << 16 | pair code << 13 | in-bin offset
-  Rec rec[8];
-  uint32_t rank[8], pc[4];
+  // the pair codes of the corners (k, k + 1); a hashed level's four are the
+  // same, since its entries differ by x ^ (x + 1) whatever y and z
+  uint32_t pc[4] = {0u, 0u, 0u, 0u};
+  if (R::kPaired) {
+    pc[0] = pair_code(c.idx[0], c.idx[1]);
+    if (dense) {
 #pragma unroll
-  for (int k = 0; k < 8; k += 2) {
-    const uint32_t e0 = c.idx[k] - loff, e1 = c.idx[k + 1] - loff;
-    const uint32_t p = R::kPaired ? pair_code(e0, e1) : 0u;
-    pc[k / 2] = p;
-    const uint32_t k0 = ((e0 >> kBinShift) << 16) | (p << 13) | (e0 & (uint32_t)(kBinEntries - 1));
-    const uint32_t k1 = ((e1 >> kBinShift) << 16) | (e1 & (uint32_t)(kBinEntries - 1));
-    if (p != 0u) {
-      rec[k] = R::pack_pair(k0, v[2 * k], v[2 * k + 1], v[2 * k + 2], v[2 * k + 3]);
-      rec[k + 1] = rec[k];
+      for (int j = 1; j < 4; ++j) pc[j] = pair_code(c.idx[2 * j], c.idx[2 * j + 1]);
     } else {
-      rec[k] = R::pack(k0, v[2 * k], v[2 * k + 1]);
-      rec[k + 1] = R::pack(k1, v[2 * k + 2], v[2 * k + 3]);
+      pc[1] = pc[2] = pc[3] = pc[0];
     }
   }
+  // records k, and k + 1 unless the pair shares record k (without a pair code
+  // the second value of record k is not read): the key is the bin << 16 |
+  // pair code << 13 | in-bin offset
+  Rec rec[8];
+  uint32_t rank[8];
+#pragma unroll
+  for (int k = 0; k < 8; k += 2) {
+    const uint32_t e0 = c.idx[k], e1 = c.idx[k + 1];
+    const uint32_t k0 = ((e0 >> kBinShift) << 16) | (pc[k / 2] << 13) | (e0 & (uint32_t)(kBinEntries - 1));
+    const uint32_t k1 = ((e1 >> kBinShift) << 16) | (e1 & (uint32_t)(kBinEntries - 1));
+    rec[k] = R::pack_pair(k0, v[2 * k], v[2 * k + 1], v[2 * k + 2], v[2 * k + 3]);
+    rec[k + 1] = R::pack(k1, v[2 * k + 2], v[2 * k + 3]);
+  }
   __syncthreads();
-  // ranks in the bins: a paired record takes one; two records of the
-  // x-neighbour corners (k, k + 1) nearly always share a bin and then take
-  // two consecutive ranks from one atomic
+  // ranks in the bins: two single records of x-neighbour corners (k, k + 1)
+  // nearly always share a bin and then take two consecutive ranks from one
+  // atomic (among paired records they are rare)
+  auto joint = [](uint32_t ba, uint32_t bb) { return !R::kPaired && ba == bb; };
   if (on) {
 #pragma unroll
     for (int k = 0; k < 8; k += 2) {
       const uint32_t ba = R::key(rec[k]) >> 16, bb = R::key(rec[k + 1]) >> 16;
-      if (pc[k / 2] != 0u) {
-        rank[k] = atomicAdd(&cnt[ba], 1u);
-      } else if (ba == bb) {
+      if (joint(ba, bb)) {
         rank[k] = atomicAdd(&cnt[ba], 2u);
         rank[k + 1] = rank[k] + 1u;
       } else {
         rank[k] = atomicAdd(&cnt[ba], 1u);
-        rank[k + 1] = atomicAdd(&cnt[bb], 1u);
+        if (pc[k / 2] == 0u) rank[k + 1] = atomicAdd(&cnt[bb], 1u);
       }
     }
   }
   __syncthreads();
-  // lst = exclusive prefix of cnt (per-thread runs of bins, a wave scan of
-  // the thread totals, then the totals of the waves before); base from the
-  // bin's first slot and the unit's offset in it
-  const int per = (nb + kUnitSamples - 1) / kUnitSamples;
-  const int b0 = min(nb, t * per), b1 = min(nb, b0 + per);
-  uint32_t mine = 0;
-  for (int k = b0; k < b1; ++k) mine += cnt[k];
-  const uint32_t incl = wave_incl_scan_u32(mine);
-  if (lane == kWave - 1) wsum[wave] = incl;
-  __syncthreads();
-  uint32_t run = incl - mine, m = 0;
+  // lst = exclusive prefix of cnt; base from the bin's first slot and the
+  // unit's offset in it; m = the unit's records
+  uint32_t m = 0;
+  if (few) {  // by one wave, while the others wait
+    if (wave == 0) {
+      const uint32_t n = t < nb ? cnt[t] : 0u, incl = wave_incl_scan_u32(n);
+      if (t < nb) {
+        lst[t] = incl - n;
+        base[t] = first_slot - (incl - n);
+      }
+      if (lane == kWave - 1) wsum[0] = incl;
+    }
+    __syncthreads();
+    m = wsum[0];
+  } else {  // per-thread runs of bins, a wave scan of the thread totals, then the totals of the waves before
+    const int per = (nb + kUnitSamples - 1) / kUnitSamples;
+    const int b0 = min(nb, t * per), b1 = min(nb, b0 + per);
+    uint32_t mine = 0;
+    for (int k = b0; k < b1; ++k) mine += cnt[k];
+    const uint32_t incl = wave_incl_scan_u32(mine);
+    if (lane == kWave - 1) wsum[wave] = incl;
+    __syncthreads();
+    uint32_t run = incl - mine;
 #pragma unroll
-  for (int w = 0; w < kUnitWaves; ++w) {
-    run += w < wave ? wsum[w] : 0u;
-    m += wsum[w];
+    for (int w = 0; w < kUnitWaves; ++w) {
+      run += w < wave ? wsum[w] : 0u;
+      m += wsum[w];
+    }
+    for (int k = b0; k < b1; ++k) {
+      const uint32_t b = bl.first[l] + (uint32_t)k;
+      lst[k] = run;
+      base[k] = rb.bin_start[b] + rb.off[(size_t)b * bl.nunits + u] - run;
+      run += cnt[k];
+    }
+    __syncthreads();
   }
-  for (int k = b0; k < b1; ++k) {
-    const uint32_t b = bl.first[l] + (uint32_t)k;
-    lst[k] = run;
-    base[k] = rb.bin_start[b] + rb.off[(size_t)b * bl.nunits + u] - run;
-    run += cnt[k];
-  }
-  __syncthreads();
   if (m > (uint32_t)kStage) {  // (uniform) each record straight to its slot
     if (on) {
 #pragma unroll
@@ -361,7 +394,7 @@ __global__ __launch_bounds__(kUnitSamples) void bin_place_kernel(SampleSrc src, 
       const uint32_t sa = lst[ba] + rank[k];
       stage[sa] = rec[k];
       if (pc[k / 2] != 0u) continue;
-      if (ba == bb)
+      if (joint(ba, bb))
         stage[sa + 1] = rec[k + 1];
       else
         stage[lst[bb] + rank[k + 1]] = rec[k + 1];
@@ -485,16 +518,19 @@ __device__ __forceinline__ int direct_used(int S, int nparts) {
 // summed when the part is done.  With direct_sum_kernel, against the counting
 // sort it replaces on such tables (every record out and back, five launches):
 // 32 768 samples of the tiny field in FP32 12 + 4 us for 88, 2^20 samples in
-// mixed precision 73 + 11 us for 212.
+// mixed precision 57 + 11 us for 212.
 template <bool kBF16>
 __global__ __launch_bounds__(kDirectThreads) void direct_scatter_kernel(SampleSrc src, LevelInfo lv, BinLevels bl,
                                                                        RecordBuffers rb, uint32_t entries,
                                                                        int nparts) {
   constexpr int kSlots = kBinEntries + 64;  // room for one pad entry a copy
   __shared__ unsigned long long acc[kSlots];
-  // neighbouring workgroups of an XCD (blockIdx mod 8) take different levels
-  const int x = (int)(blockIdx.x & 7u), j = (int)(blockIdx.x >> 3);
-  const int l = j % bl.levels, b = x + 8 * (j / bl.levels);
+  // Neighbouring workgroups of an XCD (blockIdx mod 8) take different levels,
+  // and so do those 32 apart, which come to the same CU (32 an XCD): with the
+  // slow levels (the two largest of the tiny field) in pairs on half of the
+  // CUs, 2^20 samples took 73 us instead of 57.
+  const int x = (int)(blockIdx.x & 7u), j = (int)(blockIdx.x >> 3), p = j / bl.levels;
+  const int l = (j + p * bl.levels / 32 * (bl.levels / 2)) % bl.levels, b = x + 8 * p;
   const int S = sample_count(src), used = direct_used(S, nparts);
   if (b >= used) return;
   const uint32_t E = bl.size[l], stride = E + 1;  // the pad staggers the copies over the banks
@@ -688,7 +724,7 @@ template <class R>
 void place_and_reduce(const BinPlan& p, const RecordBuffers& rb, const SampleSrc& src, const LevelInfo& lv,
                       bool overwrite, float* grad_table, float* overflow, const WeightSum* sums, hipStream_t st) {
   float* zero_table = overwrite ? grad_table : nullptr;
-  if (sums && sums->shape == kShapeTiny)
+  if (p.levels == NetTiny::L)
     launch_place<R, NetTiny>(p, rb, src, lv, zero_table, sums, st);
   else
     launch_place<R, NetFull>(p, rb, src, lv, zero_table, sums, st);
