@@ -507,11 +507,12 @@ __global__ __launch_bounds__(kFieldBwdWaves * kWave, 2) void field_bwd_kernel(Fi
 }
 
 // Networks whose rendering runs on the BF16 matrix cores in three parts
-// (bf16_ops.h): the 64-wide ones.  At 640x480 x 64 samples of the paper-scale map
-// 4.25 ms with FP32 products, bound by them (2.6 ms of matrix cycles), 3.76 ms so,
-// the errors against 64 bits the same 8e-8 to 9e-8.  (Training keeps FP32
-// products throughout: a table entry's gradient may be a small residue of its
-// terms, and the optimiser divides it by its own size.)
+// (bf16_ops.h): the 64-wide ones, whose FP32 products would take 2.6 ms of
+// matrix cycles at 640x480 x 64 samples.  There 4.41 ms with FP32 products and
+// 3.98 so, at 320x240 1.65 and 1.60, at 160x120 0.62 and 0.61; the errors against
+// 64 bits are the same (1.0e-7).  (Training keeps FP32 products throughout: a
+// table entry's gradient may be a small residue of its terms, and the optimiser
+// divides it by its own size.)
 template <class N>
 constexpr bool kSplitNet = N::HD >= 64;
 
@@ -633,19 +634,17 @@ __device__ __forceinline__ void fp32_tile(const float* __restrict__ params, cons
 // ---------------------------------------------------------------------------
 constexpr int kRenderWaves = 4;                 // waves of a group of 16 pixels
 constexpr int kRenderRound = 4 * kRenderWaves;  // samples of a round
-// Pixel groups of a workgroup: two share one copy of the split operands (60 KB,
-// two workgroups a CU; with one group a workgroup, LDS would hold half the waves).
-template <class N>
-constexpr int kRenderGroups = kSplitNet<N> ? 2 : 1;
-template <class N>
-constexpr int kRenderThreads = kRenderGroups<N> * kRenderWaves * kWave;
+constexpr int kRenderThreads = kRenderWaves * kWave;
 
 // Weight, weighted mean and weighted squared deviation of some samples' t.
 struct Moments {
   float A, M, S;
   __device__ __forceinline__ void add(float w, float t) {
     if (w == 0.0f) return;
-    const float a = A + w, dt = t - M, r = dt * w * __builtin_amdgcn_rcpf(a);
+    // w / a by a reciprocal and one Newton step, scaled so that weights below
+    // the smallest normal number have one
+    const float a = A + w, dt = t - M, ws = w * 0x1p64f, as = a * 0x1p64f, rc = __builtin_amdgcn_rcpf(as);
+    const float q = ws * rc, r = dt * fmaf(fmaf(-as, q, ws), rc, q);
     M += r;
     S += A * dt * r;
     A = a;
@@ -658,57 +657,63 @@ struct Moments {
   }
 };
 
-// Workgroup -> pixels: with tiles, group k of the launch (kRenderGroups a
-// workgroup) takes the quarter k % 4 of tile k / 4, 16 consecutive pixels;
-// without, the workgroup takes block b of request 0's image, a row of 4x4
-// pixels a group (blocks_x blocks a row).  The grid is two-dimensional because
-// the largest images have more threads than one dimension of a launch may.
+// Workgroup -> pixels: with tiles, workgroup k takes the quarter k % 4 of tile
+// k / 4, 16 consecutive pixels; without, the workgroup takes block b of request
+// 0's image, 4x4 pixels (blocks_x blocks a row, nblocks in all).  The grid is
+// two-dimensional because the largest images have more threads than one
+// dimension of a launch may.
+//
+// One group of 16 pixels a workgroup, although the split operands (60 KB) then
+// leave room for two workgroups a CU: two groups on one copy of them, sixteen
+// waves a CU instead of eight, took 4.37 ms instead of 4.16 for 640x480 x 64
+// samples of the paper-scale map and 1.86 instead of 1.70 for 320x240; what more
+// waves gather at a time pushes the others' lines out of the caches.
 template <class N>
-__global__ __launch_bounds__(kRenderThreads<N>) __attribute__((amdgpu_waves_per_eu(4))) void render_kernel(
+__global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(4))) void render_kernel(
     LevelInfo lv, Aabb box, WOffsets wo, const nsl_render_request* __restrict__ reqs, int n_req,
     const nsl_render_tile* __restrict__ tiles, uint32_t nblocks, int blocks_x, RenderParams rp) {
-  constexpr int GR = kRenderGroups<N>;
   typedef typename std::conditional<kSplitNet<N>, __bf16, float>::type Op;
   constexpr int kOps = kSplitNet<N> ? 3 * Mixed<N>::FWD : N::FWD_FLOATS;
   __shared__ __attribute__((aligned(16))) Op Af[kOps];
-  __shared__ float4 tile_out[GR * kRenderWaves][4][16];  // (o_0, z) of a wave's four tiles
-  __shared__ float tau_of[2][GR][kRenderRound][16];
-  __shared__ float sums[GR][kRenderWaves][7][16];  // C, D and the moments
-  __shared__ int alive[2][GR];
-  const int gw = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
-  const int grp = gw / kRenderWaves, wave = gw % kRenderWaves;
+  __shared__ float4 tile_out[kRenderWaves][4][16];  // (o_0, z) of a wave's four tiles
+  __shared__ float tau_of[2][kRenderRound][16];
+  __shared__ float sums[kRenderWaves][7][16];  // C, D and the moments
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
   const int lane = lane_id(), g = lane >> 4, jc = lane & 15;
   // consecutive workgroups go round the 8 XCDs: of each 512 blocks an XCD
-  // takes 64 consecutive ones, whose lines it finds in its L2 (4.33 -> 4.24 ms
-  // for 640x480 at paper scale)
+  // takes 64 consecutive ones, as many as its CUs hold, whose lines it finds in its L2
+  // (16 or 256 of them were up to 2% and 7% slower)
   uint32_t blk = blockIdx.y * gridDim.x + blockIdx.x;
   if (blk >= nblocks) return;
   if ((blk | 511u) < nblocks) blk = (blk & ~511u) | ((blk & 7u) << 6) | ((blk >> 3) & 63u);
   int req = 0, u, v;
   bool in;
   if (tiles) {
-    constexpr int per = 4 / GR;  // workgroups a tile
-    const nsl_render_tile tile = tiles[blk / per];
+    const nsl_render_tile tile = tiles[blk / 4];
     req = tile.request;
     if (req < 0 || req >= n_req) return;
     const int npix = reqs[req].H * reqs[req].W;
-    const int first = max(tile.first_pixel, 0) + 16 * GR * (int)(blk % per);
+    const int first = max(tile.first_pixel, 0) + 16 * (int)(blk % 4);
     const int last = min(tile.first_pixel + min(tile.n_pixels, NSL_RENDER_TILE), npix);
     if (first >= last) return;
-    in = first + 16 * grp + jc < last;
-    const int px = in ? first + 16 * grp + jc : first;
+    in = first + jc < last;
+    const int px = in ? first + jc : first;
     v = px / reqs[req].W;
     u = px - v * reqs[req].W;
   } else {
-    const int by = (int)blk / blocks_x, bx = (int)blk - by * blocks_x;
-    u = 4 * (GR * bx + grp) + (jc & 3);
+    // bands of four rows of blocks, down and then along each, so that the 64
+    // consecutive blocks an XCD works at are 64x16 pixels: rows of blocks
+    // instead took 4.08 ms against 3.98, and at 320x240 1.70 against 1.60
+    const int rows = (reqs[0].H + 3) / 4, band = 4 * ((int)blk / (4 * blocks_x)), high = min(4, rows - band);
+    const int i = (int)blk - band * blocks_x, bx = i / high, by = band + i - bx * high;
+    u = 4 * bx + (jc & 3);
     v = 4 * by + (jc >> 2);
     in = u < reqs[0].W && v < reqs[0].H;
     u = min(u, reqs[0].W - 1);
     v = min(v, reqs[0].H - 1);
   }
   const nsl_render_request& rq = reqs[req];
-  copy_to_lds<kRenderThreads<N>, sizeof(Af)>(Af, rq.prepared);
+  copy_to_lds<kRenderThreads, sizeof(Af)>(Af, rq.prepared);
   __syncthreads();
   LaneLevels<N> ll;
   lane_levels<N>(lv, g, ll);
@@ -722,68 +727,59 @@ __global__ __launch_bounds__(kRenderThreads<N>) __attribute__((amdgpu_waves_per_
   float carry = 0.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f, D = 0.0f;
   Moments mo{0.0f, 0.0f, 0.0f};
   bool done = !in;                          // this lane's ray has stopped
-  bool live = __ballot(!done) != 0ull;      // some ray of the group has not
   const int rounds = (rp.n_samples + kRenderRound - 1) / kRenderRound;
   const int mine = 4 * wave + g;            // this lane's sample of a round
   for (int q = 0; q < rounds; ++q) {
     const int j = q * kRenderRound + mine;
     const bool valid = j < rp.n_samples;
     const float t = t_of(j);
-    float(*tw)[16] = tau_of[q & 1][grp];
-    float4 oz;
-    float tau = 0.0f;
-    if (live) {
-      for (int k = 0; k < 4; ++k) {
-        const int jk = q * kRenderRound + 4 * wave + k;
-        if (jk >= rp.n_samples) break;
-        const float tk = t_of(jk);
-        float xn[3];
+    float(*tw)[16] = tau_of[q & 1];
+    for (int k = 0; k < 4; ++k) {
+      const int jk = q * kRenderRound + 4 * wave + k;
+      if (jk >= rp.n_samples) break;
+      const float tk = t_of(jk);
+      float xn[3];
 #pragma unroll
-        for (int i = 0; i < 3; ++i) xn[i] = normalise_axis(pos_axis(o[i], d[i], tk), box.lo[i], box.inv[i]);
-        f4 oo, zz;
-        if constexpr (kSplitNet<N>) {
-          float e[1][N::NSLOT];
-          encode<N>(rq.params, lv.table_mask, ll, xn, e[0]);
-          const f4 sh[1] = {f4{shv[0], shv[1], shv[2], shv[3]}};
-          f4 o1[1], z1[1];
-          split_mlp<N, 1>(Af, lane, e, sh, o1, z1);
-          if (any_not_finite(o1[0], z1[0])) fp32_tile<N>(rq.params, wo, lane, e[0], sh[0], o1[0], z1[0]);
-          oo = o1[0];
-          zz = z1[0];
-        } else {
-          Acts<N> act;
-          encode<N>(rq.params, lv.table_mask, ll, xn, act.e);
+      for (int i = 0; i < 3; ++i) xn[i] = normalise_axis(pos_axis(o[i], d[i], tk), box.lo[i], box.inv[i]);
+      f4 oo, zz;
+      if constexpr (kSplitNet<N>) {
+        float e[1][N::NSLOT];
+        encode<N>(rq.params, lv.table_mask, ll, xn, e[0]);
+        const f4 sh[1] = {f4{shv[0], shv[1], shv[2], shv[3]}};
+        f4 o1[1], z1[1];
+        split_mlp<N, 1>(Af, lane, e, sh, o1, z1);
+        if (any_not_finite(o1[0], z1[0])) fp32_tile<N>(rq.params, wo, lane, e[0], sh[0], o1[0], z1[0]);
+        oo = o1[0];
+        zz = z1[0];
+      } else {
+        Acts<N> act;
+        encode<N>(rq.params, lv.table_mask, ll, xn, act.e);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) act.sh[i] = shv[i];
-          mlp_fwd<N>(Af, lane, act);
-          oo = act.o;
-          zz = act.z;
-        }
-        // lanes of row 0 hold pixel jc's density and colour
-        if (g == 0) tile_out[gw][k][jc] = make_float4(oo[0], zz[0], zz[1], zz[2]);
+        for (int i = 0; i < 4; ++i) act.sh[i] = shv[i];
+        mlp_fwd<N>(Af, lane, act);
+        oo = act.o;
+        zz = act.z;
       }
-      wave_lds_fence();
-      oz = tile_out[gw][g][jc];
-      tau = valid ? expf(oz.x) * rp.dt : 0.0f;
-      tw[mine][jc] = tau;
+      // lanes of row 0 hold pixel jc's density and colour
+      if (g == 0) tile_out[wave][k][jc] = make_float4(oo[0], zz[0], zz[1], zz[2]);
     }
+    wave_lds_fence();
+    const float4 oz = tile_out[wave][g][jc];
+    const float tau = valid ? expf(oz.x) * rp.dt : 0.0f;
+    tw[mine][jc] = tau;
     __syncthreads();
-    if (GR > 1 && q > 0 && rp.stop_T > 0.0f) {  // the groups leave together
-      int any = 0;
+    // optical depth of the round before this sample, and of all of it, by
+    // sums of four (in order, sixteen roundings would reach T)
+    float sum4[kRenderWaves], before = 0.0f;
 #pragma unroll
-      for (int k = 0; k < GR; ++k) any |= alive[(q - 1) & 1][k];
-      if (!any) break;
+    for (int w = 0; w < kRenderWaves; ++w) {
+      const float t0 = tw[4 * w][jc], t1 = tw[4 * w + 1][jc], t2 = tw[4 * w + 2][jc], t3 = tw[4 * w + 3][jc];
+      sum4[w] = (t0 + t1) + (t2 + t3);
+      if (w == wave) before = (g > 0 ? t0 : 0.0f) + (g > 1 ? t1 : 0.0f) + (g > 2 ? t2 : 0.0f);
     }
-    if (!live) {
-      if (GR > 1 && wave == 0 && lane == 0) alive[q & 1][grp] = 0;
-      continue;
-    }
-    float before = 0.0f, round = 0.0f;  // optical depth of the round before this sample, and of all of it
-#pragma unroll
-    for (int i = 0; i < kRenderRound; ++i) {
-      if (i == mine) before = round;
-      round += tw[i][jc];
-    }
+    const float half = sum4[0] + sum4[1];
+    before += wave > 2 ? half + sum4[2] : wave > 1 ? half : wave > 0 ? sum4[0] : 0.0f;
+    const float round = half + (sum4[2] + sum4[3]);
     const float T0 = expf(-(carry + before));
     carry += round;
     const bool on = valid && !done && !(rp.stop_T > 0.0f && T0 < rp.stop_T);
@@ -797,9 +793,7 @@ __global__ __launch_bounds__(kRenderThreads<N>) __attribute__((amdgpu_waves_per_
     }
     if (rp.stop_T > 0.0f) {
       done |= expf(-carry) < rp.stop_T;
-      live = __ballot(!done) != 0ull;  // every wave of the group holds the same sums
-      if (GR == 1 && !live) break;
-      if (GR > 1 && wave == 0 && lane == 0) alive[q & 1][grp] = live;
+      if (__ballot(!done) == 0ull) break;  // every wave holds the same sums
     }
   }
   {
@@ -808,15 +802,15 @@ __global__ __launch_bounds__(kRenderThreads<N>) __attribute__((amdgpu_waves_per_
     for (int i = 0; i < 4; ++i) {
       s4[i] += __shfl_xor(s4[i], 16, kWave);
       s4[i] += __shfl_xor(s4[i], 32, kWave);
-      if (g == 0) sums[grp][wave][i][jc] = s4[i];
+      if (g == 0) sums[wave][i][jc] = s4[i];
     }
 #pragma unroll
     for (int x = 16; x <= 32; x <<= 1)
       mo.merge(__shfl_xor(mo.A, x, kWave), __shfl_xor(mo.M, x, kWave), __shfl_xor(mo.S, x, kWave));
     if (g == 0) {
-      sums[grp][wave][4][jc] = mo.A;
-      sums[grp][wave][5][jc] = mo.M;
-      sums[grp][wave][6][jc] = mo.S;
+      sums[wave][4][jc] = mo.A;
+      sums[wave][5][jc] = mo.M;
+      sums[wave][6][jc] = mo.S;
     }
   }
   __syncthreads();
@@ -825,7 +819,7 @@ __global__ __launch_bounds__(kRenderThreads<N>) __attribute__((amdgpu_waves_per_
   mo = Moments{0.0f, 0.0f, 0.0f};
 #pragma unroll
   for (int w = 0; w < kRenderWaves; ++w) {
-    const float(*p)[16] = sums[grp][w];
+    const float(*p)[16] = sums[w];
     C0 += p[0][jc];
     C1 += p[1][jc];
     C2 += p[2][jc];
@@ -899,13 +893,12 @@ static hipError_t launch_render(const LevelInfo& lv, const Aabb& box, const WOff
                                 const nsl_render_request* reqs, int n_req, const nsl_render_tile* tiles, int n_tiles,
                                 int H, int W, const RenderParams& rp, hipStream_t st) {
   static_assert(NSL_RENDER_TILE == 64, "four groups of 16 pixels a tile");
-  constexpr int GR = kRenderGroups<N>;
-  const int64_t bx = ((int64_t)W + 4 * GR - 1) / (4 * GR);
-  const int64_t nblocks = tiles ? (int64_t)n_tiles * (4 / GR) : bx * (((int64_t)H + 3) / 4);
+  const int64_t bx = ((int64_t)W + 3) / 4;
+  const int64_t nblocks = tiles ? (int64_t)n_tiles * 4 : bx * (((int64_t)H + 3) / 4);
   if (nblocks <= 0) return hipSuccess;
   const int64_t gx = std::min<int64_t>(nblocks, 1 << 20);
   hipLaunchKernelGGL(render_kernel<N>, dim3((unsigned)gx, (unsigned)((nblocks + gx - 1) / gx)),
-                     dim3(kRenderThreads<N>), 0, st, lv, box, wo, reqs, n_req, tiles, (uint32_t)nblocks, (int)bx, rp);
+                     dim3(kRenderThreads), 0, st, lv, box, wo, reqs, n_req, tiles, (uint32_t)nblocks, (int)bx, rp);
   return hipGetLastError();
 }
 

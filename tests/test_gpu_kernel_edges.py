@@ -247,3 +247,34 @@ def test_render_of_values_that_are_not_finite(nsl, gpu, bad, where):
         ok = np.isfinite(ref)
         assert ok.any() or where != "table"
         assert np.allclose(got[ok], ref[ok], rtol=1e-4, atol=1e-6)
+
+
+def test_render_of_vanishing_densities(nsl, gpu):
+    """Every density about 1e-38, so that a sample's weight is below the
+    smallest number with a reciprocal: depth and depth variance, whose running
+    mean divides by the weights' sum, stay finite and tiny."""
+    import torch
+    spec = W.C1_FIELD
+    f = nsl.Field(spec)
+    H, Wd, n = 24, 32, 16
+    flat, _, _ = params_for(spec, f.layout, seed=3, table_range=0.5)
+    flat[:f.layout["table_floats"]] = 0.3                 # one encoding, so one density, everywhere
+    w1 = flat[f.layout["w_offsets"][1]:][:spec.density_hidden * spec.geo_dim].reshape(-1, spec.geo_dim)
+    w1[:, 0] = -np.abs(w1[:, 0])
+    xn = np.random.default_rng(1).uniform(size=(256, 3)).astype(np.float32)
+    ws = torch.empty(f.workspace_bytes(len(xn)), dtype=torch.uint8, device=gpu)
+    X, D = _t(torch, gpu, xn), _t(torch, gpu, np.tile(np.float32([0, 0, 1]), (len(xn), 1)))
+    o = np.log(f.fwd(_t(torch, gpu, flat), X, D, ws)[0].cpu().numpy().astype(np.float64))
+    w1[:, 0] *= np.float32(-87.0 / np.median(o))
+    P = _t(torch, gpu, flat)
+    dt = 2.0 / n
+    sg = f.fwd(P, X, D, ws)[0].cpu().numpy().astype(np.float64)
+    assert np.all(sg > 0) and np.all(sg * dt < 2.0 ** -128)
+    cfg = nsl.render_config(0.5, dt, n, 0.0)
+    rw = torch.empty(nsl.render_workspace_bytes(f, H, Wd, cfg), dtype=torch.uint8, device=gpu)
+    pose = W.look_at_pose((1.5, 0.2, 0.1)).astype(np.float32).reshape(12)
+    intr = np.array([0.9375 * Wd, 0.9375 * Wd, Wd / 2, H / 2], np.float32)
+    rgb, dz, vz, _ = nsl.render(f, P, _t(torch, gpu, pose), _t(torch, gpu, intr), H, Wd, cfg, rw)
+    for a in (rgb, dz, vz):
+        a = a.cpu().numpy()
+        assert np.all(np.isfinite(a)) and np.all(a >= 0) and np.all(a < 1e-30)
