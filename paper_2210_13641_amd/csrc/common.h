@@ -124,23 +124,6 @@ __device__ __forceinline__ RayLoss ray_loss(const float C[3], float D, float4 ta
 // Wave-wide helpers (wave64).
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
-}
-
-// Inclusive scan across the wave.
-__device__ __forceinline__ float wave_incl_scan(float v) {
-  const int l = lane_id();
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    float n = __shfl_up(v, o, kWave);
-    if (l >= o) v += n;
-  }
-  return v;
-}
-
 // DPP row shift towards lower lanes: lane i of each 16-lane row receives the
 // value of lane i+N of the same row (0 when i+N leaves the row).
 template <int N>
@@ -155,6 +138,61 @@ __device__ __forceinline__ float row_from_above(float v) {
 template <int N>
 __device__ __forceinline__ int row_from_below(int v) {
   return __builtin_amdgcn_update_dpp(0, v, 0x110 + N, 0xF, 0xF, true);
+}
+
+// Cross-lane moves of a whole wave without LDS (every lane is active).
+// rotated<N>: lane i of each row gets lane i - N of it, modulo 16.
+template <int N>
+__device__ __forceinline__ float row_rotated(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xF, 0xF, true));
+}
+// Lane i gets lane i - 1, lane 0 zero.
+__device__ __forceinline__ float wave_up_1(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xF, 0xF, true));
+}
+typedef unsigned u2 __attribute__((ext_vector_type(2)));
+// Rows (0, 0, 2, 2) and (1, 1, 3, 3) of v; halves (0, 0) of a and of b.
+__device__ __forceinline__ u2 even_odd_rows(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return u2{r[0], r[1]};
+}
+__device__ __forceinline__ u2 swap_halves(uint32_t a, uint32_t b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  return u2{r[0], r[1]};
+}
+// Lane i gets lane i - 16 (the first row any value).
+__device__ __forceinline__ float wave_up_16(float v) {
+  const u2 r = even_odd_rows(v);                  // (0, 0, 2, 2), (1, 1, 3, 3)
+  const uint32_t h = swap_halves(r[0], r[1])[0];  // (0, 0, 1, 1)
+  return __uint_as_float((lane_id() & 48) == 32 ? h : r[0]);
+}
+
+// Sum over the wave, in every lane: pairs of lanes 32 apart, then 16, 8, 4, 2
+// and 1 (from 8 on a rotation brings the lane that many further, as the values repeat).
+__device__ __forceinline__ float wave_sum(float v) {
+  const u2 h = swap_halves(__float_as_uint(v), __float_as_uint(v));
+  v = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+  const u2 r = even_odd_rows(v);
+  v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  v += row_rotated<8>(v);
+  v += row_rotated<4>(v);
+  v += row_rotated<2>(v);
+  return v + row_rotated<1>(v);
+}
+
+// Inclusive scan across the wave: to each lane the value 1, 2, 4, 8, 16 and 32
+// lanes below in turn.
+__device__ __forceinline__ float wave_incl_scan(float v) {
+  const int l = lane_id();
+  v += wave_up_1(v);
+  v += wave_up_1(wave_up_1(v));
+  v += wave_up_1(wave_up_1(wave_up_1(wave_up_1(v))));
+  const float rot = row_rotated<8>(v), below = wave_up_16(rot);
+  v += (l & 8) ? rot : l < 16 ? 0.0f : below;
+  const float up = wave_up_16(v);
+  v += l < 16 ? 0.0f : up;
+  const float half = __uint_as_float(swap_halves(__float_as_uint(v), __float_as_uint(v))[0]);
+  return v + (l < 32 ? 0.0f : half);
 }
 
 // Inclusive prefix sum over the wave: within each row by DPP shifts, then the
