@@ -329,8 +329,8 @@ __device__ __forceinline__ void tile_operands(const TileIn<N>& in, int g, PActs<
 // transpose 4 x 16 values a 16-lane row.
 // ---------------------------------------------------------------------------
 constexpr int kBwdWaves = 16;
-// Networks whose backward may gather the encoding itself: the four-level
-// ones.  The larger ones are always given it.
+// Networks whose tables fit an L2: the four-level ones.  Their backward may
+// gather the encoding itself; the larger ones' is always given it.
 template <class N>
 constexpr bool kGathers = N::LPL == 1;
 constexpr int kStepSamples = 16 * kBwdWaves;  // samples of a workgroup step
@@ -701,6 +701,61 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void m
   }
 }
 
+// Forward of many samples without a given encoding, for the networks of 16
+// levels: a wave takes 64 samples and gathers level after level, one sample a
+// lane, so that all waves are at about the same level and its 2 MB stay in
+// each XCD's L2 (mixed_fwd_kernel gathers all levels of 16 samples at once, 24 MB
+// of tables).  Bound by the misses all the same, and by the lines a CU's
+// loads take in.  From kWalkMin samples on it is the faster one: a call of 100003
+// random samples 86.6 -> 71.5 us (the kernel 71.4 -> 64.8), 200000 160 -> 140, 40000
+// 39.1 -> 33.9, but 20000 25.9 -> 27.2 and 5000 13.9 -> 20.3, since a wave then
+// waits for 16 levels in turn.
+// (Two or four waves a workgroup, or two or four levels' loads in flight, were
+// slower up to 100000.)
+constexpr int kWalkMin = 32768;
+template <class N>
+__global__ __launch_bounds__(kWave) void mixed_fwd_walk_kernel(
+    LevelInfo lv, const _Float16* __restrict__ table, const __bf16* __restrict__ prep, SampleSrc src,
+    float* __restrict__ sigma_out, float* __restrict__ rgb_out) {
+  using M = Mixed<N>;
+  __shared__ __attribute__((aligned(16))) __bf16 Af[M::FWD];
+  __shared__ uint32_t enc[N::L][kWave];
+  copy_to_lds<kWave, sizeof(Af)>(Af, prep);
+  __syncthreads();
+  const int S = src.n_dev ? (int)*src.n_dev : src.n;
+  const int lane = lane_id(), g = lane >> 4, jc = lane & 15;
+  for (int64_t first = (int64_t)blockIdx.x * kWave; first < S; first += (int64_t)gridDim.x * kWave) {
+    const int s0 = (int)first, left = S - s0;
+    float xn[3] = {0.5f, 0.5f, 0.5f};
+    if (lane < left) load_position(src, s0 + lane, xn);
+#pragma unroll 1
+    for (int l = 0; l < N::L; ++l) {
+      Corner8 c;
+      corners(xn[0], xn[1], xn[2], lv.res[l], (lv.dense_bits >> l) & 1u, lv.table_mask, lv.offset[l], c);
+      const float2 e = blend_corners<true>(table, c);
+      enc[l][lane] = lane < left ? bf16_pair(e.x, e.y) : 0u;
+    }
+    wave_lds_fence();
+#pragma unroll 1
+    for (int t = 0; t < kWave / 16; ++t) {
+      if (16 * t >= left) break;
+      const bool valid = 16 * t + jc < left;
+      const int st = s0 + 16 * t + jc;
+      TileIn<N> in;
+      in.d[0] = 0.0f; in.d[1] = 0.0f; in.d[2] = 1.0f;
+      if (valid) load_direction(src, st, in.d);
+#pragma unroll
+      for (int q = 0; q < N::LPL; ++q) in.e[q] = enc[g + 4 * q][16 * t + jc];
+      PActs<N> a[1];
+      f4 sh[1];
+      tile_operands<N>(in, g, a[0], sh[0]);
+      fwd_tiles<N, 1>(Af, lane, sh, a);
+      fwd_store<N>(a[0], g, st, valid, sigma_out, rgb_out);
+    }
+    wave_lds_fence();
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Host launchers.  Shadow buffer: BF16 operands (forward, then backward),
 // padded to 256 bytes, then the FP16 table (same entry layout as FP32).
@@ -750,6 +805,13 @@ static hipError_t fwd_impl(const LevelInfo& lv, const void* shadow, const Sample
   const int grid = (tiles + 3) / 4 < kMixedFwdGrid ? (tiles + 3) / 4 : kMixedFwdGrid;
   const BinPrep none{};
   const BinPrep& b = bp ? *bp : none;
+  if constexpr (!kGathers<N>) {
+    if (!src.ecache && b.nbins == 0 && max_samples >= kWalkMin) {
+      hipLaunchKernelGGL(mixed_fwd_walk_kernel<N>, dim3(min(1 << 20, (max_samples - 1) / kWave + 1)), dim3(kWave), 0, st,
+                         lv, t16, ops, src, sigma, rgb);
+      return hipGetLastError();
+    }
+  }
   if (grid + b.nbins > 0)
     hipLaunchKernelGGL(mixed_fwd_kernel<N>, dim3(grid + b.nbins), dim3(256), 0, st, lv, t16, ops, src, sigma, rgb,
                        b);

@@ -114,6 +114,25 @@ def test_mixed_backward_at_step_edges(nsl, gpu, spec, S, k):
         check_mag(f"mixed step-edge parts W{j}", a + b, g, m, 1e-5)
 
 
+@pytest.mark.parametrize("S", [32767, 32768, 32769, 32768 + 63, 40001])
+def test_mixed_forward_level_by_level(nsl, gpu, S):
+    """nsl_field_fwd_mixed of the 16-level field around the sample count from
+    which it gathers level by level: the same bits as calls of fewer samples,
+    which gather all levels at once."""
+    import torch
+    f = nsl.Field(W.C2_FIELD)
+    flat, _, _ = params_for(W.C2_FIELD, f.layout, seed=8, table_range=0.5)
+    rng = np.random.default_rng(S)
+    xn = _t(torch, gpu, rng.uniform(-0.01, 1.01, size=(S, 3)).astype(np.float32))
+    d = rng.normal(size=(S, 3))
+    d = _t(torch, gpu, (d / np.linalg.norm(d, axis=1, keepdims=True)).astype(np.float32))
+    shadow = f.prepare_mixed(_t(torch, gpu, flat))
+    sg, rgb = f.fwd_mixed(shadow, xn, d)
+    for lo in range(0, S, 16384):
+        a, b = f.fwd_mixed(shadow, xn[lo:lo + 16384].contiguous(), d[lo:lo + 16384].contiguous())
+        assert torch.equal(sg[lo:lo + 16384], a) and torch.equal(rgb[lo:lo + 16384], b)
+
+
 @pytest.mark.parametrize("c,p", [(1, 1), (15, 63), (16, 64), (17, 257), (48, 300), (60, 65), (60, 70001)])
 def test_covariance_at_tile_edges(nsl, gpu, c, p):
     """nsl_depth_covariance around the 16x16 tiles, the 16-pixel groups, the
