@@ -505,10 +505,11 @@ int nsl_train_step(nsl_mapper* m, const nsl_field* f, float* params, float* grad
   src.ecache_stride = c->max_samples;
   if (src.ecache) {
     uint32_t* hist = counted ? b.rec.hist : nullptr;
+    const int64_t entries = f->lay.table_floats / 2;
     if (mixed)
-      HIP_TRY(mixed_encode(f->shape, f->lv, b.shadow, src, c->max_samples, hist, b.plan.bl, st), "encoding");
+      HIP_TRY(mixed_encode(f->shape, f->lv, b.shadow, src, c->max_samples, hist, b.plan.bl, entries, st), "encoding");
     else
-      HIP_TRY(field_encode(f->shape, fa, src, c->max_samples, hist, b.plan.bl, st), "encoding");
+      HIP_TRY(field_encode(f->shape, fa, src, c->max_samples, hist, b.plan.bl, entries, st), "encoding");
   }
   HIP_TRY(mark(3), "profile event");
   // with the records counted, the table-gradient column scan and bin starts
@@ -673,7 +674,7 @@ int nsl_field_fwd(const nsl_field* f, const float* params, const float* xn, cons
   if (encodes_apart(f)) {
     src.ecache = w.rec.sorted;
     src.ecache_stride = S;
-    HIP_TRY(field_encode(f->shape, fa, src, S, nullptr, w.plan.bl, st), "encoding");
+    HIP_TRY(field_encode(f->shape, fa, src, S, nullptr, w.plan.bl, f->lay.table_floats / 2, st), "encoding");
   }
   HIP_TRY(field_forward(f->shape, fa, src, S, sigma, rgb, st), "field forward");
   return NSL_OK;
@@ -693,7 +694,9 @@ int nsl_field_bwd(const nsl_field* f, const float* params, const float* xn, cons
   if (encodes_apart(f)) {
     src.ecache = w.rec.sorted;
     src.ecache_stride = S;
-    HIP_TRY(field_encode(f->shape, fa, src, S, counted ? w.rec.hist : nullptr, w.plan.bl, st), "encoding");
+    HIP_TRY(field_encode(f->shape, fa, src, S, counted ? w.rec.hist : nullptr, w.plan.bl,
+                         f->lay.table_floats / 2, st),
+            "encoding");
   }
   HIP_TRY(field_backward(f->shape, fa, src, kBwdBlocks, dsigma, drgb, w.rec, w.partial, f->wo, grads, st),
           "field backward");
@@ -740,7 +743,9 @@ int nsl_field_bwd_mixed(const nsl_field* f, const void* shadow, const float* xn,
   if (encodes_apart(f)) {
     src.ecache = w.rec.sorted;
     src.ecache_stride = S;
-    HIP_TRY(mixed_encode(f->shape, f->lv, shadow, src, S, counted ? w.rec.hist : nullptr, w.plan.bl, st), "encoding");
+    HIP_TRY(mixed_encode(f->shape, f->lv, shadow, src, S, counted ? w.rec.hist : nullptr, w.plan.bl,
+                         f->lay.table_floats / 2, st),
+            "encoding");
   }
   HIP_TRY(mixed_backward(f->shape, f->lv, shadow, src, kBwdBlocks, dsigma, drgb, w.rec, w.partial, f->wo, grads, st),
           "field backward (mixed)");
@@ -830,7 +835,7 @@ int nsl_encode_fwd(const nsl_field* f, const float* params, const float* xn, int
   SampleSrc src{};
   src.xn = xn; src.box = f->box; src.n = S; src.ecache = e_out; src.ecache_stride = S;
   FieldArgs fa{params, nullptr, f->lv};
-  HIP_TRY(field_encode(f->shape, fa, src, S, nullptr, BinLevels{}, st), "encoding");
+  HIP_TRY(field_encode(f->shape, fa, src, S, nullptr, BinLevels{}, f->lay.table_floats / 2, st), "encoding");
   return NSL_OK;
 }
 
@@ -842,7 +847,8 @@ int nsl_encode_fwd_mixed(const nsl_field* f, const void* shadow, const float* xn
   if (misaligned(shadow)) return fail(NSL_E_INVALID, "shadow must be 16-byte aligned");
   SampleSrc src{};
   src.xn = xn; src.box = f->box; src.n = S; src.ecache = e_out; src.ecache_stride = S;
-  HIP_TRY(mixed_encode(f->shape, f->lv, shadow, src, S, nullptr, BinLevels{}, st), "encoding (mixed)");
+  HIP_TRY(mixed_encode(f->shape, f->lv, shadow, src, S, nullptr, BinLevels{}, f->lay.table_floats / 2, st),
+          "encoding (mixed)");
   return NSL_OK;
 }
 

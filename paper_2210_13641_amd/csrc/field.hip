@@ -963,20 +963,11 @@ hipError_t render_one(int shape, const LevelInfo& lv, const Aabb& box, const WOf
                              : launch_render<NetFull>(lv, box, wo, req, 1, nullptr, 0, H, W, rp, st);
 }
 
-template <class N>
-static hipError_t launch_encode(const FieldArgs& a, const SampleSrc& src, int max_samples, uint32_t* hist,
-                                const BinLevels& bl, hipStream_t st) {
-  const int grid = encode_grid<N>(max_samples);
-  if (grid > 0)
-    hipLaunchKernelGGL((encode_levels_kernel<N, float, float2>), dim3(grid), dim3(256), kEncodeLds<N>, st, a.lv, a.table, src,
-                       static_cast<float2*>(src.ecache), src.ecache_stride, hist, bl);
-  return hipGetLastError();
-}
-
 hipError_t field_encode(int shape, const FieldArgs& a, const SampleSrc& src, int max_samples, uint32_t* hist,
-                        const BinLevels& bl, hipStream_t st) {
-  return shape == kShapeTiny ? launch_encode<NetTiny>(a, src, max_samples, hist, bl, st)
-                             : launch_encode<NetFull>(a, src, max_samples, hist, bl, st);
+                        const BinLevels& bl, int64_t entries, hipStream_t st) {
+  return shape == kShapeTiny
+             ? launch_encode<NetTiny, float, float2>(a.lv, a.table, src, max_samples, hist, bl, entries, st)
+             : launch_encode<NetFull, float, float2>(a.lv, a.table, src, max_samples, hist, bl, entries, st);
 }
 
 __global__ __launch_bounds__(256) void loss_sum_kernel(LossSum ls) {

@@ -633,7 +633,8 @@ __global__ __launch_bounds__(kBwdWaves * kWave) void mixed_bwd8_kernel(
 // weight operands are staged into LDS once per workgroup rather than once per
 // four tiles; with the kept encoding, a wave fetches its next tile's inputs
 // while it computes the current one (ray indices two tiles ahead).
-constexpr int kMixedFwdGrid = 1024;
+template <class N>
+constexpr int kMixedFwdGrid = N::HD >= 64 ? 1024 : 2048;  // four or eight waves a SIMD
 
 template <class N>
 __device__ __forceinline__ void fwd_store(const PActs<N>& a, int g, int s, bool valid, float* __restrict__ sigma_out,
@@ -802,7 +803,7 @@ static hipError_t fwd_impl(const LevelInfo& lv, const void* shadow, const Sample
   const int tiles = (max_samples + 15) / 16;
   const __bf16* ops = static_cast<const __bf16*>(shadow);
   const _Float16* t16 = reinterpret_cast<const _Float16*>(static_cast<const char*>(shadow) + mixed_ops_bytes<N>());
-  const int grid = (tiles + 3) / 4 < kMixedFwdGrid ? (tiles + 3) / 4 : kMixedFwdGrid;
+  const int grid = std::min((tiles + 3) / 4, kMixedFwdGrid<N>);
   const BinPrep none{};
   const BinPrep& b = bp ? *bp : none;
   if constexpr (!kGathers<N>) {
@@ -832,19 +833,14 @@ static hipError_t bwd_impl(const LevelInfo& lv, const void* shadow, const Sample
 
 template <class N>
 static hipError_t encode_impl(const LevelInfo& lv, const void* shadow, const SampleSrc& src, int max_samples,
-                              uint32_t* hist, const BinLevels& bl, hipStream_t st) {
+                              uint32_t* hist, const BinLevels& bl, int64_t entries, hipStream_t st) {
   const _Float16* t16 = reinterpret_cast<const _Float16*>(static_cast<const char*>(shadow) + mixed_ops_bytes<N>());
-  const int grid = encode_grid<N>(max_samples);
-  if (grid > 0)
-    hipLaunchKernelGGL((encode_levels_kernel<N, _Float16, uint32_t>), dim3(grid), dim3(256), kEncodeLds<N>, st, lv, t16, src,
-                       static_cast<uint32_t*>(src.ecache), src.ecache_stride, hist, bl);
-  return hipGetLastError();
+  return launch_encode<N, _Float16, uint32_t>(lv, t16, src, max_samples, hist, bl, entries, st);
 }
-
 hipError_t mixed_encode(int shape, const LevelInfo& lv, const void* shadow, const SampleSrc& src, int max_samples,
-                        uint32_t* hist, const BinLevels& bl, hipStream_t st) {
-  return shape == kShapeTiny ? encode_impl<NetTiny>(lv, shadow, src, max_samples, hist, bl, st)
-                             : encode_impl<NetFull>(lv, shadow, src, max_samples, hist, bl, st);
+                        uint32_t* hist, const BinLevels& bl, int64_t entries, hipStream_t st) {
+  return shape == kShapeTiny ? encode_impl<NetTiny>(lv, shadow, src, max_samples, hist, bl, entries, st)
+                             : encode_impl<NetFull>(lv, shadow, src, max_samples, hist, bl, entries, st);
 }
 
 hipError_t mixed_prepare(int shape, const float* params, const WOffsets& wo, int64_t table_floats, void* shadow,

@@ -170,9 +170,10 @@ hipError_t field_dw_reduce(int shape, const float* partial, int nblocks, const W
 // hist (at most kEncodeLevelBins bins a level; nullable), also the
 // table-gradient record counts per bin and unit, written to every
 // hist[bin][unit] of bl (no clearing needed): bin_scatter can then skip its
-// counting pass.  bl.nunits must be the units of max_samples.
+// counting pass.  bl.nunits must be the units of max_samples.  entries: the
+// table's.
 hipError_t field_encode(int shape, const FieldArgs& a, const SampleSrc& src, int max_samples, uint32_t* hist,
-                        const BinLevels& bl, hipStream_t st);
+                        const BinLevels& bl, int64_t entries, hipStream_t st);
 
 struct RenderParams {
   float t_near, dt, stop_T;
@@ -203,7 +204,7 @@ hipError_t mixed_forward(int shape, const LevelInfo& lv, const void* shadow, con
 // The encoding of every sample of src into src.ecache (FP16 table, BF16 out);
 // hist as for field_encode.
 hipError_t mixed_encode(int shape, const LevelInfo& lv, const void* shadow, const SampleSrc& src, int max_samples,
-                        uint32_t* hist, const BinLevels& bl, hipStream_t st);
+                        uint32_t* hist, const BinLevels& bl, int64_t entries, hipStream_t st);
 hipError_t mixed_backward(int shape, const LevelInfo& lv, const void* shadow, const SampleSrc& src, int nblocks,
                           const float* dsigma, const float* drgb, const RecordBuffers& rec, float* partial,
                           const WOffsets& wo, float* grads, hipStream_t st);

@@ -114,6 +114,30 @@ def test_mixed_backward_at_step_edges(nsl, gpu, spec, S, k):
         check_mag(f"mixed step-edge parts W{j}", a + b, g, m, 1e-5)
 
 
+# four levels of 111 KB in FP32, which the encoding reads from memory, and 56 KB
+# in FP16, which it copies to LDS
+MID_TABLES = dataclasses.replace(W.C1_FIELD, log2_table=13)
+
+
+@pytest.mark.parametrize("spec", [W.C1_FIELD, MID_TABLES], ids=["in-lds", "fp16-in-lds"])
+@pytest.mark.parametrize("S", [1, 511, 513, 525001])
+def test_encode_of_tables_in_lds(nsl, gpu, spec, S):
+    """nsl_encode_fwd (1e-5 of the magnitudes) and nsl_encode_fwd_mixed (2e-2)
+    around the workgroup's 512 samples and past one round of all workgroups,
+    with points outside the box, for tables that fit LDS and one that does not."""
+    import torch
+    f = nsl.Field(spec)
+    flat, t64, _ = params_for(spec, f.layout, seed=10, table_range=0.5)
+    xn = np.random.default_rng(S).uniform(-0.02, 1.02, size=(S, 3)).astype(np.float32)
+    X, P = _t(torch, gpu, xn), _t(torch, gpu, flat)
+    got = nsl.encode_fwd(f, P, X).cpu().numpy()
+    half = nsl.encode_fwd_mixed(f, f.prepare_mixed(P), X).view(torch.bfloat16).float().cpu().numpy()
+    want, mag, _ = ofield.encode_fwd(spec, t64, np.clip(xn, 0, 1))
+    order = lambda a: a.reshape(spec.levels, S, 2).transpose(1, 0, 2).reshape(S, 2 * spec.levels)
+    check_mag("encoding", order(got), want, mag, 1e-5)
+    check_mag("encoding (mixed)", order(half), want, mag, 2e-2)
+
+
 @pytest.mark.parametrize("S", [32767, 32768, 32769, 32768 + 63, 40001])
 def test_mixed_forward_level_by_level(nsl, gpu, S):
     """nsl_field_fwd_mixed of the 16-level field around the sample count from
