@@ -321,3 +321,32 @@ def test_render_of_vanishing_densities(nsl, gpu):
     for a in (rgb, dz, vz):
         a = a.cpu().numpy()
         assert np.all(np.isfinite(a)) and np.all(a >= 0) and np.all(a < 1e-30)
+
+
+@pytest.mark.parametrize("n,shift", [(16385, 0), (24576, 0), (24577, 1), (40003, 3)])
+def test_march_scan_at_segment_edges(nsl, gpu, n, shift):
+    """nsl_march of more candidates than the sample emission scans itself,
+    around the scan's segments of 8192, with the caller's offsets at any
+    4-byte address: counts, offsets and statistics against their definition."""
+    import torch
+    from parity import upload_keyframes
+    kf = W.c1_keyframes()
+    f = nsl.Field(W.C1_FIELD)
+    m = upload_keyframes(nsl, torch, kf, gpu)
+    ids = np.random.default_rng(n).integers(0, 1100, size=n).astype(np.uint32)     # 1024 pixels are stored
+    cfg = nsl.step_config(W.C1_SAMPLER)
+    ws = torch.empty(nsl.step_workspace_bytes(f, cfg, n), dtype=torch.uint8, device=gpu)
+    counts = torch.zeros(n, dtype=torch.int32, device=gpu)
+    offs = torch.zeros(n + 1 + shift, dtype=torch.int32, device=gpu)[shift:]
+    t = torch.zeros(cfg.max_samples, dtype=torch.float32, device=gpu)
+    ray = torch.zeros(cfg.max_samples, dtype=torch.int32, device=gpu)
+    stats = torch.zeros(4, dtype=torch.int32, device=gpu)
+    nsl.march(m, f, cfg, _t(torch, gpu, ids.view(np.int32)), ws, counts, offs, t, ray, stats)
+    want = np.where(ids < 1024, 32, 0)
+    ends = np.cumsum(want)
+    kept = ends <= cfg.max_samples
+    assert np.array_equal(counts.cpu().numpy(), want)
+    assert np.array_equal(offs.cpu().numpy(), np.concatenate([[0], ends]))
+    got = stats.cpu().numpy()
+    assert got[:3].tolist() == [int(np.sum(kept & (want > 0))), int(ends[kept].max()), int(kept.sum())]
+    assert np.array_equal(ray.cpu().numpy()[:got[1]], np.repeat(np.arange(n), want)[:got[1]])
