@@ -511,24 +511,60 @@ __device__ __forceinline__ int direct_used(int S, int nparts) {
   return max(1, min(nparts, S / kDirectShare));
 }
 
+// The accumulators of an entry's two features.  Levels of at most 4096 entries
+// add in FP64, which LDS does without a loop; larger ones, whose FP64 sums
+// would leave one workgroup a CU, add FP32 pairs by compare-and-swap.
+struct PairF64 {
+  typedef double2 T;
+  static constexpr uint32_t kEntries = 4096;
+  static __device__ __forceinline__ void add(T* p, float a, float b) {
+    __hip_atomic_fetch_add(&p->x, (double)a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_fetch_add(&p->y, (double)b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  static __device__ __forceinline__ float2 sum(const T* p, uint32_t copies, uint32_t stride) {
+    double a = 0.0, b = 0.0;
+    for (uint32_t k = 0; k < copies; ++k) {
+      a += p[k * stride].x;
+      b += p[k * stride].y;
+    }
+    return make_float2((float)a, (float)b);
+  }
+};
+struct PairF32 {
+  typedef unsigned long long T;
+  static constexpr uint32_t kEntries = kBinEntries;
+  static __device__ __forceinline__ void add(T* p, float a, float b) { lds_add_pair(p, a, b); }
+  static __device__ __forceinline__ float2 sum(const T* p, uint32_t copies, uint32_t stride) {
+    float a = 0.0f, b = 0.0f;
+    for (uint32_t k = 0; k < copies; ++k) {
+      const T w = p[k * stride];
+      a += __uint_as_float((uint32_t)w);
+      b += __uint_as_float((uint32_t)(w >> 32));
+    }
+    return make_float2(a, b);
+  }
+};
+
 // Sums of one level over one part of the samples, in LDS, then to
-// parts[b][entry].  What bounds it is the LDS compare-and-swap where the lanes
-// of the workgroup meet in a few entries (a level of 125 entries), so a level
-// takes as many copies of its accumulators as fit (one copy a group of lanes),
-// summed when the part is done.  With direct_sum_kernel, against the counting
-// sort it replaces on such tables (every record out and back, five launches):
-// 32 768 samples of the tiny field in FP32 12 + 4 us for 88, 2^20 samples in
-// mixed precision 57 + 11 us for 212.
-template <bool kBF16>
+// parts[b][entry].  A level takes as many copies of its accumulators as fit (one
+// copy a group of lanes), summed when the part is done, since lanes that meet in
+// an entry queue (a level of 125 entries).  With FP64 sums it is bound by vector
+// instructions (corners, run sums), with FP32 ones by those of the compare-and-swap loops
+// too: 2^20 samples of the tiny field in mixed precision 57.0 -> 47.0 us, 131072 in
+// FP32 18.1 -> 13.0.  With direct_sum_kernel, against the counting sort it replaces
+// on such tables (every record out and back, five launches): 32 768 samples of
+// the tiny field in FP32 8 + 4 us for 88, 2^20 samples in mixed precision
+// 47 + 11 us for 212.
+template <bool kBF16, class Acc>
 __global__ __launch_bounds__(kDirectThreads) void direct_scatter_kernel(SampleSrc src, LevelInfo lv, BinLevels bl,
                                                                        RecordBuffers rb, uint32_t entries,
                                                                        int nparts) {
-  constexpr int kSlots = kBinEntries + 64;  // room for one pad entry a copy
-  __shared__ unsigned long long acc[kSlots];
+  constexpr int kSlots = Acc::kEntries + 64;  // room for one pad entry a copy
+  __shared__ typename Acc::T acc[kSlots];
   // Neighbouring workgroups of an XCD (blockIdx mod 8) take different levels,
   // and so do those 32 apart, which come to the same CU (32 an XCD): with the
   // slow levels (the two largest of the tiny field) in pairs on half of the
-  // CUs, 2^20 samples took 73 us instead of 57.
+  // CUs, 2^20 samples took 73 us instead of 57 (with FP32 sums).
   const int x = (int)(blockIdx.x & 7u), j = (int)(blockIdx.x >> 3), p = j / bl.levels;
   const int l = (j + p * bl.levels / 32 * (bl.levels / 2)) % bl.levels, b = x + 8 * p;
   const int S = sample_count(src), used = direct_used(S, nparts);
@@ -536,12 +572,12 @@ __global__ __launch_bounds__(kDirectThreads) void direct_scatter_kernel(SampleSr
   const uint32_t E = bl.size[l], stride = E + 1;  // the pad staggers the copies over the banks
   uint32_t copies = 1;
   while (copies < 64 && 2 * copies * stride <= (uint32_t)kSlots) copies *= 2;
-  for (uint32_t i = threadIdx.x; i < copies * stride; i += kDirectThreads) acc[i] = 0ull;
+  for (uint32_t i = threadIdx.x; i < copies * stride; i += kDirectThreads) acc[i] = typename Acc::T{};
   __syncthreads();
   const int share = ((S + used - 1) / used + 63) / 64 * 64;
   const int s0 = b * share, s1 = min(S, s0 + share);
   const uint32_t loff = lv.offset[l];
-  unsigned long long* mine = acc + (threadIdx.x / 16 + threadIdx.x) % copies * stride;
+  typename Acc::T* mine = acc + (threadIdx.x / 16 + threadIdx.x) % copies * stride;
   for (int sb = s0; sb < s1; sb += kDirectThreads) {
     const int s = sb + (int)threadIdx.x;
     const bool valid = s < s1;
@@ -568,19 +604,13 @@ __global__ __launch_bounds__(kDirectThreads) void direct_scatter_kernel(SampleSr
         a0 = RecBF16::lo(w);
         a1 = RecBF16::hi(w);
       }
-      lds_add_pair(mine + (c.idx[k] - loff), a0, a1);
+      Acc::add(mine + (c.idx[k] - loff), a0, a1);
     }
   }
   __syncthreads();
   float2* out = reinterpret_cast<float2*>(rb.sorted) + (size_t)b * entries + loff;
   for (uint32_t e = threadIdx.x; e < E; e += kDirectThreads) {
-    float a0 = 0.0f, a1 = 0.0f;
-    for (uint32_t k = 0; k < copies; ++k) {
-      const unsigned long long w = acc[k * stride + e];
-      a0 += __uint_as_float((uint32_t)w);
-      a1 += __uint_as_float((uint32_t)(w >> 32));
-    }
-    out[e] = make_float2(a0, a1);
+    out[e] = Acc::sum(acc + e, copies, stride);
   }
 }
 
@@ -742,12 +772,10 @@ hipError_t bin_scatter(const BinPlan& p, const RecordBuffers& rb, const SampleSr
                        bool counted, const WeightSum* ws, bool prescanned) {
   if (p.direct_parts > 0) {
     const int grid = p.levels * ((p.direct_parts + 7) / 8 * 8);
-    if (bf16_values)
-      hipLaunchKernelGGL(direct_scatter_kernel<true>, dim3(grid), dim3(kDirectThreads), 0, st, src, lv, p.bl, rb,
-                         p.entries, p.direct_parts);
-    else
-      hipLaunchKernelGGL(direct_scatter_kernel<false>, dim3(grid), dim3(kDirectThreads), 0, st, src, lv, p.bl, rb,
-                         p.entries, p.direct_parts);
+    const bool f64 = *std::max_element(p.bl.size, p.bl.size + p.levels) <= PairF64::kEntries;
+    const auto scatter = f64 ? (bf16_values ? direct_scatter_kernel<true, PairF64> : direct_scatter_kernel<false, PairF64>)
+                             : (bf16_values ? direct_scatter_kernel<true, PairF32> : direct_scatter_kernel<false, PairF32>);
+    hipLaunchKernelGGL(scatter, dim3(grid), dim3(kDirectThreads), 0, st, src, lv, p.bl, rb, p.entries, p.direct_parts);
     if (ws && ws->shape == kShapeTiny)
       launch_direct_sum<NetTiny>(p, rb, src, overwrite, grad_table, overflow, ws, st);
     else
