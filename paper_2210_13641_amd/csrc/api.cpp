@@ -533,6 +533,7 @@ int nsl_train_step(nsl_mapper* m, const nsl_field* f, float* params, float* grad
   CompositeIO io{};
   io.sigma = b.sigma; io.rgb = b.rgb; io.t = b.t; io.off = b.rb.offsets; io.counts = b.rb.counts;
   io.max_samples = c->max_samples; io.R = n; io.delta = c->dt; io.stop_T = 0.0f; io.out6 = nullptr;
+  io.max_per_ray = march_of(f, c).max_per_ray;
   LossIO lo{};
   lo.target = b.rb.target; lo.prec = b.rb.prec; lo.rays = b.rb.rays; lo.stats = b.rb.stats;
   lo.lambda_d = c->lambda_d; lo.loss_scale = c->loss_scale; lo.scale_dev = c->scale_state;

@@ -167,17 +167,37 @@ __device__ __forceinline__ float wave_up_16(float v) {
   return __uint_as_float((lane_id() & 48) == 32 ? h : r[0]);
 }
 
-// Sum over the wave, in every lane: pairs of lanes 32 apart, then 16, 8, 4, 2
-// and 1 (from 8 on a rotation brings the lane that many further, as the values repeat).
-__device__ __forceinline__ float wave_sum(float v) {
-  const u2 h = swap_halves(__float_as_uint(v), __float_as_uint(v));
-  v = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+// Sum over each half of the wave, in every lane: pairs of lanes 16 apart, then
+// 8, 4, 2 and 1 (from 8 on a rotation brings the lane that many further, as the
+// values repeat).
+__device__ __forceinline__ float half_sum(float v) {
   const u2 r = even_odd_rows(v);
   v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
   v += row_rotated<8>(v);
   v += row_rotated<4>(v);
   v += row_rotated<2>(v);
   return v + row_rotated<1>(v);
+}
+// Sum over the wave: pairs of lanes 32 apart, then the halves.
+__device__ __forceinline__ float wave_sum(float v) {
+  const u2 h = swap_halves(__float_as_uint(v), __float_as_uint(v));
+  return half_sum(__uint_as_float(h[0]) + __uint_as_float(h[1]));
+}
+
+// Inclusive scan across each half of the wave: to each lane the value 1, 2, 4, 8
+// and 16 lanes below in turn.
+__device__ __forceinline__ float half_incl_scan(float v) {
+  const int l = lane_id() & 31;
+  float up = wave_up_1(v);
+  v += l < 1 ? 0.0f : up;
+  up = wave_up_1(wave_up_1(v));
+  v += l < 2 ? 0.0f : up;
+  up = wave_up_1(wave_up_1(wave_up_1(wave_up_1(v))));
+  v += l < 4 ? 0.0f : up;
+  const float rot = row_rotated<8>(v), below = wave_up_16(rot);
+  v += (l & 8) ? rot : l < 16 ? 0.0f : below;
+  up = wave_up_16(v);
+  return v + (l < 16 ? 0.0f : up);
 }
 
 // Inclusive scan across the wave: to each lane the value 1, 2, 4, 8, 16 and 32

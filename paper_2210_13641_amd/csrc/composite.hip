@@ -294,6 +294,65 @@ __global__ __launch_bounds__(256) void composite_loss_kernel(CompositeIO io, Los
     ray_backward(io, b, n, s, gC, gD, 0.0f, 0.0f, g_sigma, g_rgb_s);
 }
 
+// The same for rays of at most 32 samples, one on each half of a wave: the same
+// sums in the same order (the upper lanes added zeros), in half the waves.
+// Bound by vector instructions: 32768 rays of 32 samples 25.6 us with a wave a
+// ray, 14.0 so; 1024 rays, which wait for memory either way, 4.8 and 4.4.
+__global__ __launch_bounds__(256) void composite_loss_half_kernel(CompositeIO io, LossIO lo,
+                                                                  float* __restrict__ g_sigma,
+                                                                  float* __restrict__ g_rgb_s, BinPrep bp) {
+  if (bp.nbins > 0 && blockIdx.x == gridDim.x - 1) {
+    bin_start_block<256>(bp.rb, bp.nbins, bp.chunk, bp.split);
+    return;
+  }
+  const int r = 2 * (blockIdx.x * kWavesPerBlock + threadIdx.x / kWave) + (lane_id() >> 5);
+  const uint32_t i = lane_id() & 31;
+  uint32_t b = 0, n = 0;
+  if (r >= io.R || !ray_span(io, r, b, n)) n = 0;  // no lane leaves: the sums below take all of them
+  const uint32_t s = b + i;
+  const bool on = i < n;
+  float sg = 0.0f, t = 0.0f, c[3] = {0.0f, 0.0f, 0.0f};
+  if (on) {
+    sg = io.sigma[s];
+    t = io.t[s];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) c[k] = io.rgb[3 * s + k];
+  }
+  const float tau = sg * io.delta, incl = half_incl_scan(tau);
+  const float T = expf(-(incl - tau)), Tn = expf(-incl), w = on ? T * -expm1f(-tau) : 0.0f;
+  RaySums m;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) m.C[k] = half_sum(w * c[k]);
+  m.D = half_sum(w * t);
+  m.A = half_sum(w);
+  const float e = t - m.D;
+  m.V = half_sum(w * e * e);
+  const float Rf = (float)lo.stats[0];
+  const float scale = lo.scale_dev ? lo.scale_dev[0] : lo.loss_scale;
+  const float kk = 2.0f * scale / Rf;
+  RayLoss L{};
+  if (n > 0) L = ray_loss(m.C, m.D, lo.target[r], lo.prec[r], kk, kk * lo.lambda_d);
+  if (i == 0 && r < io.R) {
+    lo.parts[2 * r] = n > 0 ? L.l_rgb / Rf : 0.0f;
+    lo.parts[2 * r + 1] = n > 0 ? L.l_d / Rf : 0.0f;
+    if (lo.ray_out) {
+      const float sc = n > 0 ? lo.rays[2 * r].w : 1.0f;
+      float* o = lo.ray_out + 6 * (size_t)r;
+      o[0] = m.C[0]; o[1] = m.C[1]; o[2] = m.C[2];
+      o[3] = m.D / sc; o[4] = m.V / (sc * sc); o[5] = m.A;
+    }
+  }
+  float dtau = 0.0f;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) dtau += L.gC[k] * (Tn * c[k] - (m.C[k] - half_incl_scan(w * c[k])));
+  dtau += L.gD * (Tn * t - (m.D - half_incl_scan(w * t)));
+  if (on) {
+    g_sigma[s] = io.delta * dtau;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) g_rgb_s[3 * s + k] = L.gC[k] * w;
+  }
+}
+
 // The loss of rays rendered outside the step (out6 from compositing, ray
 // units), one thread per ray: per-ray shares of L_rgb and L_D (divided by R)
 // into parts, and with g_out the seeds of the adjoint for the upstream
@@ -363,6 +422,12 @@ hipError_t composite_loss_backward(const CompositeIO& io, const LossIO& lo, floa
                                    float* g_rgb_s, hipStream_t st, const BinPrep* bp) {
   const BinPrep none{};
   const BinPrep& b = bp ? *bp : none;
+  if (io.max_per_ray > 0 && io.max_per_ray <= kWave / 2 && !(io.stop_T > 0.0f)) {
+    const int half = (int)grid_for((io.R + 1) / 2).x + (b.nbins > 0 ? 1 : 0);
+    if (half > 0)
+      hipLaunchKernelGGL(composite_loss_half_kernel, dim3(half), dim3(256), 0, st, io, lo, g_sigma, g_rgb_s, b);
+    return hipGetLastError();
+  }
   const int grid = (int)grid_for(io.R).x + (b.nbins > 0 ? 1 : 0);
   if (grid > 0)
     hipLaunchKernelGGL(composite_loss_kernel, dim3(grid), dim3(256), 0, st, io, lo, g_sigma, g_rgb_s, b);

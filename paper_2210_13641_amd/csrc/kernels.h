@@ -271,6 +271,7 @@ struct CompositeIO {
   float delta;
   float stop_T;
   float* out6;             // [R,6] ray units (or null)
+  int max_per_ray;         // no ray has more samples (0: not known)
 };
 
 struct LossIO {

@@ -350,3 +350,24 @@ def test_march_scan_at_segment_edges(nsl, gpu, n, shift):
     got = stats.cpu().numpy()
     assert got[:3].tolist() == [int(np.sum(kept & (want > 0))), int(ends[kept].max()), int(kept.sum())]
     assert np.array_equal(ray.cpu().numpy()[:got[1]], np.repeat(np.arange(n), want)[:got[1]])
+
+
+@pytest.mark.parametrize("n_uniform", [1, 16, 17, 31, 32, 33])
+def test_step_of_short_rays(nsl, gpu, n_uniform):
+    """An FP32 step of an odd number of candidates, one of them no stored pixel
+    and the last ones cut off, around the 32 samples a ray up to which two rays
+    share a wave in the compositing: every output and gradient at 1e-5."""
+    import torch
+    from test_gpu_parity import _compare_step, _step_gpu
+    sampler = dataclasses.replace(W.C1_SAMPLER, n_uniform=n_uniform, dt=2.0 / n_uniform,
+                                  max_samples=n_uniform * 997 + n_uniform // 2)
+    spec, kf = W.C1_FIELD, W.c1_keyframes()
+    ids = np.concatenate([W.c1_pixels()[:500], np.array([5000], np.uint32), W.c1_pixels()[500:1000]])
+    f = nsl.Field(spec)
+    flat, t64, w64 = params_for(spec, f.layout, seed=11, table_range=0.2)
+    stored = ids < 1024
+    o = ostep.train_step(spec, sampler, kf, t64, w64, ids[stored])
+    g = _step_gpu(nsl, torch, gpu, spec, sampler, kf, ids, flat)
+    assert np.all(g["rays"][~stored] == 0)
+    g["rays"] = g["rays"][stored]
+    _compare_step(spec, g, o, f.layout, tol=1e-5)
