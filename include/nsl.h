@@ -352,6 +352,11 @@ int nsl_composite_bwd(const float* sigma, const float* rgb, const float* t,
                       const float* g_depth, const float* g_var, const float* g_opacity,
                       float* g_sigma, float* g_rgb_s, hipStream_t stream);
 
+/* The same for the seeds of all six outputs as rows, g_out [R,6]. */
+int nsl_composite_bwd_rows(const float* sigma, const float* rgb, const float* t,
+                           const uint32_t* ray_off, int R, float delta, const float* g_out,
+                           float* g_sigma, float* g_rgb_s, hipStream_t stream);
+
 /* ------------------------------------------------------------------------
  * The mapping loss on its own (Sec. 3.2, Eq. 3, 4 and 7), for rays rendered
  * by nsl_composite_fwd (the autograd path); the step computes the same

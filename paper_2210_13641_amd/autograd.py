@@ -56,10 +56,8 @@ class CompositeFunction(torch.autograd.Function):
     @staticmethod
     def backward(ctx, g_out):
         sigma, rgb, t, ray_off = ctx.saved_tensors
-        g = g_out.contiguous()
-        g_sigma, g_rgb = nsl.composite_bwd(sigma.detach().contiguous(), rgb.detach().contiguous(), t, ray_off,
-                                           ctx.delta, g[:, 0:3].contiguous(), g[:, 3].contiguous(),
-                                           g[:, 4].contiguous(), g[:, 5].contiguous())
+        g_sigma, g_rgb = nsl.composite_bwd_rows(sigma.detach().contiguous(), rgb.detach().contiguous(), t, ray_off,
+                                                ctx.delta, g_out.contiguous())
         return g_sigma, g_rgb, None, None, None
 
 

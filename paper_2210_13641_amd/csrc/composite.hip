@@ -153,10 +153,12 @@ __global__ __launch_bounds__(256) void composite_fwd_kernel(CompositeIO io) {
   }
 }
 
+// Seeds of ray r: g_rgb[srgb r ..], g_depth[s1 r], g_var[s1 r], g_opacity[s1 r]
+// (separate arrays: srgb 3, s1 1; rows of six values a ray: 6 and 6).
 __global__ __launch_bounds__(256) void composite_bwd_kernel(CompositeIO io, const float* __restrict__ g_rgb,
                                                             const float* __restrict__ g_depth,
                                                             const float* __restrict__ g_var,
-                                                            const float* __restrict__ g_opacity,
+                                                            const float* __restrict__ g_opacity, int srgb, int s1,
                                                             float* __restrict__ g_sigma,
                                                             float* __restrict__ g_rgb_s) {
   const int r = blockIdx.x * kWavesPerBlock + threadIdx.x / kWave;
@@ -164,10 +166,10 @@ __global__ __launch_bounds__(256) void composite_bwd_kernel(CompositeIO io, cons
   uint32_t b, n;
   if (!ray_span(io, r, b, n)) return;
   const RaySums s = ray_forward(io, b, n);
-  const float gC[3] = {g_rgb ? g_rgb[3 * r] : 0.0f, g_rgb ? g_rgb[3 * r + 1] : 0.0f,
-                       g_rgb ? g_rgb[3 * r + 2] : 0.0f};
-  ray_backward(io, b, n, s, gC, g_depth ? g_depth[r] : 0.0f, g_var ? g_var[r] : 0.0f,
-               g_opacity ? g_opacity[r] : 0.0f, g_sigma, g_rgb_s);
+  const size_t p = (size_t)srgb * r, q = (size_t)s1 * r;
+  const float gC[3] = {g_rgb ? g_rgb[p] : 0.0f, g_rgb ? g_rgb[p + 1] : 0.0f, g_rgb ? g_rgb[p + 2] : 0.0f};
+  ray_backward(io, b, n, s, gC, g_depth ? g_depth[q] : 0.0f, g_var ? g_var[q] : 0.0f,
+               g_opacity ? g_opacity[q] : 0.0f, g_sigma, g_rgb_s);
 }
 
 // Rays of at most kCacheChunks * 64 samples (every training ray: the march
@@ -401,11 +403,11 @@ hipError_t composite_forward(const CompositeIO& io, hipStream_t st) {
 }
 
 hipError_t composite_backward(const CompositeIO& io, const float* g_rgb, const float* g_depth,
-                              const float* g_var, const float* g_opacity, float* g_sigma, float* g_rgb_s,
-                              hipStream_t st) {
+                              const float* g_var, const float* g_opacity, int srgb, int s1, float* g_sigma,
+                              float* g_rgb_s, hipStream_t st) {
   if (io.R > 0)
     hipLaunchKernelGGL(composite_bwd_kernel, grid_for(io.R), dim3(256), 0, st, io, g_rgb, g_depth,
-                       g_var, g_opacity, g_sigma, g_rgb_s);
+                       g_var, g_opacity, srgb, s1, g_sigma, g_rgb_s);
   return hipGetLastError();
 }
 

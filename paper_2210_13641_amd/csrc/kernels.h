@@ -288,9 +288,10 @@ struct LossIO {
 };
 
 hipError_t composite_forward(const CompositeIO& io, hipStream_t st);
+// Seeds as arrays of stride srgb (colour) and s1 (the others), in floats.
 hipError_t composite_backward(const CompositeIO& io, const float* g_rgb, const float* g_depth,
-                              const float* g_var, const float* g_opacity, float* g_sigma, float* g_rgb_s,
-                              hipStream_t st);
+                              const float* g_var, const float* g_opacity, int srgb, int s1, float* g_sigma,
+                              float* g_rgb_s, hipStream_t st);
 // Writes the per-ray loss shares to lo.parts; their sum into lo.loss is
 // left to a LossSum (the step's last reduction launch).
 hipError_t composite_loss_backward(const CompositeIO& io, const LossIO& lo, float* g_sigma,

@@ -371,3 +371,32 @@ def test_step_of_short_rays(nsl, gpu, n_uniform):
     assert np.all(g["rays"][~stored] == 0)
     g["rays"] = g["rays"][stored]
     _compare_step(spec, g, o, f.layout, tol=1e-5)
+
+
+@pytest.mark.parametrize("R", [1, 7, 1001])
+def test_composite_adjoint_of_rows(nsl, gpu, R):
+    """nsl_composite_bwd_rows gives the bits of nsl_composite_bwd with the
+    columns of its seeds; a gradient of another shape is refused, one that is
+    expanded or transposed differentiates the same."""
+    import torch
+    from paper_2210_13641_amd import autograd as ag
+    rng = np.random.default_rng(R)
+    n = rng.integers(0, 90, R)
+    off = _t(torch, gpu, np.concatenate([[0], np.cumsum(n)]).astype(np.int32))
+    S = max(1, int(n.sum()))
+    sg = _t(torch, gpu, np.exp(rng.normal(size=S)).astype(np.float32))
+    rgb = _t(torch, gpu, rng.uniform(size=(S, 3)).astype(np.float32))
+    t = _t(torch, gpu, np.sort(rng.uniform(0.5, 2.5, S)).astype(np.float32))
+    g = _t(torch, gpu, rng.normal(size=(R, 6)).astype(np.float32))
+    cols = (g[:, :3].contiguous(), *(g[:, k].contiguous() for k in (3, 4, 5)))
+    want = nsl.composite_bwd(sg, rgb, t, off, 0.03, *cols)
+    for seeds in (g, g.t().contiguous().t()):
+        a, b = sg.clone().requires_grad_(True), rgb.clone().requires_grad_(True)
+        ag.CompositeFunction.apply(a, b, t, off, 0.03).backward(seeds)
+        assert torch.equal(a.grad, want[0]) and torch.equal(b.grad, want[1])
+    a = sg.clone().requires_grad_(True)
+    ag.CompositeFunction.apply(a, rgb, t, off, 0.03).sum().backward()       # an expanded gradient
+    one = nsl.composite_bwd_rows(sg, rgb, t, off, 0.03, torch.ones(R, 6, device=gpu))
+    assert torch.equal(a.grad, one[0])
+    with pytest.raises(ValueError):
+        nsl.composite_bwd_rows(sg, rgb, t, off, 0.03, g[:, :3].contiguous())
