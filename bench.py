@@ -317,8 +317,8 @@ def main(argv=None):
         "roofline_fp32": roof_fp32,
         "rooflines": {"mixed": roofs, "fp32": roofs_fp32},
         "recompute_encoding": {
-            "note": "keep_encoding = 0: the backward gathers the table again instead of reading the encoding "
-                    "the forward kept",
+            "note": "keep_encoding = 0: no room of its own for the encoding, which waits in the space of the "
+                    "table-gradient records until the backward has read it",
             "mixed_samples_per_s": res["mixed"]["value"],
             "fp32_samples_per_s": res["fp32"]["value"],
             "full_step_samples_per_s": {"mixed": res["mixed"]["full_value"], "fp32": res["fp32"]["full_value"]},
