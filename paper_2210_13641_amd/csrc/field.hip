@@ -900,7 +900,7 @@ template <class N>
 static hipError_t launch_prep_count(const float* params, const WOffsets& wo, float* out, float* zero, int64_t nzero,
                                     float* clear_flag, const KeyframeStore& kf, const MarchParams& mp,
                                     const uint32_t* ids, int n, const RayBuffers& rb, hipStream_t st) {
-  const int ncount = (int)march_block_count(n), nfill = (int)((nzero + 1023) / 1024);
+  const int ncount = (int)count_block_count(mp, n), nfill = (int)((nzero + 1023) / 1024);
   const int nprep = (N::FWD_FLOATS + N::BWD_FLOATS + 255) / 256;
   hipLaunchKernelGGL(prepare_count_kernel<N>, dim3(ncount + nfill + nprep), dim3(256), 0, st, params, wo, out, zero,
                      nzero, nfill, clear_flag, kf, mp, ids, n, rb, ncount);

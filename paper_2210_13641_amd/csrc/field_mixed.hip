@@ -786,7 +786,7 @@ static hipError_t prep_impl(const float* params, const WOffsets& wo, int64_t tab
   const int tblocks = (int)((span + 2047) / 2048);
   const int oblocks = (nops + 255) / 256;
   if (kf) {
-    const int ncount = (int)march_block_count(n);
+    const int ncount = (int)count_block_count(*mp, n);
     hipLaunchKernelGGL(mixed_prepare_count_kernel<N>, dim3(ncount + tblocks + oblocks), dim3(256), 0, st, params,
                        wo, static_cast<__bf16*>(shadow), t16, table_floats, zero_grads, total, tblocks, clear_flag,
                        *kf, *mp, ids, n, *rb, ncount);

@@ -246,6 +246,9 @@ hipError_t march_emit(const KeyframeStore& kf, const MarchParams& mp, const uint
 // The offsets and batch cut of counts the ray setup has written.
 hipError_t march_scan(const MarchParams& mp, int n, const RayBuffers& rb, hipStream_t st);
 size_t march_block_count(int n);
+// Workgroups of the ray setup: a thread a ray with the uniform sampler, whose
+// counts need no marching, else a wave a ray.
+size_t count_block_count(const MarchParams& mp, int n);
 // mixed_prepare and the ray setup and sample counts of march_rays in one
 // launch (field_mixed.hip); march_scan then completes march_rays.
 hipError_t mixed_prepare_count(int shape, const float* params, const WOffsets& wo, int64_t table_floats,

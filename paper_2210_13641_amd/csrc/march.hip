@@ -307,13 +307,17 @@ size_t march_block_count(int n) {
   return (size_t)(n + march_detail::kWavesPerBlock - 1) / march_detail::kWavesPerBlock;
 }
 
+size_t count_block_count(const MarchParams& mp, int n) {
+  return mp.sampler == 0 ? ((size_t)n + 255) / 256 : march_block_count(n);
+}
+
 // The emit does the scan itself for 1 <= n <= kEmitScanMax candidates.
 static bool emit_scans(int n) { return n >= 1 && n <= kEmitScanMax; }
 
 hipError_t march_rays(const KeyframeStore& kf, const MarchParams& mp, const uint32_t* ids, int n,
                       const RayBuffers& rb, hipStream_t st) {
   if (n > 0)
-    hipLaunchKernelGGL(rays_count_kernel, dim3(march_block_count(n)), dim3(256), 0, st, kf, mp, ids, n, rb);
+    hipLaunchKernelGGL(rays_count_kernel, dim3(count_block_count(mp, n)), dim3(256), 0, st, kf, mp, ids, n, rb);
   return march_scan(mp, n, rb, st);
 }
 
