@@ -696,9 +696,11 @@ struct Moments {
 // leave room for two workgroups a CU: two groups on one copy of them, sixteen
 // waves a CU instead of eight, took 4.37 ms instead of 4.16 for 640x480 x 64
 // samples of the paper-scale map and 1.86 instead of 1.70 for 320x240; what more
-// waves gather at a time pushes the others' lines out of the caches.
+// waves gather at a time pushes the others' lines out of the caches.  (The tiny
+// field's tables stay in the caches; eight waves a SIMD instead of the seven its
+// registers would leave take 247 us for 252, eight requests of 2048 tiles.)
 template <class N>
-__global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(4))) void render_kernel(
+__global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(N::HD >= 64 ? 2 : 8))) void render_kernel(
     LevelInfo lv, Aabb box, WOffsets wo, const nsl_render_request* __restrict__ reqs, int n_req,
     const nsl_render_tile* __restrict__ tiles, uint32_t nblocks, int blocks_x, RenderParams rp) {
   typedef typename std::conditional<kSplitNet<N>, __bf16, float>::type Op;
