@@ -7,8 +7,8 @@ candidates per step cut at 2^18 samples (1..256 samples per ray).  A step is
 nsl_train_step: rays + march + field forward + compositing/loss + backward to
 parameter gradients (the headline; gradient clearing included), and the full
 step adds Adam.  The backward recomputes the MLP; the headline keeps the
-encoding from the forward (keep_encoding = 1), and the variant that gathers
-it again is reported beside it.  It runs in mixed precision (FP16 tables,
+encoding from the forward (keep_encoding = 1), and the variant without room
+of its own for it is reported beside it.  It runs in mixed precision (FP16 tables,
 BF16 MLP on MFMA, FP32 accumulation and masters; the headline value) and in
 plain FP32.  Inputs are resident in device memory before timing starts.
 
