@@ -656,33 +656,36 @@ __device__ __forceinline__ void fp32_tile(const float* __restrict__ params, cons
 // with the tiny field 105 -> 45 us (compositing four tiles at once, on every
 // lane instead of the 16 that hold a tile's outputs, 5.8 -> 4.3 ms of it).
 //
-// V* = sum w (t - d*)^2 is formed without a second pass: each lane carries the
-// weight A, the weighted mean M of t and S = sum w (t - M)^2 of its samples
-// (every term non-negative), the parts of a ray are merged pair by pair, and
-// V* = S + A (M - d*)^2.
+// V* = sum w (t - d*)^2 is formed without a second pass, from the sums of w, w t
+// and w t^2 in FP64: V* = sum w t^2 - d*^2 (2 - A).  The products of FP32 values
+// are exact or rounded at 2^-53, so what cancels costs no FP32 digit: over rays of
+// constant density, of 32 and 64 samples, the mean relative error of V* is that of
+// the weights, 3.6e-8 and 4.5e-8, against 7.0e-8 and 7.2e-8 for a second pass in
+// FP32 and 1.1e-7 and 1.0e-7 for a running weighted mean and squared deviation
+// in FP32, in the same time (608 us for 160x120 x 64 samples at paper scale).
 // ---------------------------------------------------------------------------
 constexpr int kRenderWaves = 4;                 // waves of a group of 16 pixels
 constexpr int kRenderRound = 4 * kRenderWaves;  // samples of a round
 constexpr int kRenderThreads = kRenderWaves * kWave;
 
-// Weight, weighted mean and weighted squared deviation of some samples' t.
+// Sums over some samples of w, w t and w t^2.
 struct Moments {
-  float A, M, S;
+  double A, D, S;
   __device__ __forceinline__ void add(float w, float t) {
-    if (w == 0.0f) return;
-    // w / a by a reciprocal and one Newton step, scaled so that weights below
-    // the smallest normal number have one
-    const float a = A + w, dt = t - M, ws = w * 0x1p64f, as = a * 0x1p64f, rc = __builtin_amdgcn_rcpf(as);
-    const float q = ws * rc, r = dt * fmaf(fmaf(-as, q, ws), rc, q);
-    M += r;
-    S += A * dt * r;
-    A = a;
+    const double wt = (double)w * (double)t;
+    A += (double)w;
+    D += wt;
+    S = fma(wt, (double)t, S);
   }
-  __device__ __forceinline__ void merge(float A2, float M2, float S2) {
-    const float a = A + A2, dm = M2 - M, f = a == 0.0f ? 0.0f : A2 / a;
-    S += S2 + dm * dm * A * f;
-    M += dm * f;
-    A = a;
+  __device__ __forceinline__ void add(const Moments& o) {
+    A += o.A;
+    D += o.D;
+    S += o.S;
+  }
+  // sum w (t - d*)^2, which rounding may leave just below zero
+  __device__ __forceinline__ double variance() const {
+    const double v = fma(-D * D, 2.0 - A, S);
+    return v < 0.0 ? 0.0 : v;
   }
 };
 
@@ -708,7 +711,8 @@ __global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(
   __shared__ __attribute__((aligned(16))) Op Af[kOps];
   __shared__ float4 tile_out[kRenderWaves][4][16];  // (o_0, z) of a wave's four tiles
   __shared__ float tau_of[2][kRenderRound][16];
-  __shared__ float sums[kRenderWaves][7][16];  // C, D and the moments
+  __shared__ float sums[kRenderWaves][3][16];  // C
+  __shared__ Moments moments[kRenderWaves][16];
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
   const int lane = lane_id(), g = lane >> 4, jc = lane & 15;
   // consecutive workgroups go round the 8 XCDs: of each 512 blocks an XCD
@@ -755,8 +759,8 @@ __global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(
 #pragma clang fp contract(off)
     return rp.t_near + ((float)j + 0.5f) * rp.dt;
   };
-  float carry = 0.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f, D = 0.0f;
-  Moments mo{0.0f, 0.0f, 0.0f};
+  float carry = 0.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f;
+  Moments mo{0.0, 0.0, 0.0};
   bool done = !in;                          // this lane's ray has stopped
   const int rounds = (rp.n_samples + kRenderRound - 1) / kRenderRound;
   const int mine = 4 * wave + g;            // this lane's sample of a round
@@ -819,7 +823,6 @@ __global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(
       C0 += w * sigmoidf(oz.y);
       C1 += w * sigmoidf(oz.z);
       C2 += w * sigmoidf(oz.w);
-      D += w * t;
       mo.add(w, t);
     }
     if (rp.stop_T > 0.0f) {
@@ -828,43 +831,37 @@ __global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(
     }
   }
   {
-    float s4[4] = {C0, C1, C2, D};
+    float s3[3] = {C0, C1, C2};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      s4[i] += __shfl_xor(s4[i], 16, kWave);
-      s4[i] += __shfl_xor(s4[i], 32, kWave);
-      if (g == 0) sums[wave][i][jc] = s4[i];
+    for (int i = 0; i < 3; ++i) {
+      s3[i] += __shfl_xor(s3[i], 16, kWave);
+      s3[i] += __shfl_xor(s3[i], 32, kWave);
+      if (g == 0) sums[wave][i][jc] = s3[i];
     }
 #pragma unroll
     for (int x = 16; x <= 32; x <<= 1)
-      mo.merge(__shfl_xor(mo.A, x, kWave), __shfl_xor(mo.M, x, kWave), __shfl_xor(mo.S, x, kWave));
-    if (g == 0) {
-      sums[wave][4][jc] = mo.A;
-      sums[wave][5][jc] = mo.M;
-      sums[wave][6][jc] = mo.S;
-    }
+      mo.add(Moments{__shfl_xor(mo.A, x, kWave), __shfl_xor(mo.D, x, kWave), __shfl_xor(mo.S, x, kWave)});
+    if (g == 0) moments[wave][jc] = mo;
   }
   __syncthreads();
   if (wave != 0 || g != 0 || !in) return;
-  C0 = C1 = C2 = D = 0.0f;
-  mo = Moments{0.0f, 0.0f, 0.0f};
+  C0 = C1 = C2 = 0.0f;
+  mo = Moments{0.0, 0.0, 0.0};
 #pragma unroll
   for (int w = 0; w < kRenderWaves; ++w) {
     const float(*p)[16] = sums[w];
     C0 += p[0][jc];
     C1 += p[1][jc];
     C2 += p[2][jc];
-    D += p[3][jc];
-    mo.merge(p[4][jc], p[5][jc], p[6][jc]);
+    mo.add(moments[w][jc]);
   }
-  const float e = mo.M - D, V = mo.S + mo.A * e * e;
   const size_t px = (size_t)v * rq.W + u;
   rq.rgb[3 * px] = C0;
   rq.rgb[3 * px + 1] = C1;
   rq.rgb[3 * px + 2] = C2;
-  rq.depth_z[px] = D / s;
-  rq.var_z[px] = V / (s * s);
-  if (rq.opacity) rq.opacity[px] = mo.A;
+  rq.depth_z[px] = (float)mo.D / s;
+  rq.var_z[px] = (float)mo.variance() / (s * s);
+  if (rq.opacity) rq.opacity[px] = (float)mo.A;
 }
 
 // ---------------------------------------------------------------------------

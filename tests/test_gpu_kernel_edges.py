@@ -400,3 +400,33 @@ def test_composite_adjoint_of_rows(nsl, gpu, R):
     assert torch.equal(a.grad, one[0])
     with pytest.raises(ValueError):
         nsl.composite_bwd_rows(sg, rgb, t, off, 0.03, g[:, :3].contiguous())
+
+
+@pytest.mark.parametrize("spec", [W.C1_FIELD, W.C2_FIELD], ids=["tiny", "full"])
+@pytest.mark.parametrize("n", [32, 64])
+def test_render_depth_variance_error(nsl, gpu, spec, n):
+    """V* of rays of constant density 1 (a field of zeros) against FP64: the
+    mean relative error over 400 rays of different t_near and dt stays below
+    8e-8.  Weights and t rounded to FP32 with V* summed exactly give 3.6e-8
+    (32 samples) and 4.5e-8 (64), with the sum about the final d* in FP32
+    7.0e-8 and 7.2e-8."""
+    import torch
+    f = nsl.Field(spec)
+    P = torch.zeros(f.layout["total"], device=gpu)
+    pose = _t(torch, gpu, W.look_at_pose((1.5, 0.0, 0.0)).astype(np.float32).reshape(12))
+    intr = _t(torch, gpu, np.array([1.0, 1.0, 0.5, 0.5], np.float32))    # the pixel looks straight ahead: s = 1
+    rng = np.random.default_rng(n)
+    j = np.arange(n, dtype=np.float32) + np.float32(0.5)
+    got, want = [], []
+    ws = None
+    for _ in range(400):
+        near, dt = np.float32(rng.uniform(0.05, 2.0)), np.float32(np.exp(rng.uniform(np.log(0.01), np.log(0.3))))
+        cfg = nsl.render_config(float(near), float(dt), n, 0.0)
+        if ws is None:
+            ws = torch.empty(nsl.render_workspace_bytes(f, 1, 1, cfg), dtype=torch.uint8, device=gpu)
+        got.append(nsl.render(f, P, pose, intr, 1, 1, cfg, ws)[2])
+        t = (near + j * dt).astype(np.float64)
+        w = np.exp(-np.float64(dt) * np.arange(n)) * -np.expm1(-np.float64(dt))
+        want.append((w * (t - (w * t).sum()) ** 2).sum())
+    err = np.abs(torch.cat(got).cpu().numpy().astype(np.float64) / np.array(want) - 1.0)
+    assert err.mean() < 8e-8, err.mean()
