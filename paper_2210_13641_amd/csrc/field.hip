@@ -8,6 +8,7 @@
 // forward kernel; the backward kernel re-derives every activation from the
 // sample position instead of reading stored activations.
 #include <algorithm>
+#include <type_traits>
 
 #include "bf16_ops.h"
 #include "bins.h"
@@ -646,6 +647,14 @@ __device__ __forceinline__ void fp32_tile(const float* __restrict__ params, cons
 // of the round through LDS (one barrier a round), and the rays leave together,
 // once the transmittance left for each is below stop_T.
 //
+// A group of fewer pixels (the edge of an image, a ragged tile, an image of one
+// row) does not repeat them over the columns: with np pixels rounded up to a power
+// of two P, a tile takes 16 / P consecutive samples of each, the waves share the
+// tiles of a pass of 16 / P rounds, and the rounds are composited in their order,
+// so that a pixel has the same bits whatever shares its workgroup.  At 64 samples
+// one pixel took 64 us at paper scale as 16 equal columns, 20 so; 19200 tiles of
+// one pixel 11.7 and 2.2 ms, 16384 pixels in one row 689 and 212 us.
+//
 // The gathers bound it.  Samples of one ray are several cells apart at the
 // fine levels, so a tile of 16 samples of a ray touched four lines of the
 // table per sample and level; 16 neighbouring pixels at one depth share most
@@ -709,10 +718,12 @@ __global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(
   typedef typename std::conditional<kSplitNet<N>, __bf16, float>::type Op;
   constexpr int kOps = kSplitNet<N> ? 3 * Mixed<N>::FWD : N::FWD_FLOATS;
   __shared__ __attribute__((aligned(16))) Op Af[kOps];
-  __shared__ float4 tile_out[kRenderWaves][4][16];  // (o_0, z) of a wave's four tiles
+  __shared__ float4 tile_out[kRenderRound][16];  // (o_0, z) of sample 16 r + m: [m][column r P + pixel]
   __shared__ float tau_of[2][kRenderRound][16];
   __shared__ float sums[kRenderWaves][3][16];  // C
   __shared__ Moments moments[kRenderWaves][16];
+  __shared__ float scale_of[16];
+  __shared__ uint32_t px_of[16];
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
   const int lane = lane_id(), g = lane >> 4, jc = lane & 15;
   // consecutive workgroups go round the 8 XCDs: of each 512 blocks an XCD
@@ -721,8 +732,12 @@ __global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(
   uint32_t blk = blockIdx.y * gridDim.x + blockIdx.x;
   if (blk >= nblocks) return;
   if ((blk | 511u) < nblocks) blk = (blk & ~511u) | ((blk & 7u) << 6) | ((blk >> 3) & 63u);
-  int req = 0, u, v;
-  bool in;
+  // its np pixels, pix of which this lane's column takes: np rounded up to P = 2^lg
+  int req = 0, u, v, np, lg, pix;
+  auto columns = [&] {
+    lg = np > 1 ? 32 - __clz(np - 1) : 0;
+    pix = jc & ((1 << lg) - 1);
+  };
   if (tiles) {
     const nsl_render_tile tile = tiles[blk / 4];
     req = tile.request;
@@ -731,8 +746,9 @@ __global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(
     const int first = max(tile.first_pixel, 0) + 16 * (int)(blk % 4);
     const int last = min(tile.first_pixel + min(tile.n_pixels, NSL_RENDER_TILE), npix);
     if (first >= last) return;
-    in = first + jc < last;
-    const int px = in ? first + jc : first;
+    np = min(16, last - first);
+    columns();
+    const int px = first + min(pix, np - 1);
     v = px / reqs[req].W;
     u = px - v * reqs[req].W;
   } else {
@@ -741,11 +757,12 @@ __global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(
     // instead took 4.08 ms against 3.98, and at 320x240 1.70 against 1.60
     const int rows = (reqs[0].H + 3) / 4, band = 4 * ((int)blk / (4 * blocks_x)), high = min(4, rows - band);
     const int i = (int)blk - band * blocks_x, bx = i / high, by = band + i - bx * high;
-    u = 4 * bx + (jc & 3);
-    v = 4 * by + (jc >> 2);
-    in = u < reqs[0].W && v < reqs[0].H;
-    u = min(u, reqs[0].W - 1);
-    v = min(v, reqs[0].H - 1);
+    const int w4 = min(4, reqs[0].W - 4 * bx);
+    np = w4 * min(4, reqs[0].H - 4 * by);
+    columns();
+    const int at = min(pix, np - 1), y = w4 == 3 ? (at * 11) >> 5 : at >> (w4 / 2);  // at / w4
+    u = 4 * bx + at - y * w4;
+    v = 4 * by + y;
   }
   const nsl_render_request& rq = reqs[req];
   copy_to_lds<kRenderThreads, sizeof(Af)>(Af, rq.prepared);
@@ -755,81 +772,122 @@ __global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(
   float o[3], d[3], s, shv[4];
   camera_ray(rq.pose, rq.intr, u, v, o, d, s);
   sh_lane<N>(d, g, shv);
+  if (threadIdx.x < 16) {
+    scale_of[jc] = s;
+    px_of[jc] = (uint32_t)(v * rq.W + u);
+  }
   auto t_of = [&](int j) {
 #pragma clang fp contract(off)
     return rp.t_near + ((float)j + 0.5f) * rp.dt;
   };
   float carry = 0.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f;
   Moments mo{0.0, 0.0, 0.0};
-  bool done = !in;                          // this lane's ray has stopped
-  const int rounds = (rp.n_samples + kRenderRound - 1) / kRenderRound;
+  bool done = pix >= np;                    // this lane's ray has stopped
   const int mine = 4 * wave + g;            // this lane's sample of a round
-  for (int q = 0; q < rounds; ++q) {
-    const int j = q * kRenderRound + mine;
-    const bool valid = j < rp.n_samples;
-    const float t = t_of(j);
-    float(*tw)[16] = tau_of[q & 1];
-    for (int k = 0; k < 4; ++k) {
-      const int jk = q * kRenderRound + 4 * wave + k;
-      if (jk >= rp.n_samples) break;
-      const float tk = t_of(jk);
-      float xn[3];
+  // the passes over the rays' samples: one round each where a group has all
+  // columns (kFull), else 2^per
+  auto passes = [&](auto full) {
+    constexpr bool kFull = decltype(full)::value;
+    const int r = kFull ? 0 : jc >> lg, per = kFull ? 0 : 4 - lg;
+    const int span = kRenderRound << per;
+    auto from_round = [&](auto x, int i) { return __shfl(x, (lane & 48) | (i << lg) | pix, kWave); };
+    for (int base = 0, q = 0; base < rp.n_samples; base += span, ++q) {
+      const int left = min(rp.n_samples - base, span), nr = (left + kRenderRound - 1) / kRenderRound;
+      const int ntile = (left + (1 << per) - 1) >> per;
+      for (int k = 0; k < 4; ++k) {
+        const int ti = kFull ? 4 * wave + k : wave + kRenderWaves * k;
+        if (ti >= ntile) break;
+        const int jl = (ti << per) + r;       // this column's sample of the pass
+        const float tk = t_of(base + jl);
+        float xn[3];
 #pragma unroll
-      for (int i = 0; i < 3; ++i) xn[i] = normalise_axis(pos_axis(o[i], d[i], tk), box.lo[i], box.inv[i]);
-      f4 oo, zz;
-      if constexpr (kSplitNet<N>) {
-        float e[1][N::NSLOT];
-        encode<N>(rq.params, lv.table_mask, ll, xn, e[0]);
-        const f4 sh[1] = {f4{shv[0], shv[1], shv[2], shv[3]}};
-        f4 o1[1], z1[1];
-        split_mlp<N, 1>(Af, lane, e, sh, o1, z1);
-        if (any_not_finite(o1[0], z1[0])) fp32_tile<N>(rq.params, wo, lane, e[0], sh[0], o1[0], z1[0]);
-        oo = o1[0];
-        zz = z1[0];
-      } else {
-        Acts<N> act;
-        encode<N>(rq.params, lv.table_mask, ll, xn, act.e);
+        for (int i = 0; i < 3; ++i) xn[i] = normalise_axis(pos_axis(o[i], d[i], tk), box.lo[i], box.inv[i]);
+        f4 oo, zz;
+        if constexpr (kSplitNet<N>) {
+          float e[1][N::NSLOT];
+          encode<N>(rq.params, lv.table_mask, ll, xn, e[0]);
+          const f4 sh[1] = {f4{shv[0], shv[1], shv[2], shv[3]}};
+          f4 o1[1], z1[1];
+          split_mlp<N, 1>(Af, lane, e, sh, o1, z1);
+          if (any_not_finite(o1[0], z1[0])) fp32_tile<N>(rq.params, wo, lane, e[0], sh[0], o1[0], z1[0]);
+          oo = o1[0];
+          zz = z1[0];
+        } else {
+          Acts<N> act;
+          encode<N>(rq.params, lv.table_mask, ll, xn, act.e);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) act.sh[i] = shv[i];
-        mlp_fwd<N>(Af, lane, act);
-        oo = act.o;
-        zz = act.z;
+          for (int i = 0; i < 4; ++i) act.sh[i] = shv[i];
+          mlp_fwd<N>(Af, lane, act);
+          oo = act.o;
+          zz = act.z;
+        }
+        // lanes of row 0 hold the column's density and colour
+        const int row = kFull ? ti : jl & (kRenderRound - 1), col = kFull ? jc : ((jl / kRenderRound) << lg) | pix;
+        if (g == 0) tile_out[row][col] = make_float4(oo[0], zz[0], zz[1], zz[2]);
       }
-      // lanes of row 0 hold pixel jc's density and colour
-      if (g == 0) tile_out[wave][k][jc] = make_float4(oo[0], zz[0], zz[1], zz[2]);
-    }
-    wave_lds_fence();
-    const float4 oz = tile_out[wave][g][jc];
-    const float tau = valid ? expf(oz.x) * rp.dt : 0.0f;
-    tw[mine][jc] = tau;
-    __syncthreads();
-    // optical depth of the round before this sample, and of all of it, by
-    // sums of four (in order, sixteen roundings would reach T)
-    float sum4[kRenderWaves], before = 0.0f;
+      if constexpr (kFull)
+        wave_lds_fence();  // a wave composites its own tiles
+      else
+        __syncthreads();
+      const int j = base + kRenderRound * r + mine;
+      const bool valid = j < rp.n_samples;
+      const float t = t_of(j);
+      float(*tw)[16] = tau_of[q & 1];
+      const float4 oz = tile_out[mine][jc];
+      const float tau = valid ? expf(oz.x) * rp.dt : 0.0f;
+      tw[mine][jc] = tau;
+      __syncthreads();
+      // optical depth of the round before this sample, and of all of it, by
+      // sums of four (in order, sixteen roundings would reach T)
+      float sum4[kRenderWaves], before = 0.0f;
 #pragma unroll
-    for (int w = 0; w < kRenderWaves; ++w) {
-      const float t0 = tw[4 * w][jc], t1 = tw[4 * w + 1][jc], t2 = tw[4 * w + 2][jc], t3 = tw[4 * w + 3][jc];
-      sum4[w] = (t0 + t1) + (t2 + t3);
-      if (w == wave) before = (g > 0 ? t0 : 0.0f) + (g > 1 ? t1 : 0.0f) + (g > 2 ? t2 : 0.0f);
+      for (int w = 0; w < kRenderWaves; ++w) {
+        const float t0 = tw[4 * w][jc], t1 = tw[4 * w + 1][jc], t2 = tw[4 * w + 2][jc], t3 = tw[4 * w + 3][jc];
+        sum4[w] = (t0 + t1) + (t2 + t3);
+        if (w == wave) before = (g > 0 ? t0 : 0.0f) + (g > 1 ? t1 : 0.0f) + (g > 2 ? t2 : 0.0f);
+      }
+      const float half = sum4[0] + sum4[1];
+      before += wave > 2 ? half + sum4[2] : wave > 1 ? half : wave > 0 ? sum4[0] : 0.0f;
+      const float round = half + (sum4[2] + sum4[3]);
+      float start = carry;  // the optical depth before this lane's round
+      if constexpr (kFull) {
+        carry += round;
+      } else {
+        for (int i = 0; i < nr; ++i) {
+          if (r == i) start = carry;
+          carry += from_round(round, i);
+        }
+      }
+      const float T0 = expf(-(start + before));
+      const bool on = valid && !done && !(rp.stop_T > 0.0f && (T0 < rp.stop_T || (!kFull && expf(-start) < rp.stop_T)));
+      auto add = [&] {
+        const float w = T0 * -expm1f(-tau);
+        C0 = fmaf(w, sigmoidf(oz.y), C0);
+        C1 = fmaf(w, sigmoidf(oz.z), C1);
+        C2 = fmaf(w, sigmoidf(oz.w), C2);
+        mo.add(w, t);
+      };
+      if constexpr (kFull) {
+        if (on) add();
+      } else {  // round after round, as the rays of a full group
+        for (int i = 0; i < nr; ++i) {
+          if (on && r == i) add();
+          C0 = from_round(C0, i);
+          C1 = from_round(C1, i);
+          C2 = from_round(C2, i);
+          mo = Moments{from_round(mo.A, i), from_round(mo.D, i), from_round(mo.S, i)};
+        }
+      }
+      if (rp.stop_T > 0.0f) {
+        done |= expf(-carry) < rp.stop_T;
+        if (__ballot(!done) == 0ull) break;  // every wave holds the same sums
+      }
     }
-    const float half = sum4[0] + sum4[1];
-    before += wave > 2 ? half + sum4[2] : wave > 1 ? half : wave > 0 ? sum4[0] : 0.0f;
-    const float round = half + (sum4[2] + sum4[3]);
-    const float T0 = expf(-(carry + before));
-    carry += round;
-    const bool on = valid && !done && !(rp.stop_T > 0.0f && T0 < rp.stop_T);
-    if (on) {
-      const float w = T0 * -expm1f(-tau);
-      C0 += w * sigmoidf(oz.y);
-      C1 += w * sigmoidf(oz.z);
-      C2 += w * sigmoidf(oz.w);
-      mo.add(w, t);
-    }
-    if (rp.stop_T > 0.0f) {
-      done |= expf(-carry) < rp.stop_T;
-      if (__ballot(!done) == 0ull) break;  // every wave holds the same sums
-    }
-  }
+  };
+  if (lg == 4)
+    passes(std::true_type{});
+  else
+    passes(std::false_type{});
   {
     float s3[3] = {C0, C1, C2};
 #pragma unroll
@@ -844,7 +902,7 @@ __global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(
     if (g == 0) moments[wave][jc] = mo;
   }
   __syncthreads();
-  if (wave != 0 || g != 0 || !in) return;
+  if (wave != 0 || g != 0 || jc >= np) return;
   C0 = C1 = C2 = 0.0f;
   mo = Moments{0.0, 0.0, 0.0};
 #pragma unroll
@@ -855,7 +913,8 @@ __global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(
     C2 += p[2][jc];
     mo.add(moments[w][jc]);
   }
-  const size_t px = (size_t)v * rq.W + u;
+  const size_t px = px_of[jc];
+  s = scale_of[jc];
   rq.rgb[3 * px] = C0;
   rq.rgb[3 * px + 1] = C1;
   rq.rgb[3 * px + 2] = C2;

@@ -430,3 +430,71 @@ def test_render_depth_variance_error(nsl, gpu, spec, n):
         want.append((w * (t - (w * t).sum()) ** 2).sum())
     err = np.abs(torch.cat(got).cpu().numpy().astype(np.float64) / np.array(want) - 1.0)
     assert err.mean() < 8e-8, err.mean()
+
+
+@pytest.mark.parametrize("stop_T", [0.0, 0.3])
+@pytest.mark.parametrize("spec,n", [(W.C1_FIELD, 1), (W.C1_FIELD, 17), (W.C1_FIELD, 300), (W.C2_FIELD, 40),
+                                    (W.C2_FIELD, 300)], ids=["tiny-1", "tiny-17", "tiny-300", "full-40", "full-300"])
+def test_render_of_few_pixels_equals_the_whole_image(nsl, gpu, spec, n, stop_T):
+    """Groups of 1 to 16 pixels, whose tiles hold 16 to 1 samples of a ray,
+    give the pixels of nsl_render bit for bit: one pass over a ray and several,
+    images whose edges are groups of one to four columns or rows, of one pixel,
+    one row and one column."""
+    import torch
+    f = nsl.Field(spec)
+    flat, _, _ = params_for(spec, f.layout, seed=n, table_range=2.0)
+    P = _t(torch, gpu, flat)
+    prep = nsl.prepare(f, P)
+    pose = W.look_at_pose((1.5, 0.3, 0.2)).astype(np.float32).reshape(12)
+    cfg = nsl.render_config(0.5, 2.0 / n, n, stop_T)
+    rng = np.random.default_rng(n)
+    for H, Wd in ((1, 1), (1, 37), (33, 1), (2, 19), (7, 13)):
+        intr = np.array([12.0, 12.0, Wd / 2, H / 2], np.float32)
+        new = lambda: [torch.full((H * Wd, 3), -9.0, device=gpu)] + [torch.full((H * Wd,), -9.0, device=gpu) for _ in range(3)]
+        whole, tiled = new(), new()
+        ws = torch.empty(nsl.render_workspace_bytes(f, H, Wd, cfg), dtype=torch.uint8, device=gpu)
+        nsl.render(f, P, _t(torch, gpu, pose), _t(torch, gpu, intr), H, Wd, cfg, ws, *whole)
+        assert all(bool((a != -9.0).all()) for a in whole)
+        tiles, p = [], 0
+        while p < H * Wd:
+            k = int(rng.integers(1, 20))
+            tiles.append(nsl.RenderTile(0, p, k))
+            p += k
+        rq = nsl.records_to_device([nsl.render_request(P, prep, pose, intr, H, Wd, *tiled)], nsl.RenderRequest, gpu)
+        nsl.render_batch(f, rq, 1, nsl.records_to_device(tiles, nsl.RenderTile, gpu), len(tiles), cfg)
+        for a, b in zip(whole, tiled):
+            assert torch.equal(a, b), (H, Wd)
+
+
+def _shortest_ms(torch, call, n=8):
+    """The shortest of seven timings of n calls, per call."""
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    best = np.inf
+    for _ in range(8):                      # (the first warms up: it is longer)
+        a.record()
+        for _ in range(n):
+            call()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) / n)
+    return best
+
+
+def test_render_of_one_row_costs_its_pixels(nsl, gpu):
+    """16384 pixels in one row or one column take at most twice the time of a
+    128x128 image (about as long; three times as long when every 4x4 block evaluated
+    the pixels it does not have)."""
+    import torch
+    f = nsl.Field(W.C1_FIELD)
+    P = _t(torch, gpu, params_for(W.C1_FIELD, f.layout, seed=1, table_range=0.2)[0])
+    pose = _t(torch, gpu, W.look_at_pose((1.5, 0.2, 0.1)).astype(np.float32).reshape(12))
+    cfg = nsl.render_config(0.5, 2.0 / 64, 64, 0.0)
+
+    def ms(H, Wd):
+        s = 0.9375 * max(H, Wd)
+        intr = _t(torch, gpu, np.array([s, s, Wd / 2, H / 2], np.float32))
+        ws = torch.empty(nsl.render_workspace_bytes(f, H, Wd, cfg), dtype=torch.uint8, device=gpu)
+        return _shortest_ms(torch, lambda: nsl.render(f, P, pose, intr, H, Wd, cfg, ws))
+
+    square = ms(128, 128)
+    assert ms(1, 16384) < 2.0 * square and ms(16384, 1) < 2.0 * square
