@@ -652,8 +652,8 @@ __device__ __forceinline__ void fp32_tile(const float* __restrict__ params, cons
 // of two P, a tile takes 16 / P consecutive samples of each, the waves share the
 // tiles of a pass of 16 / P rounds, and the rounds are composited in their order,
 // so that a pixel has the same bits whatever shares its workgroup.  At 64 samples
-// one pixel took 64 us at paper scale as 16 equal columns, 20 so; 19200 tiles of
-// one pixel 11.7 and 2.2 ms, 16384 pixels in one row 689 and 212 us.
+// one pixel took 64 us at paper scale as 16 equal columns, 20 so; 16384 pixels in
+// one row 689 and 212 us.
 //
 // The gathers bound it.  Samples of one ray are several cells apart at the
 // fine levels, so a tile of 16 samples of a ray touched four lines of the
@@ -698,8 +698,12 @@ struct Moments {
   }
 };
 
-// Workgroup -> pixels: with tiles, workgroup k takes the quarter k % 4 of tile
-// k / 4, 16 consecutive pixels; without, the workgroup takes block b of request
+// Workgroup -> pixels: with tiles, the workgroups 4 k .. 4 k + 3 take the quarters
+// of tile k, 16 consecutive pixels each, in an order that turns with k: workgroups
+// go round the XCDs and, within one, round its shader engines in a fixed order, so
+// that with quarter k % 4 in workgroup k, the first quarters of tiles of at most 16
+// pixels all met on a fourth of the CUs (1200 such tiles at paper scale 1.55 ms
+// instead of 0.72, 19200 of one pixel 2.2 instead of 0.70).  Without tiles, the workgroup takes block b of request
 // 0's image, 4x4 pixels (blocks_x blocks a row, nblocks in all).  The grid is
 // two-dimensional because the largest images have more threads than one
 // dimension of a launch may.
@@ -739,11 +743,12 @@ __global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(
     pix = jc & ((1 << lg) - 1);
   };
   if (tiles) {
-    const nsl_render_tile tile = tiles[blk / 4];
+    const uint32_t k = blk / 4, quarter = (blk - k / 2 - k / 8) & 3u;
+    const nsl_render_tile tile = tiles[k];
     req = tile.request;
     if (req < 0 || req >= n_req) return;
     const int npix = reqs[req].H * reqs[req].W;
-    const int first = max(tile.first_pixel, 0) + 16 * (int)(blk % 4);
+    const int first = max(tile.first_pixel, 0) + 16 * (int)quarter;
     const int last = min(tile.first_pixel + min(tile.n_pixels, NSL_RENDER_TILE), npix);
     if (first >= last) return;
     np = min(16, last - first);
