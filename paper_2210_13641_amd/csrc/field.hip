@@ -704,7 +704,7 @@ struct Moments {
 // that with quarter k % 4 in workgroup k, the first quarters of tiles of at most 16
 // pixels all met on a fourth of the CUs (1200 such tiles at paper scale 1.55 ms
 // instead of 0.72, 19200 of one pixel 2.2 instead of 0.70).  Without tiles, the workgroup takes block b of request
-// 0's image, 4x4 pixels (blocks_x blocks a row, nblocks in all).  The grid is
+// 0's image, side x side pixels (blocks_x blocks a row, nblocks in all).  The grid is
 // two-dimensional because the largest images have more threads than one
 // dimension of a launch may.
 //
@@ -718,7 +718,7 @@ struct Moments {
 template <class N>
 __global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(N::HD >= 64 ? 2 : 8))) void render_kernel(
     LevelInfo lv, Aabb box, WOffsets wo, const nsl_render_request* __restrict__ reqs, int n_req,
-    const nsl_render_tile* __restrict__ tiles, uint32_t nblocks, int blocks_x, RenderParams rp) {
+    const nsl_render_tile* __restrict__ tiles, uint32_t nblocks, int blocks_x, int side, RenderParams rp) {
   typedef typename std::conditional<kSplitNet<N>, __bf16, float>::type Op;
   constexpr int kOps = kSplitNet<N> ? 3 * Mixed<N>::FWD : N::FWD_FLOATS;
   __shared__ __attribute__((aligned(16))) Op Af[kOps];
@@ -760,14 +760,14 @@ __global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(
     // bands of four rows of blocks, down and then along each, so that the 64
     // consecutive blocks an XCD works at are 64x16 pixels: rows of blocks
     // instead took 4.08 ms against 3.98, and at 320x240 1.70 against 1.60
-    const int rows = (reqs[0].H + 3) / 4, band = 4 * ((int)blk / (4 * blocks_x)), high = min(4, rows - band);
+    const int rows = (reqs[0].H + side - 1) / side, band = 4 * ((int)blk / (4 * blocks_x)), high = min(4, rows - band);
     const int i = (int)blk - band * blocks_x, bx = i / high, by = band + i - bx * high;
-    const int w4 = min(4, reqs[0].W - 4 * bx);
-    np = w4 * min(4, reqs[0].H - 4 * by);
+    const int w4 = min(side, reqs[0].W - side * bx);
+    np = w4 * min(side, reqs[0].H - side * by);
     columns();
     const int at = min(pix, np - 1), y = w4 == 3 ? (at * 11) >> 5 : at >> (w4 / 2);  // at / w4
-    u = 4 * bx + at - y * w4;
-    v = 4 * by + y;
+    u = side * bx + at - y * w4;
+    v = side * by + y;
   }
   const nsl_render_request& rq = reqs[req];
   copy_to_lds<kRenderThreads, sizeof(Af)>(Af, rq.prepared);
@@ -999,17 +999,22 @@ static hipError_t launch_bwd(const FieldArgs& a, const SampleSrc& src, int nbloc
   return hipGetLastError();
 }
 
+// Images of at most this many 4x4 blocks, which leave half of the chip without a
+// workgroup or more, go by 2x2 blocks: at paper scale, 64 samples, 4x4 pixels
+// 27 us instead of 135, 16x16 37 instead of 124, 32x32 60 instead of 121.
+constexpr int kRenderFewBlocks = 128;
 template <class N>
 static hipError_t launch_render(const LevelInfo& lv, const Aabb& box, const WOffsets& wo,
                                 const nsl_render_request* reqs, int n_req, const nsl_render_tile* tiles, int n_tiles,
                                 int H, int W, const RenderParams& rp, hipStream_t st) {
   static_assert(NSL_RENDER_TILE == 64, "four groups of 16 pixels a tile");
-  const int64_t bx = ((int64_t)W + 3) / 4;
-  const int64_t nblocks = tiles ? (int64_t)n_tiles * 4 : bx * (((int64_t)H + 3) / 4);
+  auto across = [](int n, int side) { return ((int64_t)n + side - 1) / side; };
+  const int side = across(W, 4) * across(H, 4) <= kRenderFewBlocks ? 2 : 4;
+  const int64_t bx = across(W, side), nblocks = tiles ? (int64_t)n_tiles * 4 : bx * across(H, side);
   if (nblocks <= 0) return hipSuccess;
   const int64_t gx = std::min<int64_t>(nblocks, 1 << 20);
   hipLaunchKernelGGL(render_kernel<N>, dim3((unsigned)gx, (unsigned)((nblocks + gx - 1) / gx)),
-                     dim3(kRenderThreads), 0, st, lv, box, wo, reqs, n_req, tiles, (uint32_t)nblocks, (int)bx, rp);
+                     dim3(kRenderThreads), 0, st, lv, box, wo, reqs, n_req, tiles, (uint32_t)nblocks, (int)bx, side, rp);
   return hipGetLastError();
 }
 

@@ -523,3 +523,20 @@ def test_render_of_ragged_tiles_costs_their_pixels(nsl, gpu, spec):
 
     whole = ms(64)
     assert ms(16) < 2.0 * whole and ms(1) < 2.0 * whole
+
+
+def test_render_of_a_small_image_spreads_over_the_chip(nsl, gpu):
+    """4x4 pixels of the 64-wide network take at most three times as long as one
+    (1.3 times; 6.7 times as one group of 16, whose 64 tiles four waves share)."""
+    import torch
+    f = nsl.Field(W.C2_FIELD)
+    P = _t(torch, gpu, params_for(W.C2_FIELD, f.layout, seed=1, table_range=0.2)[0])
+    pose = _t(torch, gpu, W.look_at_pose((1.5, 0.2, 0.1)).astype(np.float32).reshape(12))
+    cfg = nsl.render_config(0.5, 2.0 / 64, 64, 0.0)
+
+    def ms(side):
+        intr = _t(torch, gpu, np.array([side, side, side / 2, side / 2], np.float32))
+        ws = torch.empty(nsl.render_workspace_bytes(f, side, side, cfg), dtype=torch.uint8, device=gpu)
+        return _shortest_ms(torch, lambda: nsl.render(f, P, pose, intr, side, side, cfg, ws))
+
+    assert ms(4) < 3.0 * ms(1)
