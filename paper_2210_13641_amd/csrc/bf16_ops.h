@@ -81,7 +81,7 @@ __device__ __forceinline__ bf8 lds_bf8(const __bf16* A, int block, int lane) {
 // why only the 64-wide networks take this route.
 //
 // A value that is not finite (or above the largest BF16) has no parts: its
-// outputs come out NaN, and the caller evaluates those tiles with FP32 products.
+// outputs come out NaN, and the caller evaluates those columns with FP32 products.
 // ---------------------------------------------------------------------------
 
 struct Split8 {
@@ -189,12 +189,12 @@ __device__ __forceinline__ void split_mlp(const __bf16* Af, int lane, const floa
   for (int t = 0; t < T; ++t) z[t] = r[t][0];
 }
 
-// Whether any output of the tile is not finite (wave-uniform).
-__device__ __forceinline__ bool any_not_finite(f4 o, f4 z) {
-  float c = 0.0f;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) c = fmaf(o[r], 0.0f, fmaf(z[r], 0.0f, c));
-  return __ballot(c != c) != 0ull;
+// Whether a column's density logit and colour logits (rows 0 .. 2 of z) are
+// finite.  Whatever in a column has no parts makes its next layer NaN and, since
+// relu_nan keeps them, one of these.
+__device__ __forceinline__ bool all_finite(float o0, f4 z) {
+  const float c = fmaf(o0, 0.0f, fmaf(z[0], 0.0f, fmaf(z[1], 0.0f, z[2] * 0.0f)));
+  return c == c;
 }
 
 }  // namespace nsl

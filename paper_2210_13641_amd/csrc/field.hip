@@ -589,7 +589,7 @@ __global__ __launch_bounds__(256) void render_prep_kernel(const float* __restric
 }
 
 // One tile with FP32 products, its weights from the parameter vector: for
-// tiles that split_mlp cannot represent (values that are not finite).  The
+// columns that split_mlp cannot represent (values that are not finite).  The
 // loops over a layer's tiles stay rolled: these tiles are rare, and the
 // registers are the fast path's.
 template <class N, int J>
@@ -814,9 +814,15 @@ __global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(
           const f4 sh[1] = {f4{shv[0], shv[1], shv[2], shv[3]}};
           f4 o1[1], z1[1];
           split_mlp<N, 1>(Af, lane, e, sh, o1, z1);
-          if (any_not_finite(o1[0], z1[0])) fp32_tile<N>(rq.params, wo, lane, e[0], sh[0], o1[0], z1[0]);
           oo = o1[0];
           zz = z1[0];
+          const bool bad = g == 0 && !all_finite(oo[0], zz);
+          if (__ballot(bad) != 0ull) {  // those columns alone: a pixel's bits do not depend on the others
+            f4 o2, z2;
+            fp32_tile<N>(rq.params, wo, lane, e[0], sh[0], o2, z2);
+            oo = bad ? o2 : oo;
+            zz = bad ? z2 : zz;
+          }
         } else {
           Acts<N> act;
           encode<N>(rq.params, lv.table_mask, ll, xn, act.e);

@@ -540,3 +540,39 @@ def test_render_of_a_small_image_spreads_over_the_chip(nsl, gpu):
         return _shortest_ms(torch, lambda: nsl.render(f, P, pose, intr, side, side, cfg, ws))
 
     assert ms(4) < 3.0 * ms(1)
+
+
+def test_render_beside_values_that_are_not_finite(nsl, gpu):
+    """Infinite entries of the 16-level field's table: the pixels whose rays stay
+    clear of their cells keep the bits of the render without them, those in a
+    4x4 block with a touched one included."""
+    import torch
+    from oracle import rays as orays
+    spec = W.C2_FIELD
+    f = nsl.Field(spec)
+    H, Wd, n = 160, 160, 12                              # 1600 blocks of 4x4
+    flat, _, _ = params_for(spec, f.layout, seed=9, table_range=2.0)
+    bad = flat.copy()
+    at = 2 * (f.layout["level_offset"][1] + 23 * 23 * 11 + 23 * 11 + 11)     # level 1: 22 cells an axis
+    bad[at - 2:at + 4] = np.inf                          # vertices x = 10, 11, 12 of y = z = 11
+    pose = W.look_at_pose((1.5, 0.2, 0.1)).astype(np.float32)
+    intr = np.array([150.0, 150.0, Wd / 2, H / 2], np.float32)
+    dt = np.float32(2.0 / n)
+    cfg = nsl.render_config(0.5, float(dt), n, 0.0)
+    ws = torch.empty(nsl.render_workspace_bytes(f, H, Wd, cfg), dtype=torch.uint8, device=gpu)
+    out = []
+    for p in (flat, bad):
+        op = torch.empty(H * Wd, device=gpu)
+        r = nsl.render(f, _t(torch, gpu, p), _t(torch, gpu, pose.reshape(12)), _t(torch, gpu, intr), H, Wd, cfg, ws,
+                       opacity=op)
+        out.append(np.concatenate([a.cpu().numpy().reshape(H * Wd, -1) for a in r], 1))
+    o32, d32, _ = orays.rays_fp32(pose[None], intr[None], np.arange(H * Wd, dtype=np.uint32), H, Wd)
+    t = np.float32(0.5) + (np.arange(n, dtype=np.float32) + np.float32(0.5)) * dt
+    cell = np.clip((o32[:, None] + t[None, :, None] * d32[:, None] + 1.0) * 0.5, 0, 1) * 22
+    lo, hi = np.array([9, 10, 10]), np.array([13, 12, 12])
+    near = ((cell > lo - 1e-3) & (cell < hi + 1e-3)).all(-1).any(-1)
+    inside = ((cell > lo + 1e-3) & (cell < hi - 1e-3)).all(-1).any(-1)
+    assert not np.isfinite(out[1][inside]).all(-1).any()
+    block = near.reshape(H // 4, 4, Wd // 4, 4).any((1, 3)).repeat(4, 0).repeat(4, 1).reshape(-1)
+    assert np.sum(block & ~near) > 100                   # clear pixels beside touched ones
+    assert np.array_equal(out[0][~near].view(np.int32), out[1][~near].view(np.int32))
