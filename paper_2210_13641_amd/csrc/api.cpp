@@ -101,7 +101,8 @@ struct nsl_field {
   WOffsets wo;
 };
 
-// Whether the encoding of the samples gets a launch of its own, level by level
+// Whether the encoding of a step's or a field backward's samples gets a launch of
+// its own, level by level
 // (each XCD's L2 then holds one level's slice of the table), also where the
 // caller keeps no room for it: it then waits in the space of the
 // table-gradient records (80 L bytes a sample, the encoding takes at most
@@ -109,8 +110,13 @@ struct nsl_field {
 // inside the MLP kernels, every XCD's L2 sees the whole table (24 or 49 MB),
 // and each wave waits on its own gathers: a mixed step of 60 007 samples took
 // 43 + 34 us in the MLP kernels and 18 us in the count and scans, against 45 us
-// for the same work and the encoding.  The tables of the 4-level field fit an
-// L2 and are gathered in place: a launch would cost more.
+// for the same work and the encoding.  Small calls do not lose by the launch: a
+// field backward of 64 samples took 74 (FP32) and 54 us (mixed) before these
+// kernels and takes 51 and 41, a mixed step of 16 candidates 92 and 73.  The
+// tables of the 4-level field fit an
+// L2 and are gathered in place: a launch would cost more.  (nsl_field_fwd gathers
+// in place for either: forwards on several streams may share a workspace, of which
+// it writes the weight operands alone.)
 static bool encodes_apart(const nsl_field* f) { return f->shape == kShapeFull; }
 
 struct nsl_mapper {
@@ -672,11 +678,6 @@ int nsl_field_fwd(const nsl_field* f, const float* params, const float* xn, cons
   if (rc) return rc;
   HIP_TRY(field_prep(f->shape, params, f->wo, w.wprep, st), "prep weights");
   FieldArgs fa{params, w.wprep, f->lv};
-  if (encodes_apart(f)) {
-    src.ecache = w.rec.sorted;
-    src.ecache_stride = S;
-    HIP_TRY(field_encode(f->shape, fa, src, S, nullptr, w.plan.bl, f->lay.table_floats / 2, st), "encoding");
-  }
   HIP_TRY(field_forward(f->shape, fa, src, S, sigma, rgb, st), "field forward");
   return NSL_OK;
 }

@@ -576,3 +576,30 @@ def test_render_beside_values_that_are_not_finite(nsl, gpu):
     block = near.reshape(H // 4, 4, Wd // 4, 4).any((1, 3)).repeat(4, 0).repeat(4, 1).reshape(-1)
     assert np.sum(block & ~near) > 100                   # clear pixels beside touched ones
     assert np.array_equal(out[0][~near].view(np.int32), out[1][~near].view(np.int32))
+
+
+@pytest.mark.parametrize("spec", [W.C1_FIELD, W.C2_FIELD], ids=["tiny", "full"])
+@pytest.mark.parametrize("S", [1, 4097, 19999, 20000, 40001])
+def test_field_forward_leaves_the_records_alone(nsl, gpu, spec, S):
+    """nsl_field_fwd and Field.fwd write the weight operands of their workspace
+    and nothing behind them, where a backward on another stream may hold its
+    encoding or records; and both give the bits of calls of fewer samples, around
+    the count from which Field.fwd encodes apart."""
+    import torch
+    f = nsl.Field(spec)
+    flat, _, _ = params_for(spec, f.layout, seed=12, table_range=0.5)
+    P = _t(torch, gpu, flat)
+    rng = np.random.default_rng(S)
+    X = _t(torch, gpu, rng.uniform(-0.01, 1.01, size=(S, 3)).astype(np.float32))
+    d = rng.normal(size=(S, 3))
+    D = _t(torch, gpu, (d / np.linalg.norm(d, axis=1, keepdims=True)).astype(np.float32))
+    ws = torch.full((f.workspace_bytes(S),), 0xA5, dtype=torch.uint8, device=gpu)
+    sg, rgb = f.fwd(P, X, D, ws)
+    sg2, rgb2 = torch.empty_like(sg), torch.empty_like(rgb)
+    assert nsl._lib.nsl_field_fwd(f.handle, P.data_ptr(), X.data_ptr(), D.data_ptr(), S, sg2.data_ptr(),
+                                  rgb2.data_ptr(), ws.data_ptr(), ws.numel(), nsl._stream()) == 0
+    assert bool((ws[nsl.prepared_bytes(f):] == 0xA5).all())
+    assert torch.equal(sg, sg2) and torch.equal(rgb, rgb2)
+    for lo in range(0, S, 16384):
+        a, b = f.fwd(P, X[lo:lo + 16384].contiguous(), D[lo:lo + 16384].contiguous(), ws)
+        assert torch.equal(sg[lo:lo + 16384], a) and torch.equal(rgb[lo:lo + 16384], b)
