@@ -294,7 +294,8 @@ int nsl_profile_read(double* ms, int* n_steps);
 
 /* Rays and samples of the step for the given candidates (the sampler of
  * nsl_train_step).  Outputs (device): counts[n_candidates] samples per
- * candidate before the cut, offsets[n_candidates+1] exclusive prefix,
+ * candidate before the cut, offsets[n_candidates+1] exclusive prefix (from
+ * 2^32 - 2^26 on not exact, but never below that),
  * t[max_samples] and ray[max_samples] (candidate index of each sample) for
  * the kept candidates, stats (device).  Workspace: nsl_step_workspace_bytes. */
 int nsl_march(nsl_mapper* m, const nsl_field* f, const nsl_step_config* cfg,

@@ -1,7 +1,8 @@
 // Rays, samples and the batch cut of the mapping step on gfx950.
 //
 // The first pass sets up every candidate ray and counts its samples (one
-// wave a ray, march_common.h), a scan turns counts into offsets and applies
+// wave a ray with the occupancy sampler, one thread a ray with the uniform one;
+// march_common.h), a scan turns counts into offsets and applies
 // the batch cut, the second pass writes the samples.  Up to kEmitScanMax
 // candidates the second pass does the scan itself (each workgroup the prefix
 // before its candidates, one more workgroup the statistics), else a
@@ -21,6 +22,12 @@ __global__ __launch_bounds__(256) void rays_count_kernel(KeyframeStore kf, March
 }
 
 constexpr int kScanThreads = 1024, kScanRays = 8;
+// Offsets stop here: candidates times samples a ray may reach 2^32 (2^20 of 4096),
+// and an offset that wrapped would be below max_samples again, with its samples
+// over those of the kept candidates.  A segment's counts (8192 of at most 4096)
+// and a ray's samples still fit above it.
+constexpr uint32_t kMaxOffset = 0xFFFFFFFFu - (1u << 26);
+static_assert((int64_t)kScanRays * kScanThreads * 4096 < (1 << 26), "a segment fits");
 
 // Single-block exclusive scan of the counts, batch cut and statistics, over
 // segments of kScanRays * kScanThreads rays: each thread loads kScanRays
@@ -35,6 +42,8 @@ __global__ __launch_bounds__(kScanThreads) void scan_cut_kernel(RayBuffers rb, i
   constexpr int Q = kScanRays / 4;
   const int tid = threadIdx.x, wave = tid / kWave;
   uint32_t carry = 0, nr = 0, nk = 0, nm = 0, smax = 0;
+  // a caller's arrays may not be
+  const bool aligned = (((uintptr_t)rb.offsets | (uintptr_t)rb.counts) & 15u) == 0;
   struct Rays {
     uint32_t count[kScanRays];
     float prec[kScanRays];
@@ -45,13 +54,14 @@ __global__ __launch_bounds__(kScanThreads) void scan_cut_kernel(RayBuffers rb, i
       const int64_t i = i0 + 4 * q;
       uint4 c = make_uint4(0u, 0u, 0u, 0u);
       float4 p = make_float4(1.0f, 1.0f, 1.0f, 1.0f);
-      if (i + 4 <= n) {
+      if (aligned && i + 4 <= n) {
         c = *reinterpret_cast<const uint4*>(rb.counts + i);
         p = *reinterpret_cast<const float4*>(rb.prec + i);
       } else {
         if (i < n) c.x = rb.counts[i], p.x = rb.prec[i];
         if (i + 1 < n) c.y = rb.counts[i + 1], p.y = rb.prec[i + 1];
         if (i + 2 < n) c.z = rb.counts[i + 2], p.z = rb.prec[i + 2];
+        if (i + 3 < n) c.w = rb.counts[i + 3], p.w = rb.prec[i + 3];
       }
       const uint32_t c4[4] = {c.x, c.y, c.z, c.w};
       const float p4[4] = {p.x, p.y, p.z, p.w};
@@ -63,7 +73,6 @@ __global__ __launch_bounds__(kScanThreads) void scan_cut_kernel(RayBuffers rb, i
     }
   };
   constexpr int kSegment = kScanRays * kScanThreads;
-  const bool aligned = ((uintptr_t)rb.offsets & 15u) == 0;  // a caller's array may not be
   Rays next;
   fetch((int64_t)kScanRays * tid, next);
   for (int64_t seg = 0; seg < n; seg += kSegment) {
@@ -88,7 +97,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_cut_kernel(RayBuffers rb, i
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const int j = 4 * q + k;
-        off[k] = run;
+        off[k] = min(run, kMaxOffset);
         run += r.count[j];
         if (i0 + j < n && run <= (uint32_t)max_samples) {
           ++nk;
@@ -108,7 +117,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_cut_kernel(RayBuffers rb, i
           if (i + k < n) rb.offsets[i + k] = off[k];
       }
     }
-    carry += total;
+    carry = min(carry + total, kMaxOffset);
     __syncthreads();
   }
   if (tid == 0) rb.offsets[n] = carry;

@@ -1,8 +1,9 @@
 // Ray setup and occupancy marching of one candidate pixel ray, shared by the
-// march kernels and the mixed-precision step's preparation launch (which
-// counts the samples of every candidate beside its table conversion).
+// march kernels and the steps' preparation launches (which count the samples of
+// every candidate beside their other work).
 //
-// One wave owns one candidate pixel ray.  For the occupancy sampler the 64
+// With the uniform sampler a thread sets up a ray.  With the occupancy sampler a
+// wave owns one candidate pixel ray: its 64
 // lanes test 64 consecutive lattice points t_k = (k+1/2) dt at a time
 // (AABB membership and the cell's occupancy bit), and a ballot compacts the
 // kept ones; the lattice range is first narrowed to the ray's AABB chord

@@ -603,3 +603,37 @@ def test_field_forward_leaves_the_records_alone(nsl, gpu, spec, S):
     for lo in range(0, S, 16384):
         a, b = f.fwd(P, X[lo:lo + 16384].contiguous(), D[lo:lo + 16384].contiguous(), ws)
         assert torch.equal(sg[lo:lo + 16384], a) and torch.equal(rgb[lo:lo + 16384], b)
+
+
+@pytest.mark.parametrize("n,n_uniform,shift", [(16386, 32, 1), (40003, 32, 2), (24576, 32, 3), (1 << 20, 4096, 0),
+                                               ((1 << 20) + 70001, 4096, 1)])
+def test_march_scan_of_any_counts(nsl, gpu, n, n_uniform, shift):
+    """nsl_march with the caller's counts at any 4-byte address, and with 2^32
+    samples and more before the cut: a wrapped offset would start over below
+    max_samples.  Every candidate's offset is the exact prefix as far as 32 bits
+    less 2^26 go, and the kept ones are a prefix."""
+    import torch
+    from parity import upload_keyframes
+    f = nsl.Field(W.C1_FIELD)
+    m = upload_keyframes(nsl, torch, W.c1_keyframes(), gpu)
+    ids = np.random.default_rng(n).integers(0, 1100 if n < 1 << 20 else 1024, size=n).astype(np.uint32)
+    cfg = nsl.step_config(dataclasses.replace(W.C1_SAMPLER, n_uniform=n_uniform, max_samples=70000))
+    ws = torch.empty(nsl.step_workspace_bytes(f, cfg, n), dtype=torch.uint8, device=gpu)
+    counts = torch.zeros(n + shift, dtype=torch.int32, device=gpu)[shift:]
+    offs = torch.zeros(n + 1, dtype=torch.int32, device=gpu)
+    t = torch.zeros(cfg.max_samples, dtype=torch.float32, device=gpu)
+    ray = torch.full((cfg.max_samples,), -1, dtype=torch.int32, device=gpu)
+    stats = torch.zeros(4, dtype=torch.int32, device=gpu)
+    nsl.march(m, f, cfg, _t(torch, gpu, ids.view(np.int32)), ws, counts, offs, t, ray, stats)
+    want = np.where(ids < 1024, n_uniform, 0).astype(np.int64)
+    ends = np.cumsum(want)
+    kept = ends <= cfg.max_samples
+    cap = 2 ** 32 - 1 - 2 ** 26
+    assert np.array_equal(counts.cpu().numpy(), want)
+    assert np.array_equal(offs.cpu().numpy().view(np.uint32), np.minimum(np.concatenate([[0], ends]), cap))
+    got = stats.cpu().numpy()
+    assert got[:3].tolist() == [int(np.sum(kept & (want > 0))), int(ends[kept].max()), int(kept.sum())]
+    own = ray.cpu().numpy()
+    assert np.array_equal(own[:got[1]], np.repeat(np.arange(n), want)[:got[1]] if n < 1 << 20 else
+                          np.arange(got[1]) // n_uniform)
+    assert np.all(own[got[1]:] == -1)
