@@ -199,7 +199,6 @@ __device__ __forceinline__ void fwd_tile_out(const float* Af, int lane, int g, i
 // encoding a wave fetches its next tile's inputs while it computes the
 // current one (ray indices two tiles ahead).
 constexpr int kFieldFwdGrid = 768;
-constexpr bool kFieldFwdPrefetch = true;
 
 // Workgroups past the MLP's (bp.nbins of them) run the table-gradient column
 // scan (bins.h), which needs only the record counts of the encoding.
@@ -221,7 +220,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
   const int first = blockIdx.x * (blockDim.x / kWave) + (threadIdx.x / kWave);
   const int step = G * (blockDim.x / kWave);
   if (first >= ntiles) return;
-  if (kFieldFwdPrefetch && src.ecache) {
+  if (src.ecache) {
     auto rid = [&](int s) -> uint32_t { return src.t && s < S ? src.ray[s] : 0u; };
     float e[N::NSLOT], d[3];
     const int s0 = 16 * first + jc;
@@ -250,10 +249,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void f
       Acts<N> act;
       float xn[3] = {0.5f, 0.5f, 0.5f}, d[3] = {0.0f, 0.0f, 1.0f};
       if (valid) load_sample(src, s, xn, d);
-      if (src.ecache)
-        read_encoding<N>(static_cast<const float2*>(src.ecache), src.ecache_stride, g, s, valid, act.e);
-      else
-        encode<N>(a.table, a.lv.table_mask, ll, xn, act.e);
+      encode<N>(a.table, a.lv.table_mask, ll, xn, act.e);
       fwd_tile_out<N>(Af, lane, g, s, valid, act, d, sigma_out, rgb_out);
     }
   }
@@ -391,7 +387,7 @@ __global__ __launch_bounds__(kFieldBwdWaves * kWave, 2) void field_bwd_kernel(Fi
   const float *Xs = stage, *Ys = stage + N::XROWS * kBwdRow;
   float *Xw = stage + 16 * w + jc, *Yw = Xw + N::XROWS * kBwdRow;  // this lane's column
   LaneLevels<N> ll;
-  lane_levels<N>(a.lv, g, ll);
+  if constexpr (kGathers<N>) lane_levels<N>(a.lv, g, ll);
   OwnedDW<N, 0> dw0;
   OwnedDW<N, 1> dw1;
   OwnedDW<N, 2> dw2;
@@ -417,7 +413,8 @@ __global__ __launch_bounds__(kFieldBwdWaves * kWave, 2) void field_bwd_kernel(Fi
   const uint32_t stride = kBwdStep * gridDim.x;  // samples
   In in;
   uint32_t rid1 = 0u;
-  if (src.ecache) {
+  const bool given = src.ecache;  // (with the larger networks always)
+  if (given) {
     const uint32_t s0 = kBwdStep * blockIdx.x + 16 * w + jc;
     fetch_kept<N>(src, g, s0, s0 < S, rid(s0), in.e, in.d);
     seeds(s0, in);
@@ -428,12 +425,12 @@ __global__ __launch_bounds__(kFieldBwdWaves * kWave, 2) void field_bwd_kernel(Fi
     const bool valid = s < S;
     const int nt = (int)min((uint32_t)kFieldBwdWaves, (S - p + 15) / 16);  // tiles of 16 samples in this step
     In next;
-    if (src.ecache) {
+    if (given) {
       const uint32_t s1 = s + stride;
       fetch_kept<N>(src, g, s1, s1 < S, rid1, next.e, next.d);
       seeds(s1, next);
       rid1 = rid(s1 + stride);
-    } else {
+    } else if constexpr (kGathers<N>) {
       float xn[3] = {0.5f, 0.5f, 0.5f};
       in.d[0] = in.d[1] = 0.0f;
       in.d[2] = 1.0f;
@@ -445,6 +442,8 @@ __global__ __launch_bounds__(kFieldBwdWaves * kWave, 2) void field_bwd_kernel(Fi
       }
       seeds(s, in);
       next = in;
+    } else {
+      next = in;  // (never: but without a branch here the loop took 151 us instead of 147 at 262144 samples)
     }
     Acts<N> act;
 #pragma unroll
@@ -1000,6 +999,7 @@ template <class N>
 static hipError_t launch_bwd(const FieldArgs& a, const SampleSrc& src, int nblocks,
                              const float* dsigma, const float* drgb, const RecordBuffers& rec,
                              float* partial, const WOffsets& wo, float* grads, hipStream_t st) {
+  if (!kGathers<N> && !src.ecache) return hipErrorInvalidValue;
   hipLaunchKernelGGL(field_bwd_kernel<N>, dim3(nblocks), dim3(kFieldBwdWaves * kWave), 0, st, a, src, dsigma, drgb,
                      rec, partial);
   return hipGetLastError();

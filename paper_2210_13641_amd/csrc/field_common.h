@@ -46,6 +46,11 @@ __device__ __forceinline__ void load_sample(const SampleSrc& src, int s, float x
   load_direction(src, s, d);
 }
 
+// Networks whose tables fit an L2: the four-level ones.  Their backward may
+// gather the encoding itself; the larger ones' is always given it.
+template <class N>
+constexpr bool kGathers = N::LPL == 1;
+
 // Per-lane level constants (levels g, g+4, ... of this lane group).
 template <class N>
 struct LaneLevels {
@@ -469,21 +474,6 @@ __device__ __forceinline__ f4 relu4(f4 v) {
 __device__ __forceinline__ void wave_lds_fence() {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __builtin_amdgcn_wave_barrier();
-}
-
-// Inclusive prefix sum within each 16-lane row.
-__device__ __forceinline__ float row_incl_scan(float v) {
-  v += __int_as_float(row_from_below<1>(__float_as_int(v)));
-  v += __int_as_float(row_from_below<2>(__float_as_int(v)));
-  v += __int_as_float(row_from_below<4>(__float_as_int(v)));
-  v += __int_as_float(row_from_below<8>(__float_as_int(v)));
-  return v;
-}
-
-__device__ __forceinline__ float row_sum(float v) {
-#pragma unroll
-  for (int o = 1; o < 16; o <<= 1) v += __shfl_xor(v, o, 16);
-  return v;
 }
 
 // LDS scratch of the sums below (floats), passed in by the kernel, which may

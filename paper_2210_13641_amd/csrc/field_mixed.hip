@@ -329,10 +329,6 @@ __device__ __forceinline__ void tile_operands(const TileIn<N>& in, int g, PActs<
 // transpose 4 x 16 values a 16-lane row.
 // ---------------------------------------------------------------------------
 constexpr int kBwdWaves = 16;
-// Networks whose tables fit an L2: the four-level ones.  Their backward may
-// gather the encoding itself; the larger ones' is always given it.
-template <class N>
-constexpr bool kGathers = N::LPL == 1;
 constexpr int kStepSamples = 16 * kBwdWaves;  // samples of a workgroup step
 
 // Staging groups: the layers whose weight-gradient products follow one
