@@ -637,3 +637,144 @@ def test_march_scan_of_any_counts(nsl, gpu, n, n_uniform, shift):
     assert np.array_equal(own[:got[1]], np.repeat(np.arange(n), want)[:got[1]] if n < 1 << 20 else
                           np.arange(got[1]) // n_uniform)
     assert np.all(own[got[1]:] == -1)
+
+
+# four levels whose table does not fit LDS in FP16 either, the last one of several bins
+WIDE_TABLES = dataclasses.replace(W.C1_FIELD, log2_table=15)
+
+
+def _same_step(a, b, nt):
+    """Two steps with the same encoding: the same bits but for the order of the
+    table-gradient sums."""
+    assert np.array_equal(a["stats"], b["stats"]) and np.array_equal(a["loss"], b["loss"])
+    assert np.array_equal(a["rays"], b["rays"])
+    assert np.array_equal(a["grads"][nt:], b["grads"][nt:])
+    ga, gb = a["grads"][:nt].astype(np.float64), b["grads"][:nt].astype(np.float64)
+    assert np.count_nonzero(ga) > 0.1 * nt
+    assert np.allclose(ga, gb, rtol=1e-5, atol=1e-6 * np.abs(ga).max())
+
+
+@pytest.mark.parametrize("mixed", [False, True], ids=["fp32", "mixed"])
+@pytest.mark.parametrize("spec", [W.C1_FIELD, MID_TABLES, WIDE_TABLES], ids=["in-lds", "fp16-in-lds", "in-memory"])
+def test_step_of_four_levels_with_and_without_kept_encoding(nsl, gpu, spec, mixed):
+    """The 4-level field gathers its table in the network's kernels, or with the
+    encoding kept in a launch before them (from LDS, or level by level, which also
+    counts the table-gradient records): the same step either way."""
+    import torch
+    from test_gpu_parity import _step_gpu
+    f = nsl.Field(spec)
+    flat, _, _ = params_for(spec, f.layout, seed=13, table_range=0.3)
+    kf, ids = W.c1_keyframes(), W.c1_pixels()
+    a, b = [_step_gpu(nsl, torch, gpu, spec, W.C1_SAMPLER, kf, ids, flat, keep_encoding=k, mixed=mixed)
+            for k in (False, True)]
+    _same_step(a, b, f.layout["table_floats"])
+
+
+SMALL_SCENE = dataclasses.replace(SMALL_TABLES, aabb_min=(-2.0,) * 3, aabb_max=(2.0,) * 3)
+
+
+@pytest.mark.parametrize("keep", [False, True], ids=["shared", "kept"])
+def test_step_of_sixteen_single_bin_levels(nsl, gpu, keep):
+    """A step of 16 levels that each fit one bin, whose encoding (not kept) and
+    sums over the parts of the samples lie in one region in turn: loss, outputs,
+    table and weight gradients against the oracle at 1e-5; in mixed precision the
+    same step with the encoding in that region and in its own."""
+    import torch
+    from test_gpu_parity import _compare_step, _step_gpu
+    spec, kf, ids = SMALL_SCENE, W.c1_keyframes(), W.c1_pixels()
+    f = nsl.Field(spec)
+    flat, t64, w64 = params_for(spec, f.layout, seed=14, table_range=0.2)
+    g = _step_gpu(nsl, torch, gpu, spec, W.C1_SAMPLER, kf, ids, flat, keep_encoding=keep)
+    _compare_step(spec, g, ostep.train_step(spec, W.C1_SAMPLER, kf, t64, w64, ids), f.layout, tol=1e-5)
+    if keep:
+        a, b = [_step_gpu(nsl, torch, gpu, spec, W.C1_SAMPLER, kf, ids, flat, keep_encoding=k, mixed=True)
+                for k in (False, True)]
+        _same_step(a, b, f.layout["table_floats"])
+
+
+@pytest.mark.parametrize("S", [16, 700, 20001])
+def test_field_backward_of_sixteen_single_bin_levels(nsl, gpu, S):
+    """nsl_field_bwd (1e-5) and nsl_field_bwd_mixed (2e-2) of the same field against
+    the oracle: the counting sort (too few samples for a part), one part and several."""
+    import torch
+    spec = SMALL_SCENE
+    f = nsl.Field(spec)
+    flat, t64, w64 = params_for(spec, f.layout, seed=15, table_range=0.5)
+    rng = np.random.default_rng(S)
+    xn = rng.uniform(size=(S, 3)).astype(np.float32)
+    d = rng.normal(size=(S, 3))
+    d = (d / np.linalg.norm(d, axis=1, keepdims=True)).astype(np.float32)
+    dsig, drgb = rng.normal(size=S).astype(np.float32), rng.normal(size=(S, 3)).astype(np.float32)
+    P = _t(torch, gpu, flat)
+    args = [_t(torch, gpu, a) for a in (xn, d, dsig, drgb)]
+    ws = torch.empty(f.workspace_bytes(S), dtype=torch.uint8, device=gpu)
+    e, em, corners = ofield.encode_fwd(spec, t64, xn)
+    sh = ofield.sh_basis(d.astype(np.float64), spec.sh_bands)
+    for mixed, tol in ((False, 1e-5), (True, 2e-2)):
+        G = torch.zeros(f.layout["total"], device=gpu)
+        f.bwd_mixed(f.prepare_mixed(P), *args, G, ws) if mixed else f.bwd(P, *args, G, ws)
+        cache = ofield.mlp_fwd(spec, w64, e, em, sh, band=tol)
+        ds64, dc64 = dsig.astype(np.float64), drgb.astype(np.float64)
+        dWs, dWm, de, dem = ofield.mlp_bwd(spec, w64, cache, ds64, np.abs(ds64), dc64, np.abs(dc64), band_tol=tol)
+        gt, gtm = ofield.encode_bwd(spec, corners, de, dem, f.layout["table_floats"])
+        tab, gws = split_grads(G.cpu().numpy(), f.layout, spec)
+        check_mag(f"small 16-level table gradient {mixed}", tab, gt, gtm, tol)
+        for j, (a, b, m) in enumerate(zip(gws, dWs, dWm)):
+            check_mag(f"small 16-level grad W{j} {mixed}", a, b, m, tol)
+
+
+@pytest.mark.parametrize("log2_table", [19, 21])
+@pytest.mark.parametrize("S", [255, 20001])
+def test_field_backward_counts_as_the_layers_do(nsl, gpu, S, log2_table):
+    """nsl_field_bwd of the 16-level field, whose encoding counts the
+    table-gradient records (2^19 entries a level; 2^21 are too many bins),
+    against nsl_encode_fwd, nsl_mlp_bwd and nsl_encode_bwd, which counts them in a
+    pass of its own: the weight gradients bit for bit, the table's up to the order
+    of its sums."""
+    import torch
+    spec = dataclasses.replace(W.C2_FIELD, log2_table=log2_table)
+    f = nsl.Field(spec)
+    nt = f.layout["table_floats"]
+    rng = np.random.default_rng(S)
+    P = _t(torch, gpu, params_for(spec, f.layout, seed=16, table_range=0.5)[0])
+    o, step = rng.uniform(0.2, 0.8, size=(S // 32 + 1, 1, 3)), rng.normal(size=(S // 32 + 1, 1, 3)) * 0.003
+    xn = (o + step * np.arange(32)[:, None]).clip(0, 1).reshape(-1, 3)[:S]       # samples along rays share cells
+    d = rng.normal(size=(S, 3))
+    X, D = _t(torch, gpu, xn.astype(np.float32)), _t(torch, gpu, (d / np.linalg.norm(d, axis=1, keepdims=True)).astype(np.float32))
+    ds, dc = _t(torch, gpu, rng.normal(size=S).astype(np.float32)), _t(torch, gpu, rng.normal(size=(S, 3)).astype(np.float32))
+    ws = torch.empty(f.workspace_bytes(S), dtype=torch.uint8, device=gpu)
+    a, b = torch.zeros_like(P), torch.zeros_like(P)
+    f.bwd(P, X, D, ds, dc, a, ws)
+    nsl.encode_bwd(f, X, nsl.mlp_bwd(f, P, nsl.encode_fwd(f, P, X), D, ds, dc, b, ws), b)
+    assert torch.equal(a[nt:], b[nt:])
+    ga, gb = a[:nt].cpu().numpy().astype(np.float64), b[:nt].cpu().numpy().astype(np.float64)
+    assert np.array_equal(ga != 0, gb != 0) and np.count_nonzero(ga) > 0
+    assert np.allclose(ga, gb, rtol=1e-5, atol=1e-6 * np.abs(ga).max())
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("n_uniform", [32, 33])
+def test_step_keeps_bad_densities_to_their_rays(nsl, gpu, bad, n_uniform):
+    """A vertex of the tiny field's table that is not finite, in the compositing
+    of two rays a wave (32 samples) and of one (33): the outputs of the rays clear
+    of its cells keep their bits, beside touched rays in the same wave."""
+    import torch
+    from oracle import rays as orays
+    from test_gpu_parity import _step_gpu
+    spec, kf, ids = W.C1_FIELD, W.c1_keyframes(), W.c1_pixels()
+    sampler = dataclasses.replace(W.C1_SAMPLER, n_uniform=n_uniform, dt=2.0 / n_uniform)
+    f = nsl.Field(spec)
+    flat, _, _ = params_for(spec, f.layout, seed=17, table_range=0.3)
+    hurt = flat.copy()
+    at = 2 * (f.layout["level_offset"][1] + (4 * 9 + 4) * 9 + 4)          # level 1: 8 cells an axis
+    hurt[at:at + 2] = bad
+    a, b = [_step_gpu(nsl, torch, gpu, spec, sampler, kf, ids, p)["rays"] for p in (flat, hurt)]
+    o32, d32, _ = orays.rays_fp32(kf.pose, kf.intr, ids, 32, 32)
+    t = orays.uniform_t(sampler)
+    cell = np.clip((o32[:, None] + t[None, :, None] * d32[:, None] + 2.0) / 4.0, 0, 1) * 8
+    near = ((cell > 3 - 1e-3) & (cell < 5 + 1e-3)).all(-1).any(-1)
+    inside = ((cell > 3 + 1e-3) & (cell < 5 - 1e-3)).all(-1).any(-1)
+    assert inside.any() and np.sum(near.reshape(-1, 2).any(1) & ~near.reshape(-1, 2).all(1)) > 0   # pairs of one each
+    if not np.isnan(bad):                                # (the network's ReLU makes a NaN zero)
+        assert not np.isfinite(b[inside]).all(1).any()
+    assert np.array_equal(a[~near].view(np.int32), b[~near].view(np.int32))
