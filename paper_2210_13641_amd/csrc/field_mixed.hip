@@ -706,10 +706,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void m
 // loads take in.  From kWalkMin samples on it is the faster one: a call of 100003
 // random samples 86.6 -> 71.5 us (the kernel 71.4 -> 64.8), 200000 160 -> 140, 40000
 // 39.1 -> 33.9, but 20000 25.9 -> 27.2 and 5000 13.9 -> 20.3, since a wave then
-// waits for 16 levels in turn.
+// waits for 16 levels in turn.  And with tables of more than an L2's 4 MB: of
+// 100003 samples along rays, levels of 2^17 entries take 51 us either way, of 2^18 61.7 -> 57.4,
+// but of 2^16 32.4 -> 41.7 and of 2^10 18.7 -> 29.4 (random samples: 2^16 40 -> 46,
+// 2^10 18.6 -> 29.9).
 // (Two or four waves a workgroup, or two or four levels' loads in flight, were
 // slower up to 100000.)
 constexpr int kWalkMin = 32768;
+constexpr int64_t kWalkTable = 4 << 20;
 template <class N>
 __global__ __launch_bounds__(kWave) void mixed_fwd_walk_kernel(
     LevelInfo lv, const _Float16* __restrict__ table, const __bf16* __restrict__ prep, SampleSrc src,
@@ -803,7 +807,10 @@ static hipError_t fwd_impl(const LevelInfo& lv, const void* shadow, const Sample
   const BinPrep none{};
   const BinPrep& b = bp ? *bp : none;
   if constexpr (!kGathers<N>) {
-    if (!src.ecache && b.nbins == 0 && max_samples >= kWalkMin) {
+    const int last = lv.levels - 1;
+    const int64_t m = lv.res[last] + 1;  // (the last level's entries: of a dense one its vertices)
+    const int64_t entries = lv.offset[last] + ((lv.dense_bits >> last) & 1u ? m * m * m : (int64_t)lv.table_mask + 1);
+    if (!src.ecache && b.nbins == 0 && max_samples >= kWalkMin && entries * 4 > kWalkTable) {
       hipLaunchKernelGGL(mixed_fwd_walk_kernel<N>, dim3(min(1 << 20, (max_samples - 1) / kWave + 1)), dim3(kWave), 0, st,
                          lv, t16, ops, src, sigma, rgb);
       return hipGetLastError();
