@@ -374,9 +374,11 @@ __global__ __launch_bounds__(256) void encode_levels_kernel(LevelInfo lv, const 
 // wave's 64 random reads take about a tenth of what the vector memory path
 // takes for them.  It holds for tables of up to kLdsTable bytes, which leave room
 // for two workgroups a CU.  The tiny field (9046 entries) at 2^20 samples: FP16
-// 42 -> 18 us, FP32 49 -> 20 us; up to 131072 samples either way takes no
-// longer than the launch.
+// 42 -> 18 us, FP32 49 -> 20 us, 131072 samples 7.3 -> 5.8 and 8.0 -> 6.2; from
+// kLdsSamples on, since the copy is a latency of its own: 65536 samples 5.6 and 5.7
+// us either way, 8192 samples 4.5 -> 5.4 and 4.6 -> 5.8.
 constexpr size_t kLdsTable = 80 * 1024;
+constexpr int kLdsSamples = 98304;
 constexpr int kLdsTableThreads = 512;
 template <class N, class T, class E>
 __global__ __launch_bounds__(kLdsTableThreads) void encode_lds_kernel(LevelInfo lv, const T* __restrict__ table,
@@ -384,6 +386,8 @@ __global__ __launch_bounds__(kLdsTableThreads) void encode_lds_kernel(LevelInfo 
                                                                       int entries) {
   typedef T T2 __attribute__((ext_vector_type(2)));
   extern __shared__ __attribute__((aligned(16))) char encode_lds[];
+  const int S = src.n_dev ? (int)*src.n_dev : src.n;
+  if ((int64_t)blockIdx.x * kLdsTableThreads >= S) return;  // (the grid is that of the largest batch)
   T2* dst = reinterpret_cast<T2*>(encode_lds);
   const T2* from = reinterpret_cast<const T2*>(table);
   constexpr int kBatch = 8;  // loads of a thread in flight
@@ -398,7 +402,6 @@ __global__ __launch_bounds__(kLdsTableThreads) void encode_lds_kernel(LevelInfo 
     }
   }
   __syncthreads();
-  const int S = src.n_dev ? (int)*src.n_dev : src.n;
   for (int64_t i = (int64_t)blockIdx.x * kLdsTableThreads + threadIdx.x; i < S;
        i += (int64_t)gridDim.x * kLdsTableThreads) {
     const int s = (int)i;
@@ -421,7 +424,7 @@ __host__ inline hipError_t launch_encode(const LevelInfo& lv, const T* table, co
   if (max_samples <= 0) return hipSuccess;
   const size_t bytes = (size_t)entries * 2 * sizeof(T);
   if constexpr (N::L <= 4) {
-    if (!hist && bytes > 0 && bytes <= kLdsTable) {
+    if (!hist && bytes > 0 && bytes <= kLdsTable && max_samples >= kLdsSamples) {
       const int fit = 256 * std::min(4, (int)(160 * 1024 / bytes));  // resident workgroups
       const int grid = std::min(fit, (max_samples - 1) / kLdsTableThreads + 1);
       hipLaunchKernelGGL((encode_lds_kernel<N, T, E>), dim3(grid), dim3(kLdsTableThreads), bytes, st, lv, table, src,

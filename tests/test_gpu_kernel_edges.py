@@ -821,3 +821,21 @@ def test_mixed_forward_around_the_level_walk(nsl, gpu, log2_table):
     if log2_table == 10:
         g, big = field(19)
         assert _shortest_ms(torch, lambda: f.fwd_mixed(sh, X, D)) < _shortest_ms(torch, lambda: g.fwd_mixed(big, X, D)) / 3
+
+
+@pytest.mark.parametrize("spec", [W.C1_FIELD, MID_TABLES], ids=["in-lds", "fp16-in-lds"])
+@pytest.mark.parametrize("S", [98303, 98304, 98305, 98816, 131071])
+def test_encode_around_the_copy_to_lds(nsl, gpu, spec, S):
+    """nsl_encode_fwd and nsl_encode_fwd_mixed around the sample count from which
+    a small table is copied to LDS, and around its 512 samples a workgroup: the bits of
+    calls of fewer samples, which read it from memory."""
+    import torch
+    f = nsl.Field(spec)
+    P = _t(torch, gpu, params_for(spec, f.layout, seed=10, table_range=0.5)[0])
+    sh = f.prepare_mixed(P)
+    X = torch.rand(S, 3, device=gpu) * 1.04 - 0.02
+    a, b = nsl.encode_fwd(f, P, X), nsl.encode_fwd_mixed(f, sh, X)
+    for lo in range(0, S, 65000):
+        x = X[lo:lo + 65000].contiguous()
+        assert torch.equal(a[:, lo:lo + 65000], nsl.encode_fwd(f, P, x))
+        assert torch.equal(b[:, lo:lo + 65000], nsl.encode_fwd_mixed(f, sh, x))
