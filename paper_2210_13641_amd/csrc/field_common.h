@@ -225,12 +225,12 @@ __device__ __forceinline__ void read_encoding(const E* __restrict__ ec, int stri
 // 77 us instead of 82.
 // At a fine level the four lines a sample touches fill the 32 KB L1 within one
 // wave; more waves a CU evict each other's lines between the two x-neighbour
-// loads.  kEncodeLds bytes of unused LDS hold a CU to three workgroups, 12
+// loads.  kEncodeLds bytes of unused LDS (beside the counts) hold a CU to three workgroups, 12
 // waves: FP16 88 -> 80 us and 10 % fewer L2 requests against eight workgroups, FP32
 // 106 -> 103 us (two workgroups: 87 and 117).
 constexpr int kEncodeUnits = 2;
 template <class N>
-constexpr size_t kEncodeLds = N::L >= 16 ? 52000 : 0;
+constexpr size_t kEncodeLds = N::L >= 16 ? 53024 - kEncodeUnits * kEncodeLevelBins * sizeof(uint32_t) : 0;
 template <class N>
 __host__ __device__ constexpr int encode_grid(int max_samples) {
   return N::L * ((max_samples + 256 * kEncodeUnits - 1) / (256 * kEncodeUnits));

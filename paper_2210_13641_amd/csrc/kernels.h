@@ -57,7 +57,7 @@ constexpr int kBinEntries = 1 << kBinShift;
 constexpr uint32_t kChunk = 65536;            // corner additions per reduce workgroup (at most)
 constexpr int64_t kMaxTableEntries = (int64_t)1 << 25;  // all levels together
 constexpr int kUnitSamples = 256;             // samples of one level per counting / placement workgroup
-constexpr int kEncodeLevelBins = 128;         // bins of a level the counting encoding supports (2^20 entries)
+constexpr int kEncodeLevelBins = 256;         // bins of a level the counting encoding supports (2^21 entries)
 
 // The bins of the table: level l's entries [offset[l], offset[l] + size[l])
 // are cut into bins of kBinEntries entries from the level's first entry (the

@@ -727,8 +727,8 @@ def test_field_backward_of_sixteen_single_bin_levels(nsl, gpu, S):
 @pytest.mark.parametrize("S", [255, 20001])
 def test_field_backward_counts_as_the_layers_do(nsl, gpu, S, log2_table):
     """nsl_field_bwd of the 16-level field, whose encoding counts the
-    table-gradient records (2^19 entries a level; 2^21 are too many bins),
-    against nsl_encode_fwd, nsl_mlp_bwd and nsl_encode_bwd, which counts them in a
+    table-gradient records (2^19 entries a level; 2^21, which fill the 256 bins it
+    counts at most), against nsl_encode_fwd, nsl_mlp_bwd and nsl_encode_bwd, which counts them in a
     pass of its own: the weight gradients bit for bit, the table's up to the order
     of its sums."""
     import torch
