@@ -316,7 +316,7 @@ def main(argv=None):
         "roofline": roof,
         "roofline_fp32": roof_fp32,
         "rooflines": {"mixed": roofs, "fp32": roofs_fp32},
-        "recompute_encoding": {
+        "recompute_encoding": {       # (the key is older than the variant: nothing is computed twice)
             "note": "keep_encoding = 0: no room of its own for the encoding, which waits in the space of the "
                     "table-gradient records until the backward has read it",
             "mixed_samples_per_s": res["mixed"]["value"],

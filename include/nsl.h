@@ -247,8 +247,8 @@ typedef struct nsl_step_config {
   float loss_scale;
   int32_t precision;     /* NSL_PRECISION_FP32 or NSL_PRECISION_MIXED */
   float* scale_state;    /* device float[4] or NULL (static loss_scale) */
-  int32_t keep_encoding; /* 0: the backward recomputes the encoding from the table; 1: the
-                            forward keeps it in the workspace for the backward */
+  int32_t keep_encoding; /* 1: room of its own in the workspace for the encoding, which the
+                            backward reads; 0: none (above) */
 } nsl_step_config;
 
 typedef struct nsl_step_stats {
@@ -322,9 +322,10 @@ int nsl_field_fwd(const nsl_field* f, const float* params, const float* xn, cons
 
 /* Adjoint of nsl_field_fwd: accumulates (+=) dL/dparams into grads given
  * dsigma [S] and drgb [S,3].  The table part (the trilinear weights times
- * dL/de, summed over samples and corners) is written as records, grouped by
- * table bin and reduced in LDS (summation order unspecified); the weight
- * part is reduced in a fixed order. */
+ * dL/de, summed over samples and corners; summation order unspecified) is
+ * written as records, grouped by table bin and reduced in LDS, or, for tables
+ * whose levels have at most 2^13 entries each, summed in LDS without records;
+ * the weight part is reduced in a fixed order. */
 int nsl_field_bwd(const nsl_field* f, const float* params, const float* xn, const float* dirs,
                   int S, const float* dsigma, const float* drgb, float* grads, void* workspace,
                   size_t workspace_bytes, hipStream_t stream);
@@ -408,7 +409,8 @@ int nsl_loss_bwd(const float* out6, int R, const float* rgb_target, const float*
  * level-major [levels][S] float2 (FP32); each (sample, level, corner)
  * contributes w_c * dL/de, formed in FP32 (precision NSL_PRECISION_FP32) or
  * rounded to BF16 (NSL_PRECISION_MIXED, the mixed step's records), and every
- * sum is FP32.  overwrite = 0 adds to grads; overwrite = 1 sets the table
+ * sum is FP32 (FP64 in LDS for tables whose levels have at most 2^12 entries
+ * each, its parts then summed in FP32).  overwrite = 0 adds to grads; overwrite = 1 sets the table
  * part to the gradient (untouched entries become 0).  The MLP part of grads
  * is not touched.  grads and de must be 16-byte aligned; ws:
  * nsl_encode_bwd_workspace_bytes(f, S) bytes.  S * 8 * levels < 2^32.

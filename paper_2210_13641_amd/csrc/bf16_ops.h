@@ -67,7 +67,9 @@ __device__ __forceinline__ bf8 lds_bf8(const __bf16* A, int block, int lane) {
 }
 
 // ---------------------------------------------------------------------------
-// FP32 products on the BF16 matrix cores.  An FP32 value is the sum of three
+// FP32 products on the BF16 matrix cores, in the three-part form of Henry, Tang
+// and Heinecke ("Leveraging the bfloat16 artificial intelligence datatype for
+// higher-precision computations", 2019).  An FP32 value is the sum of three
 // BF16 values, x = h + m + l, each the nearest to what the ones before leave
 // (8 significant bits a part, the last error at most 2^-27 |x|), and a product
 // of two values is the six part products of 2^-18 or more: h h, h m, m h,

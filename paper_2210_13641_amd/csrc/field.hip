@@ -1,12 +1,12 @@
-// Hash-grid field on gfx950: fused encode + density/colour MLP forward, and
-// the recompute adjoint (encode, MLP forward again, MLP backward with
-// weight gradients, scatter into the table gradient).
+// Hash-grid field on gfx950: density/colour MLP forward, the recompute adjoint
+// (MLP forward again, MLP backward with weight gradients and dL/de), and fused
+// rendering.
 //
-// One wave evaluates 16 samples: lane (g, j) = (lane/16, lane%16) gathers
-// levels g, g+4, ... of sample j, which are exactly its B-operand slots of
-// the first MFMA layer (net.h).  Nothing but sigma and colour leaves the
-// forward kernel; the backward kernel re-derives every activation from the
-// sample position instead of reading stored activations.
+// One wave evaluates 16 samples: lane (g, j) = (lane/16, lane%16) takes
+// levels g, g+4, ... of sample j (given, or gathered here), which are exactly
+// its B-operand slots of the first MFMA layer (net.h).  Nothing but sigma and
+// colour leaves the forward kernel; the backward kernel computes every
+// activation again instead of reading stored ones.
 #include <algorithm>
 #include <type_traits>
 
@@ -538,8 +538,8 @@ __global__ __launch_bounds__(kFieldBwdWaves * kWave, 2) void field_bwd_kernel(Fi
 // Networks whose rendering runs on the BF16 matrix cores in three parts
 // (bf16_ops.h): the 64-wide ones, whose FP32 products would take 2.6 ms of
 // matrix cycles at 640x480 x 64 samples.  There 4.41 ms with FP32 products and
-// 3.98 so, at 320x240 1.65 and 1.60, at 160x120 0.62 and 0.61; the errors against
-// 64 bits are the same (1.0e-7).  (Training keeps FP32 products throughout: a
+// 3.98 so, at 320x240 1.65 and 1.60, at 160x120 0.62 and 0.61; the errors of the
+// outputs against 64 bits are the same with either.  (Training keeps FP32 products throughout: a
 // table entry's gradient may be a small residue of its terms, and the optimiser
 // divides it by its own size.)
 template <class N>

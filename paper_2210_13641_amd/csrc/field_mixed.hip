@@ -566,7 +566,8 @@ __device__ __forceinline__ void bwd_tile(const __bf16* __restrict__ Af, const __
 // a tile takes.  At 262k samples of the 64-wide network 46.8 us with eight
 // waves of up to 256 registers, two-byte stores to [feature][sample] rows and
 // the weights read a layer ahead, 38.6 so; at 100003 samples 26.4 and 21.6; the
-// 32-wide network at 1M samples 75.7 and 54.7.  (Eight waves with two
+// 32-wide network at 1M samples 75.7 and 54.7.  Of the 64-wide network's 128 registers
+// two values spill (12 bytes of scratch a lane).  (Eight waves with two
 // tiles each and 32x32 products, which halve the LDS reads: 48.1, 26.8, 75.0.)
 template <class N>
 __global__ __launch_bounds__(kBwdWaves * kWave) void mixed_bwd8_kernel(
