@@ -357,7 +357,10 @@ __global__ __launch_bounds__(256) void encode_levels_kernel(LevelInfo lv, const 
     if (valid[k]) store_encoding(out + (size_t)l * stride + s[k], blend_corners<sizeof(T) == 2>(table, c[k]));
   if (!hist) return;
   __shared__ uint32_t cnt[U][kEncodeLevelBins];
-  for (int i = threadIdx.x; i < U * kEncodeLevelBins; i += 256) (&cnt[0][0])[i] = 0u;
+  for (int i = threadIdx.x; i < bl.max_level_bins; i += 256) {
+#pragma unroll
+    for (int k = 0; k < U; ++k) cnt[k][i] = 0u;
+  }
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < U; ++k)
