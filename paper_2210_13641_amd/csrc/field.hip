@@ -768,6 +768,8 @@ __global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(
     u = side * bx + at - y * w4;
     v = side * by + y;
   }
+  np = __builtin_amdgcn_readfirstlane(np);
+  lg = __builtin_amdgcn_readfirstlane(lg);
   const nsl_render_request& rq = reqs[req];
   copy_to_lds<kRenderThreads, sizeof(Af)>(Af, rq.prepared);
   __syncthreads();
@@ -894,37 +896,44 @@ __global__ __launch_bounds__(kRenderThreads) __attribute__((amdgpu_waves_per_eu(
       }
     }
   };
-  if (lg == 4)
-    passes(std::true_type{});
-  else
+  // (in this order: full groups first took 0.4% longer, a launch of eight requests
+  // of the tiny field 215.9 us for 215.0)
+  if (np <= 8)
     passes(std::false_type{});
-  {
-    float s3[3] = {C0, C1, C2};
+  else
+    passes(std::true_type{});
+  // (the lane's place again, from nothing: held over the loop it would spill, and
+  // the reload costs a memory latency)
+  int lane2;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane2));
+  const int g2 = lane2 >> 4, jc2 = lane2 & 15;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      s3[i] += __shfl_xor(s3[i], 16, kWave);
-      s3[i] += __shfl_xor(s3[i], 32, kWave);
-      if (g == 0) sums[wave][i][jc] = s3[i];
-    }
-#pragma unroll
-    for (int x = 16; x <= 32; x <<= 1)
-      mo.add(Moments{__shfl_xor(mo.A, x, kWave), __shfl_xor(mo.D, x, kWave), __shfl_xor(mo.S, x, kWave)});
-    if (g == 0) moments[wave][jc] = mo;
+  for (int x = 16; x <= 32; x <<= 1) {
+    C0 += __shfl_xor(C0, x, kWave);
+    C1 += __shfl_xor(C1, x, kWave);
+    C2 += __shfl_xor(C2, x, kWave);
+    mo.add(Moments{__shfl_xor(mo.A, x, kWave), __shfl_xor(mo.D, x, kWave), __shfl_xor(mo.S, x, kWave)});
+  }
+  if (g2 == 0) {
+    sums[wave][0][jc2] = C0;
+    sums[wave][1][jc2] = C1;
+    sums[wave][2][jc2] = C2;
+    moments[wave][jc2] = mo;
   }
   __syncthreads();
-  if (wave != 0 || g != 0 || jc >= np) return;
+  if (wave != 0 || g2 != 0 || jc2 >= np) return;
   C0 = C1 = C2 = 0.0f;
   mo = Moments{0.0, 0.0, 0.0};
 #pragma unroll
   for (int w = 0; w < kRenderWaves; ++w) {
     const float(*p)[16] = sums[w];
-    C0 += p[0][jc];
-    C1 += p[1][jc];
-    C2 += p[2][jc];
-    mo.add(moments[w][jc]);
+    C0 += p[0][jc2];
+    C1 += p[1][jc2];
+    C2 += p[2][jc2];
+    mo.add(moments[w][jc2]);
   }
-  const size_t px = px_of[jc];
-  s = scale_of[jc];
+  const size_t px = px_of[jc2];
+  s = scale_of[jc2];
   rq.rgb[3 * px] = C0;
   rq.rgb[3 * px + 1] = C1;
   rq.rgb[3 * px + 2] = C2;
